@@ -13,7 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libccmi.so")
 STRESS_LIB = os.path.join(PKG, "libccmi_stress.so")
-SOURCES = ["cc_api.hip", "cc_kernels.hip", "cc_tiled.hip", "cc_batch.hip", "cc_serve.hip",
+SOURCES = ["cc_api.hip", "cc_kernels.hip", "cc_tiled.hip", "cc_filter.hip", "cc_batch.hip", "cc_serve.hip",
            "cc_exchange.hip", "cc_wide.hip", "cc_noalloc.hip", "cc_tune.hip"]
 
 HIPCC_FLAGS = [

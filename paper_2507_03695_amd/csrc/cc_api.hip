@@ -72,7 +72,8 @@ int slot_create(Slot* s, int device, uint32_t samples) {
     s->table = next_pow2(4ull * samples);
     if (s->table < 1024) s->table = 1024;
     CCM_HIP(hipSetDevice(device));
-    size_t bytes = sizeof(DevState) + (2ull * s->table + 5ull * kGridCap + 2) * sizeof(uint32_t);
+    size_t bytes = sizeof(DevState) + (2ull * s->table + 5ull * kGridCap + 2) * sizeof(uint32_t) +
+                   256 + lds_bits_max_n() / 8;
     char* base = nullptr;
     hipError_t e = hipMalloc(&base, bytes);
     if (e != hipSuccess) {
@@ -84,6 +85,8 @@ int slot_create(Slot* s, int device, uint32_t samples) {
     s->hcounts = s->hkeys + s->table;
     s->bmin = s->hcounts + s->table;
     s->xs = s->bmin + kGridCap;
+    s->gbits = reinterpret_cast<uint32_t*>(
+        ((uintptr_t)(s->xs + 4ull * kGridCap + 2) + 255) & ~(uintptr_t)255);
     CCM_HIP(hipMemset(s->st, 0, sizeof(DevState)));
     // one 64-byte block: the status word, or a 64-bit value read back by an entry point
     e = hipHostMalloc(&s->host_status, 64, hipHostMallocDefault);
@@ -659,7 +662,7 @@ extern "C" int cc_get_zroot(cc_ctx* ctx, void* stream, uint32_t* zroot_out) {
     int rc = set_dev(ctx);
     if (rc) return rc;
     if ((rc = cohere((hipStream_t)stream))) return rc;
-    CCM_HIP(hipMemcpyAsync(ctx->slot.host_status, &ctx->slot.st->zroot, sizeof(uint32_t),
+    CCM_HIP(hipMemcpyAsync(ctx->slot.host_status, &ctx->slot.st->zpub, sizeof(uint32_t),
                            hipMemcpyDeviceToHost, (hipStream_t)stream));
     CCM_HIP(hipStreamSynchronize((hipStream_t)stream));
     *zroot_out = *ctx->slot.host_status;

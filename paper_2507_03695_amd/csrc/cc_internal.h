@@ -20,9 +20,10 @@ namespace ccm {
 // only through explicit copies.
 struct DevState {
     uint32_t status;    // kStatus* bits, reported and cleared by slot_sync
-    uint32_t minz;      // smallest member of the zero root's component (compress, k_minz)
-    uint32_t zroot;     // the zero root chosen for the current solve
-    uint32_t pad0;
+    uint32_t zroot;     // the root whose component the bitmap describes: the zero root,
+                        // or the giant component's root of a plain whole solve
+    uint32_t zpub;      // the zero root chosen by the latest cc_zroot (cc_get_zroot, cc_canon)
+    uint32_t mpub;      // smallest member of zpub's component (zero-root compress; cc_canon)
     uint64_t zsel;      // packed argmax (count << 32) | (0xFFFFFFFF - id); 0 = none
     uint64_t log_count; // messages of a drained update log (cc_hook_log_drain)
     uint64_t pad1[4];
@@ -103,6 +104,9 @@ struct Slot {
     // Zero-root membership bitmap: bit x set => x is in the zero root's tree.
     uint32_t* zbits = nullptr;     // device, ceil(n/32) words (grown on demand)
     uint64_t zbits_cap = 0;        // words
+    // Bitmap of a plain whole solve's giant component (cc_filter.hip), for arrays
+    // of at most lds_bits_max_n() vertices.
+    uint32_t* gbits = nullptr;
     // Host-side order of the steps: a CC_F_ZROOT hook needs cc_zroot after the
     // latest cc_init on the same n (the bitmap describes that solve).
     uint64_t cur_n = 0;
@@ -214,6 +218,20 @@ void tiled_free(TiledScratch* t);
 // The same on CSR input, where the rows already are the first-endpoint buckets.
 int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
                        uint32_t* P, hipStream_t stream, bool sym = false);
+
+// Hooks that test a bitmap in LDS (cc_filter.hip).
+// Largest n whose whole bitmap fits a workgroup's LDS.
+uint64_t lds_bits_max_n();
+// The bitmap of one root's component, from a flat forest: the zero root's, or
+// (pick) that of the root most often seen above sampled endpoints.
+int run_giant_bits(uint64_t n, uint64_t m, const uint32_t* edges, const uint32_t* P, uint32_t* zbits,
+                   DevState* st, bool pick, hipStream_t stream);
+// About `want` entries hooked in P (no bitmap), spread evenly over the list.
+int run_warm(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, DevState* st, bool zr,
+             bool split, bool sym, uint64_t want, hipStream_t stream);
+// Every entry tested against the whole bitmap in LDS, the rest hooked in P.
+int run_hook_lds(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, uint32_t* zbits,
+                 DevState* st, bool split, bool sym, int device, hipStream_t stream);
 
 // Batched path (cc_batch.hip).
 // The schedule taken when nothing else is known about a batch.

@@ -19,20 +19,13 @@
 #include <algorithm>
 
 #include "cc_internal.h"
+#include "cc_link.h"
 
 namespace ccm {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBlock = 256;
-
-// ---- keys: Formula 1's R used as an order while P stores vertex IDs ----------
-// key(x) = x on the plain path; with a zero root z, key(z) = 0 and key(x) = x+1.
-template <bool ZR>
-__device__ __forceinline__ bool key_less(uint32_t a, uint32_t b, uint32_t z) {
-    if (ZR) return (a == z) | ((b != z) & (a < b));
-    return a < b;
-}
 
 // ---- init --------------------------------------------------------------------
 // P_v = v (Algorithm 1 / 3 initialisation; with R the stored values stay vertex
@@ -42,7 +35,7 @@ __global__ __launch_bounds__(kBlock) void k_init(uint32_t* __restrict__ P, uint6
                                                  DevState* st) {
     const uint64_t tid = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-    if (tid == 0) st_agent(&st->minz, kEmpty);
+    if (tid == 0) st_agent(&st->mpub, kEmpty);
     for (uint64_t v = tid; v < n; v += stride) st_agent(&P[v], (uint32_t)v);
 }
 
@@ -58,7 +51,10 @@ __global__ __launch_bounds__(kBlock) void k_zfill(uint32_t* keys, uint32_t* coun
                                                   DevState* st) {
     uint32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) st_agent64(&st->zsel, 0);
-    for (; i < T; i += gridDim.x * kBlock) { keys[i] = kEmpty; counts[i] = 0; }
+    for (; i < T; i += gridDim.x * kBlock) {
+        st_agent(&keys[i], kEmpty);
+        st_agent(&counts[i], 0u);
+    }
 }
 
 __device__ __forceinline__ void table_add(uint32_t* keys, uint32_t* counts, uint32_t mask,
@@ -94,7 +90,7 @@ __global__ __launch_bounds__(kBlock) void k_zcount(const uint32_t* __restrict__ 
 __global__ __launch_bounds__(kBlock) void k_degfill(uint32_t* deg, uint64_t n, DevState* st) {
     uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) st_agent64(&st->zsel, 0);
-    for (; i < n; i += (uint64_t)gridDim.x * kBlock) deg[i] = 0;
+    for (; i < n; i += (uint64_t)gridDim.x * kBlock) st_agent(&deg[i], 0u);
 }
 
 __global__ __launch_bounds__(kBlock) void k_degcount(const uint32_t* __restrict__ edges, uint64_t m,
@@ -111,22 +107,6 @@ __global__ __launch_bounds__(kBlock) void k_degcount(const uint32_t* __restrict_
 
 __device__ __forceinline__ uint64_t pack_sel(uint32_t count, uint32_t id) {
     return count ? ((uint64_t)count << 32) | (uint64_t)(0xFFFFFFFFu - id) : 0;
-}
-
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x) {
-    for (int off = 32; off > 0; off >>= 1) {
-        uint64_t y = __shfl_xor(x, off, 64);
-        x = y > x ? y : x;
-    }
-    return x;
-}
-
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
-    for (int off = 32; off > 0; off >>= 1) {
-        uint32_t y = __shfl_xor(x, off, 64);
-        x = y < x ? y : x;
-    }
-    return x;
 }
 
 // argmax over (count desc, id asc); ids come from a table (keys != nullptr) or
@@ -163,6 +143,7 @@ __global__ void k_zfinish(DevState* st, int use_hint, uint32_t hint) {
             z = s ? 0xFFFFFFFFu - (uint32_t)(s & 0xFFFFFFFFu) : 0u;
         }
         st_agent(&st->zroot, z);
+        st_agent(&st->zpub, z);
     }
 }
 
@@ -197,95 +178,10 @@ __global__ __launch_bounds__(kBlock) void k_zbits_clear(uint32_t* zbits, uint64_
     const uint64_t zw = z >> 5;
     for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < words;
          i += (uint64_t)gridDim.x * kBlock)
-        zbits[i] = (i == zw) ? (1u << (z & 31)) : 0u;
+        st_agent(&zbits[i], (i == zw) ? (1u << (z & 31)) : 0u);
 }
 
 // ---- hook ---------------------------------------------------------------------
-
-// Root of x, given px = a value read from P[x]. SPLIT = 1: path splitting (each
-// visited vertex takes its grandparent); SPLIT = 0: plain walk.
-// The splitting writes are device-coherent stores. A plain store would leave a
-// dirty line in the writing XCD's L2 whose other words are that XCD's copies;
-// links are CASes performed at the memory side, which that copy does not see,
-// so the line's write-back can undo a link made meanwhile in the same line (a
-// whole-device batch lost links this way). Each store is issued after the next
-// step's load, so that its latency overlaps the walk instead of adding to it.
-template <int SPLIT>
-__device__ __forceinline__ uint32_t find_root(uint32_t* P, uint32_t x, uint32_t px) {
-    if (px == x) return x;
-    uint32_t gp = P[px];
-    while (gp != px) {
-        const uint32_t ggp = P[gp];
-        if (SPLIT) {
-            stress_delay(x);
-            st_agent(&P[x], gp);
-        }
-        x = px;
-        px = gp;
-        gp = ggp;
-    }
-    return px;
-}
-
-// The check before each link's CAS. Global atomics are performed at the memory
-// side, past the XCD's L2, and leave the L2's copy of the word as it was; a
-// walk that reads P through the L2 can therefore end at a root that has since
-// been linked. A CAS on such an entry fails, but only after its round trip, and
-// every CAS on one word waits for the ones before it: a giant component's
-// former root collects thousands (ER n = 2^16, 2^20 entries: 16,000 CAS on one
-// word, a 1.6 ms hook). The entry is read coherently first (a load, which does
-// not wait behind the CASes) and a changed entry continues the walk from its
-// new value; the CAS is issued only on an entry that still reads as a root.
-// ER n = 2^16, 2^20 entries: 1.7 M CAS -> 0.11 M, 1.6-3.4 ms -> 0.16 ms.
-// Algorithm 1 / 3 hooking of one entry whose endpoints u, v have parents pu, pv.
-// Returns the root under which both endpoints ended up (the surviving root of
-// the link, or the common root found). When it is the zero root z, both
-// endpoints are certainly in z's tree: z has the smallest key and is never
-// linked under anything. If this call's CAS is the one that links, *linked
-// (when given) receives the root that was linked; the return value is then its
-// new parent.
-template <bool ZR, int SPLIT>
-__device__ __forceinline__ uint32_t link(uint32_t* P, uint32_t u, uint32_t pu, uint32_t v,
-                                         uint32_t pv, uint32_t z, uint32_t* linked = nullptr) {
-    while (true) {
-        const uint32_t ru = find_root<SPLIT>(P, u, pu);
-        const uint32_t rv = find_root<SPLIT>(P, v, pv);
-        if (ru == rv) return ru;
-        const bool u_low = key_less<ZR>(ru, rv, z);
-        const uint32_t hi = u_low ? rv : ru;
-        const uint32_t lo = u_low ? ru : rv;
-        stress_delay(hi);
-        // hi's entry read coherently first (the check described above)
-        const uint32_t cur = ld_agent(&P[hi]);
-        if (cur != hi) {
-            u = hi; pu = cur;
-            v = lo; pv = lo;
-            continue;
-        }
-        const uint32_t old = atomicCAS(&P[hi], hi, lo);
-        if (old == hi) {
-            if (linked) *linked = hi;
-            return lo;
-        }
-        // hi was linked by someone else: its current parent is `old`
-        u = hi; pu = old;
-        v = lo; pv = lo;
-    }
-}
-
-__device__ __forceinline__ bool zbit(const uint32_t* zbits, uint32_t x) {
-    return (zbits[x >> 5] >> (x & 31)) & 1u;
-}
-
-// Sets x's bit. The word is read coherently first and the atomic (performed at
-// the memory side, where the atomics on one word wait for each other) is issued
-// only if the bit is still clear: most of a giant component's members are
-// reached by many entries, and their word would otherwise take an atomic for
-// each (bits only go from 0 to 1, so a set bit read anywhere stays set).
-__device__ __forceinline__ void zbit_set(uint32_t* zbits, uint32_t x) {
-    const uint32_t b = 1u << (x & 31);
-    if (!(ld_agent(&zbits[x >> 5]) & b)) atomicOr(&zbits[x >> 5], b);
-}
 
 constexpr int kEPT = 4;  // entries per thread per tile
 
@@ -655,8 +551,8 @@ __global__ __launch_bounds__(kBlock) void k_csr_hook(const uint64_t* __restrict_
 // cc_tiled.hip), so a tree that holds a marked vertex belongs to z's component.
 // Here every marked vertex passes its mark on to its root; k_resolve then
 // relabels the members of marked trees.
-// The same pass finds the smallest member of z's component (minz, reduced over
-// the blocks by k_minz). Outside z's tree every tree is rooted at its smallest
+// The same pass finds the smallest member of z's component (per block;
+// k_resolve reduces the blocks' minima). Outside z's tree every tree is rooted at its smallest
 // ID (its keys are the IDs), so the candidates are: each member of z's tree
 // (z included), each root whose own bit is set, and the root of each marked
 // vertex. A root whose bit is set during this pass is the root of a marked
@@ -672,6 +568,7 @@ __global__ __launch_bounds__(kBlock) void k_compress(uint32_t* P, uint64_t n, De
     const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     uint32_t local_min = kEmpty;
+    uint32_t passed = kEmpty;                 // root this thread last passed a mark to
     for (uint64_t v0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v0 < n; v0 += kVPT * stride) {
         uint32_t pv[kVPT], bw[kVPT];
 #pragma unroll
@@ -686,6 +583,7 @@ __global__ __launch_bounds__(kBlock) void k_compress(uint32_t* P, uint64_t n, De
         const uint32_t p = pv[i];
         uint32_t r = (uint32_t)v;
         const bool marked = ZR && ((bw[i] >> (v & 31)) & 1u);
+        uint32_t pass = kEmpty;               // root to pass v's mark to
         if (ZR && v < n && p == (uint32_t)v && ((uint32_t)v == z || marked))
             local_min = min(local_min, (uint32_t)v);
         if (v < n && p != (uint32_t)v) {
@@ -702,14 +600,27 @@ __global__ __launch_bounds__(kBlock) void k_compress(uint32_t* P, uint64_t n, De
             if (ZR && r == z) {
                 local_min = min(local_min, (uint32_t)v);
             } else if (marked) {
-                zbit_set(zbits, r);
+                pass = r;
                 local_min = min(local_min, r);
+            }
+        }
+        if (ZR) {
+            // one lane per distinct root passes the mark: the members of a marked
+            // tree share it, and a coherent read of its word by every one of them
+            // serialises (ER n = 1.1 M, 2.5 M entries: pass 210 -> 60 us)
+            uint64_t left = __ballot(pass != kEmpty && pass != passed);
+            while (left) {
+                const int l = __ffsll((unsigned long long)left) - 1;
+                const uint32_t first = __shfl(pass, l, 64);
+                if ((int)(threadIdx.x & 63) == l) zbit_set(zbits, first);
+                if (pass == first) passed = first;
+                left &= ~__ballot(pass == first);
             }
         }
         }
     }
     if (ZR) {
-        // one value per block; k_minz reduces them (one atomic per block on a
+        // one value per block; k_resolve reduces them (one atomic per block on a
         // single word would serialise)
         __shared__ uint32_t s_min[kBlock / 64];
         local_min = wave_min_u32(local_min);
@@ -718,20 +629,34 @@ __global__ __launch_bounds__(kBlock) void k_compress(uint32_t* P, uint64_t n, De
         if (threadIdx.x == 0) {
             uint32_t b = s_min[0];
             for (int w = 1; w < kBlock / 64; ++w) b = min(b, s_min[w]);
-            bmin[blockIdx.x] = b;
+            st_agent(&bmin[blockIdx.x], b);
         }
     }
 }
 
-// Zero root only, after k_compress and k_minz: every member of z's component
-// (its root is z, or v or its root is marked) gets the label z, or with FINAL
-// the component's smallest ID minz at once (no k_canon pass needed). Marks are
-// read coherently: they were set by atomics.
+// Zero root only, after k_compress: every member of z's component (its root is
+// z, or v or its root is marked) gets the label z, or with FINAL the component's
+// smallest ID at once (no k_canon pass needed). Every block reduces compress's
+// nb <= kZrGrid per-block minima for itself (8 KB; a launch of its own for that
+// cost 5 us); block 0 records the result. Marks are read coherently: they were
+// set by atomics.
 template <bool FINAL>
 __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t* P, uint64_t n, DevState* st,
-                                                    const uint32_t* zbits) {
+                                                    const uint32_t* zbits, const uint32_t* bmin,
+                                                    uint32_t nb, int pub) {
+    __shared__ uint32_t s_min[kBlock / 64];
     const uint32_t z = ld_agent(&st->zroot);
-    const uint32_t lab = FINAL ? ld_agent(&st->minz) : z;
+    uint32_t lab = z;
+    if (FINAL || blockIdx.x == 0) {
+        uint32_t x = kEmpty;
+        for (uint32_t i = threadIdx.x; i < nb; i += kBlock) x = min(x, ld_agent(&bmin[i]));
+        x = wave_min_u32(x);
+        if ((threadIdx.x & 63) == 0) s_min[threadIdx.x >> 6] = x;
+        __syncthreads();
+        for (int w = 0; w < kBlock / 64; ++w) x = min(x, s_min[w]);
+        if (FINAL) lab = x;
+        if (pub && blockIdx.x == 0 && threadIdx.x == 0) st_agent(&st->mpub, x);
+    }
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t v0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v0 < n; v0 += kVPT * stride) {
         uint32_t rr[kVPT], bv[kVPT];
@@ -754,24 +679,9 @@ __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t* P, uint64_t n, Dev
     }
 }
 
-// minz = the smallest of the per-block minima (one block).
-__global__ __launch_bounds__(1024) void k_minz(const uint32_t* __restrict__ bmin, uint32_t nb,
-                                               DevState* st) {
-    __shared__ uint32_t s_min[1024 / 64];
-    uint32_t x = kEmpty;
-    for (uint32_t i = threadIdx.x; i < nb; i += 1024) x = min(x, bmin[i]);
-    x = wave_min_u32(x);
-    if ((threadIdx.x & 63) == 0) s_min[threadIdx.x >> 6] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 1024 / 64; ++w) x = min(x, s_min[w]);
-        st_agent(&st->minz, x);
-    }
-}
-
 // ---- relabel the zero root's component to its smallest ID ---------------------------
 __global__ __launch_bounds__(kBlock) void k_canon(uint32_t* L, uint64_t n, const DevState* st) {
-    const uint32_t z = ld_agent(&st->zroot), mz = ld_agent(&st->minz);
+    const uint32_t z = ld_agent(&st->zpub), mz = ld_agent(&st->mpub);
     if (mz == z || mz == kEmpty) return;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     for (uint64_t v0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x; v0 < n; v0 += kVPT * stride) {
@@ -821,6 +731,24 @@ int run_init(Slot* s, uint64_t n, uint32_t* P, hipStream_t stream) {
     return CC_OK;
 }
 
+// Whether the hook tests every entry against the whole bitmap in LDS
+// (cc_filter.hip) instead of hooking each in P. It needs a sample, two more
+// passes over P and the bitmap, about 40 us in all, and drops little where the
+// sample (n entries at most) leaves no giant component. Whole solves, direct
+// against LDS (us): R-MAT n = 2^16, 2^20 entries 128 against 120 (plain); n =
+// 1,000,003, 15 M entries 924 against 258 (zero root), 511 against 262 (plain);
+// ER n = 1.1 M, 2.5 M entries (zero root) 1172 against 621.
+static bool lds_eligible(uint64_t n, uint64_t m) {
+    return n <= lds_bits_max_n() && m >= (1ull << 18) && m >= 2 * n;
+}
+// Entries of the sample: one per vertex (R-MAT n = 1,000,003, 15 M entries, whole
+// solve with n/4, n/2, n and 2n: 341, 283, 254, 271 us), at most a quarter of all.
+static uint64_t warm_entries(uint64_t n, uint64_t m) { return std::min<uint64_t>(m / 4, n); }
+// Internal flag of run_compress: the bitmap is the giant component's of a plain solve.
+constexpr uint32_t kGiant = 0x40000000u;
+// Blocks of the zero root's compress and resolve (8 per CU).
+constexpr uint32_t kZrGrid = 2048;
+
 static uint64_t sample_count(uint64_t m, uint64_t K) { return m <= K ? m : K; }
 
 // Size the membership bitmap for n vertices and clear it (only z set). Marks the
@@ -842,8 +770,6 @@ int zbits_reset(Slot* s, uint64_t n, hipStream_t stream) {
     }
     k_zbits_clear<<<grid_for(words, kBlock, kGridCap), kBlock, 0, stream>>>(s->zbits, words, s->st);
     CCM_HIP(hipGetLastError());
-    int rcc = cohere(stream);       // cleared words written back before push's atomics
-    if (rcc) return rcc;
     s->zr_ready = (n == s->cur_n);
     return CC_OK;
 }
@@ -870,8 +796,6 @@ int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t f
             s->deg_cap = n;
         }
         k_degfill<<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(s->deg, n, s->st);
-        int rcc = cohere(stream);   // zero-filled lines written back before the atomics
-        if (rcc) return rcc;
         if (m) k_degcount<<<grid_for(m, kBlock, kGridCap), kBlock, 0, stream>>>(edges, m, n, s->deg, s->st);
         k_zargmax<<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(nullptr, s->deg, n, s->st);
     } else {
@@ -879,8 +803,6 @@ int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t f
         const uint64_t cnt = sample_count(m, K);
         k_zfill<<<grid_for(s->table, kBlock, 1024), kBlock, 0, stream>>>(s->hkeys, s->hcounts,
                                                                           s->table, s->st);
-        int rcc = cohere(stream);   // filled lines written back before the atomics
-        if (rcc) return rcc;
         if (cnt)
             k_zcount<<<grid_for(cnt, kBlock, 1024), kBlock, 0, stream>>>(
                 edges, m, K, cnt, n, s->hkeys, s->hcounts, s->table - 1, s->st);
@@ -922,33 +844,29 @@ int run_hook(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
     uint32_t* zb = s->zbits;
     const uint32_t g = (uint32_t)blocks;
     const bool linkz = hook_links_z(flags, n);
-    if (!(flags & CC_F_NO_SPLIT) && hook_in_two_parts(n, m, split)) {
-        // in two parts (whole solves, ER n = 2^16 with 2^20 entries: plain 0.150
-        // -> 0.115 ms; the zero-root hook alone 0.266 -> 0.198 ms). With a zero
-        // root the pass between is compress's: trees pointer-jumped and the
-        // roots of marked vertices marked, which the rest of the hook reads as
-        // connections to z like any other mark.
+    if (zr && !(flags & CC_F_NO_SPLIT) && lds_eligible(n, m)) {
+        int rc = run_warm(n, m, edges, P, s->st, true, split, sym != 0, warm_entries(n, m), stream);
+        if (rc) return rc;
+        k_compress<true><<<grid_for(n, kBlock, kZrGrid), kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin);
+        CCM_HIP(hipGetLastError());
+        if ((rc = run_giant_bits(n, m, edges, P, zb, s->st, false, stream))) return rc;
+        return run_hook_lds(n, m, edges, P, zb, s->st, split, sym != 0, s->device, stream);
+    }
+    if (!zr && !(flags & CC_F_NO_SPLIT) && hook_in_two_parts(n, m, split)) {
+        // in two parts (ER n = 2^16 with 2^20 entries, whole solve: 0.150 -> 0.115 ms)
         const uint64_t m1 = m / 4;
         const uint32_t g1 = (uint32_t)((m1 + per - 1) / per);
         const uint32_t g2 = (uint32_t)((m - m1 + per - 1) / per);
-        const uint32_t gn = grid_for(n, kBlock, kGridCap);
-        for (int part = 0; part < 2; ++part) {
-            const uint32_t* e = part ? edges + 2 * m1 : edges;
-            const uint64_t mp = part ? m - m1 : m1;
-            const uint32_t gp = part ? g2 : g1;
-            if (!zr) k_hook<false, 0><<<gp, kBlock, 0, stream>>>(e, mp, n32, P, zb, s->st, sym);
-            else if (linkz)
-                k_hook<true, 0, false, true><<<gp, kBlock, 0, stream>>>(e, mp, n32, P, zb, s->st, sym);
-            else k_hook<true, 0><<<gp, kBlock, 0, stream>>>(e, mp, n32, P, zb, s->st, sym);
-            CCM_HIP(hipGetLastError());
-            if (part) break;
-            int rc = cohere(stream);
-            if (rc) return rc;
-            if (zr) k_compress<true><<<gn, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin);
-            else k_compress<false><<<gn, kBlock, 0, stream>>>(P, n, s->st, nullptr, nullptr);
-            CCM_HIP(hipGetLastError());
-            if ((rc = cohere(stream))) return rc;
-        }
+        k_hook<false, 0><<<g1, kBlock, 0, stream>>>(edges, m1, n32, P, zb, s->st, sym);
+        CCM_HIP(hipGetLastError());
+        int rc = cohere(stream);
+        if (rc) return rc;
+        k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, s->st, nullptr,
+                                                                             nullptr);
+        CCM_HIP(hipGetLastError());
+        if ((rc = cohere(stream))) return rc;
+        k_hook<false, 0><<<g2, kBlock, 0, stream>>>(edges + 2 * m1, m - m1, n32, P, zb, s->st, sym);
+        CCM_HIP(hipGetLastError());
         return CC_OK;
     }
     if (zr && linkz && split)
@@ -1009,22 +927,20 @@ int log_count_snap(Slot* s, uint64_t* host_word, hipStream_t stream) {
 
 int run_compress(Slot* s, uint64_t n, uint32_t* P, uint32_t flags, hipStream_t stream,
                  bool final_labels) {
-    const uint32_t g = grid_for(n, kBlock, kGridCap);
+    uint32_t* zb = (flags & kGiant) ? s->gbits : s->zbits;
     final_labels = final_labels || (flags & CC_F_CANON);
     if (flags & CC_F_ZROOT) {
-        if (!s->zr_ready || s->cur_n != n)
+        const int pub = !(flags & kGiant);
+        if (pub && (!s->zr_ready || s->cur_n != n))
             return fail(CC_EINVAL, "a CC_F_ZROOT compress needs cc_init then cc_zroot on the same n");
-        k_compress<true><<<g, kBlock, 0, stream>>>(P, n, s->st, s->zbits, s->bmin);
+        const uint32_t g = grid_for(n, kBlock, kZrGrid);
+        k_compress<true><<<g, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin);
         CCM_HIP(hipGetLastError());
-        int rc = cohere(stream);
-        if (rc) return rc;
-        k_minz<<<1, 1024, 0, stream>>>(s->bmin, g, s->st);
-        CCM_HIP(hipGetLastError());
-        if ((rc = cohere(stream))) return rc;
-        if (final_labels) k_resolve<true><<<g, kBlock, 0, stream>>>(P, n, s->st, s->zbits);
-        else k_resolve<false><<<g, kBlock, 0, stream>>>(P, n, s->st, s->zbits);
+        if (final_labels) k_resolve<true><<<g, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin, g, pub);
+        else k_resolve<false><<<g, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin, g, pub);
     } else {
-        k_compress<false><<<g, kBlock, 0, stream>>>(P, n, s->st, nullptr, nullptr);
+        k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, s->st, nullptr,
+                                                                             nullptr);
     }
     CCM_HIP(hipGetLastError());
     return CC_OK;
@@ -1145,7 +1061,6 @@ int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const ui
         else k_csr_hook<false, 0><<<g, kBlock, 0, stream>>>(off, adj, n32, m, s->csr_tiles, ntiles, L, zb, s->st, sym);
         CCM_HIP(hipGetLastError());
     }
-    if ((rc = cohere(stream))) return rc;
     if ((rc = run_compress(s, n, L, flags, stream, true))) return rc;
     return cohere(stream);
 }
@@ -1204,6 +1119,22 @@ void slot_return_scratch(Slot* s, const LentScratch* saved) {
     s->zr_ready = false;
 }
 
+// The hook of a plain whole solve whose bitmap fits LDS: a sample hooked by
+// Algorithm 1, pointer jumping, the bitmap of the giant component's root, every
+// entry against it. From there on the giant component's root plays the zero
+// root's part (it is a root, so its key can become the smallest one).
+static int run_hook_giant(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P,
+                          uint32_t flags, hipStream_t stream) {
+    const bool split = split_walks(flags, n);
+    const bool sym = flags & CC_F_SYMMETRIC;
+    int rc = run_warm(n, m, edges, P, s->st, false, split, sym, warm_entries(n, m), stream);
+    if (rc) return rc;
+    k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, s->st, nullptr, nullptr);
+    CCM_HIP(hipGetLastError());
+    if ((rc = run_giant_bits(n, m, edges, P, s->gbits, s->st, true, stream))) return rc;
+    return run_hook_lds(n, m, edges, P, s->gbits, s->st, split, sym, s->device, stream);
+}
+
 int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* L,
               uint32_t flags, uint32_t hint, hipStream_t stream) {
     if (n == 0) return CC_OK;
@@ -1214,8 +1145,13 @@ int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* 
         if ((rc = run_push(s, n, m, edges, L, stream))) return rc;
     }
     if ((rc = cohere(stream))) return rc;
-    if ((rc = run_hook(s, n, m, edges, L, flags, stream))) return rc;
-    if ((rc = cohere(stream))) return rc;
+    const bool giant = !(flags & (CC_F_ZROOT | CC_F_NO_SPLIT)) && lds_eligible(n, m);
+    if (giant) {
+        if ((rc = run_hook_giant(s, n, m, edges, L, flags, stream))) return rc;
+        flags |= CC_F_ZROOT | kGiant;
+    } else if ((rc = run_hook(s, n, m, edges, L, flags, stream))) {
+        return rc;
+    }
     if ((rc = run_compress(s, n, L, flags, stream, true))) return rc;
     return cohere(stream);
 }

@@ -1,0 +1,114 @@
+// cc_link.h — device helpers shared by the single-graph kernels: the key order,
+// the finds, the link, membership marks and wave reductions.
+#pragma once
+
+#include "cc_internal.h"
+
+namespace ccm {
+
+// ---- keys: Formula 1's R used as an order while P stores vertex IDs ----------
+// key(x) = x on the plain path; with a zero root z, key(z) = 0 and key(x) = x+1.
+template <bool ZR>
+__device__ __forceinline__ bool key_less(uint32_t a, uint32_t b, uint32_t z) {
+    if (ZR) return (a == z) | ((b != z) & (a < b));
+    return a < b;
+}
+
+// Root of x, given px = a value read from P[x]. SPLIT = 1: path splitting (each
+// visited vertex takes its grandparent); SPLIT = 0: plain walk.
+// The splitting writes are device-coherent stores. A plain store would leave a
+// dirty line in the writing XCD's L2 whose other words are that XCD's copies;
+// links are CASes performed at the memory side, which that copy does not see,
+// so the line's write-back can undo a link made meanwhile in the same line (a
+// whole-device batch lost links this way). Each store is issued after the next
+// step's load, so that its latency overlaps the walk instead of adding to it.
+template <int SPLIT>
+__device__ __forceinline__ uint32_t find_root(uint32_t* P, uint32_t x, uint32_t px) {
+    if (px == x) return x;
+    uint32_t gp = P[px];
+    while (gp != px) {
+        const uint32_t ggp = P[gp];
+        if (SPLIT) {
+            stress_delay(x);
+            st_agent(&P[x], gp);
+        }
+        x = px;
+        px = gp;
+        gp = ggp;
+    }
+    return px;
+}
+
+// The check before each link's CAS. Global atomics are performed at the memory
+// side, past the XCD's L2, and leave the L2's copy of the word as it was; a
+// walk that reads P through the L2 can therefore end at a root that has since
+// been linked. A CAS on such an entry fails, but only after its round trip, and
+// every CAS on one word waits for the ones before it: a giant component's
+// former root collects thousands (ER n = 2^16, 2^20 entries: 16,000 CAS on one
+// word, a 1.6 ms hook). The entry is read coherently first (a load, which does
+// not wait behind the CASes) and a changed entry continues the walk from its
+// new value; the CAS is issued only on an entry that still reads as a root.
+// ER n = 2^16, 2^20 entries: 1.7 M CAS -> 0.11 M, 1.6-3.4 ms -> 0.16 ms.
+// Algorithm 1 / 3 hooking of one entry whose endpoints u, v have parents pu, pv.
+// Returns the root under which both endpoints ended up (the surviving root of
+// the link, or the common root found). When it is the zero root z, both
+// endpoints are certainly in z's tree: z has the smallest key and is never
+// linked under anything. If this call's CAS is the one that links, *linked
+// (when given) receives the root that was linked; the return value is then its
+// new parent.
+template <bool ZR, int SPLIT>
+__device__ __forceinline__ uint32_t link(uint32_t* P, uint32_t u, uint32_t pu, uint32_t v,
+                                         uint32_t pv, uint32_t z, uint32_t* linked = nullptr) {
+    while (true) {
+        const uint32_t ru = find_root<SPLIT>(P, u, pu);
+        const uint32_t rv = find_root<SPLIT>(P, v, pv);
+        if (ru == rv) return ru;
+        const bool u_low = key_less<ZR>(ru, rv, z);
+        const uint32_t hi = u_low ? rv : ru;
+        const uint32_t lo = u_low ? ru : rv;
+        stress_delay(hi);
+        // hi's entry read coherently first (the check described above)
+        const uint32_t cur = ld_agent(&P[hi]);
+        if (cur != hi) {
+            u = hi; pu = cur;
+            v = lo; pv = lo;
+            continue;
+        }
+        const uint32_t old = atomicCAS(&P[hi], hi, lo);
+        if (old == hi) {
+            if (linked) *linked = hi;
+            return lo;
+        }
+        // hi was linked by someone else: its current parent is `old`
+        u = hi; pu = old;
+        v = lo; pv = lo;
+    }
+}
+
+// Sets x's bit. The word is read coherently first and the atomic (performed at
+// the memory side, where the atomics on one word wait for each other) is issued
+// only if the bit is still clear: most of a giant component's members are
+// reached by many entries, and their word would otherwise take an atomic for
+// each (bits only go from 0 to 1, so a set bit read anywhere stays set).
+__device__ __forceinline__ void zbit_set(uint32_t* zbits, uint32_t x) {
+    const uint32_t b = 1u << (x & 31);
+    if (!(ld_agent(&zbits[x >> 5]) & b)) atomicOr(&zbits[x >> 5], b);
+}
+
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x) {
+    for (int off = 32; off > 0; off >>= 1) {
+        uint64_t y = __shfl_xor(x, off, 64);
+        x = y > x ? y : x;
+    }
+    return x;
+}
+
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
+    for (int off = 32; off > 0; off >>= 1) {
+        uint32_t y = __shfl_xor(x, off, 64);
+        x = y < x ? y : x;
+    }
+    return x;
+}
+
+}  // namespace ccm

@@ -53,8 +53,9 @@ static int scratch_of(int dev, char** out) {
 __global__ void k_na_reset(DevState* st) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         st_agent(&st->status, 0u);
-        st_agent(&st->minz, kEmpty);
         st_agent(&st->zroot, 0u);
+        st_agent(&st->zpub, 0u);
+        st_agent(&st->mpub, kEmpty);
         st_agent64(&st->zsel, 0ull);
     }
 }
@@ -109,6 +110,7 @@ extern "C" int cc_solve_noalloc(uint64_t n, uint64_t m, const uint32_t* edge_lis
     s.samples = kNoAllocSamples;
     s.zbits = reinterpret_cast<uint32_t*>(base + kOffBits);
     s.zbits_cap = kBitsWords;
+    s.gbits = s.zbits;              // a call uses one or the other
     s.no_grow = true;
     s.no_tiled = true;
     k_na_reset<<<1, 64, 0, hs>>>(s.st);

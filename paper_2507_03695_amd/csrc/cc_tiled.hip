@@ -33,6 +33,7 @@
 #include <algorithm>
 
 #include "cc_internal.h"
+#include "cc_link.h"
 
 namespace ccm {
 
@@ -66,54 +67,6 @@ constexpr int kC1 = 8192;                            // level-1 chunk (entries)
 constexpr int kC2 = 8192;                            // level-2 chunk (entries)
 constexpr int kPartBlock = 1024;
 constexpr int kPartEPT = kC1 / kPartBlock;           // 8
-
-// ---- shared device helpers (same rules as the plain hook) ---------------------
-
-__device__ __forceinline__ bool t_key_less(uint32_t a, uint32_t b, uint32_t z) {
-    return (a == z) | ((b != z) & (a < b));
-}
-
-// Root of x with path splitting: device-coherent splitting stores, each issued
-// after the next step's load (the rule and its reasons are those of
-// cc_kernels.hip's find_root).
-__device__ __forceinline__ uint32_t t_find(uint32_t* P, uint32_t x, uint32_t px) {
-    if (px == x) return x;
-    uint32_t gp = P[px];
-    while (gp != px) {
-        const uint32_t ggp = P[gp];
-        stress_delay(x);
-        st_agent(&P[x], gp);
-        x = px;
-        px = gp;
-        gp = ggp;
-    }
-    return px;
-}
-
-__device__ __forceinline__ uint32_t t_link(uint32_t* P, uint32_t u, uint32_t pu, uint32_t v,
-                                           uint32_t pv, uint32_t z) {
-    while (true) {
-        const uint32_t ru = t_find(P, u, pu);
-        const uint32_t rv = t_find(P, v, pv);
-        if (ru == rv) return ru;
-        const bool u_low = t_key_less(ru, rv, z);
-        const uint32_t hi = u_low ? rv : ru;
-        const uint32_t lo = u_low ? ru : rv;
-        stress_delay(hi);
-        // a coherent read before the CAS, as in cc_kernels.hip's link: a root
-        // seen through a stale L2 copy is not CASed
-        const uint32_t cur = ld_agent(&P[hi]);
-        if (cur != hi) {
-            u = hi; pu = cur;
-            v = lo; pv = lo;
-            continue;
-        }
-        const uint32_t old = atomicCAS(&P[hi], hi, lo);
-        if (old == hi) return lo;
-        u = hi; pu = old;
-        v = lo; pv = lo;
-    }
-}
 
 // Exclusive scan of cnt[0..R) into start[0..R] by the first wave (R <= 256);
 // start[R] is the total.
@@ -500,7 +453,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_hookplain(const uint32_t* __r
         const uint32_t u = e[k].x, v = e[k].y;
         if (!h[k] || u == v) continue;
         if (pu[k] == pv[k] || pu[k] == v || pv[k] == u) continue;   // same tree already
-        (void)t_link(P, u, pu[k], v, pv[k], kEmpty);               // no zero root: key = ID
+        (void)link<false, 1>(P, u, pu[k], v, pv[k], 0);
     }
 }
 
@@ -1117,7 +1070,7 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
         for (int k = 0; k < kHook4EPT; ++k) {
             if (!h[k]) continue;
             if (pu[k] == pv[k] || pu[k] == v[k] || pv[k] == u[k]) continue;
-            (void)t_link(P, u[k], pu[k], v[k], pv[k], z);
+            (void)link<true, 1>(P, u[k], pu[k], v[k], pv[k], z);
         }
     }
 }
