@@ -83,16 +83,21 @@ int cc_version(void);
    hook take a sample first and then test every entry against the bitmap of
    the sample's giant component (on the plain path) or of z's.             */
 #define CC_F_NO_SPLIT     0x8u
-/* Keep the direct hook, which takes the entries in their given order, where
-   the regrouped hooks would apply (4 <= ceil(n / 2^19) <= 256, or 8 <= with
-   CC_F_ZROOT, and 2^24 <= m < 2^32, without CC_F_NO_SPLIT). With CC_F_ZROOT the regrouped hook
-   sorts the entries by the vertex ranges of both endpoints so that both
-   membership tests read LDS; without it, the plain hook takes the entries
-   grouped by their first endpoint's range, so that those parent reads stay in
-   L2. Labels are identical either way. Pass it for lists in which a vertex
-   recurs in many entries at once, such as a Reducer's messages from several
-   shares: grouped, their links contend for the same roots (R-MAT-26's 165 M
-   SiskinCC messages: 4.6 ms in the given order, 13 ms grouped). */
+/* Keep the direct hook, which takes the entries in their given order, where the
+   regrouped hooks would apply (none does with CC_F_NO_SPLIT).
+   - The filter sorts the entries by the ranges of 2^19 vertices of both
+     endpoints, so that both membership tests read LDS. Whole solves and the
+     CC_F_ZROOT hook take it from n = 1,179,649 to 2^27 with at least one entry
+     per vertex and 2^20 entries (2^24 beyond 22 ranges), below 2^32; on the
+     plain path the bitmap is that of the giant component a sample of the
+     entries shows. If the sample shows none, the device takes the direct hook.
+   - The plain cc_hook takes the entries grouped by their first endpoint's range
+     (4 <= ceil(n / 2^19) <= 256, 2^24 <= m < 2^32), so that those parent reads
+     stay in L2.
+   Labels are identical either way. Pass it for lists in which a vertex recurs in
+   many entries at once, such as a Reducer's messages from several shares:
+   grouped, their links contend for the same roots (R-MAT-26's 165 M SiskinCC
+   messages: 4.6 ms in the given order, 13 ms grouped). */
 #define CC_F_NO_TILE      0x10u
 /* cc_compress with CC_F_ZROOT: give the zero root's component its smallest ID
    in the same pass (what cc_canon writes), so that no cc_canon is needed.
@@ -132,7 +137,7 @@ typedef struct cc_ctx_opts {
    root selection state, a sampled-degree hash table, per-block minima) and
    pinned host staging, and grows on demand what larger solves need: the
    zero-root membership bitmap (n/8 bytes), the buffers of the regrouped hooks
-   (about 14 bytes per entry), the CSR tile tables and the batch work list.
+   (5 to 11 bytes per entry, 6 per entry more with CSR input), the CSR tile tables and the batch work list.
    opts may be NULL (defaults). */
 int cc_create(cc_ctx** out, const cc_ctx_opts* opts);
 /* Release a context and everything it owns. Waits for its work to finish. */

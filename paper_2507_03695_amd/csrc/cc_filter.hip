@@ -9,76 +9,92 @@
 // instead of one L2 line each), and only the entries with an unmarked endpoint
 // go further.
 #include <algorithm>
+#include <type_traits>
 
 #include "cc_internal.h"
 #include "cc_link.h"
 
 namespace ccm {
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
 // ---- the sample -------------------------------------------------------------------------
 // Algorithm 1 / 3 on every tstride-th run of kWBlock entries (so that a list in
-// any order, sorted rows for instance, is sampled evenly), without the bitmap.
-// One entry per thread: the pass is a chain of dependent reads and CASes per
-// entry, and a thread with four would take four times as long.
+// any order, sorted rows for instance, is sampled evenly), without the bitmap
+// and without path splitting: the trees are young, and the splitting stores of
+// all entries meet on the words just below the few large roots (R-MAT n = 2^22,
+// 2^21 entries sampled: 389 us with splitting, 125 without). One entry per
+// thread: the pass is a chain of dependent reads and CASes per entry.
 constexpr int kWBlock = 256;
+constexpr uint32_t kWGrid = 8192;
 
-template <bool ZR, int SPLIT>
-__global__ __launch_bounds__(kWBlock) void k_warm(const uint32_t* __restrict__ edges, uint64_t m,
-                                                  uint32_t n, uint64_t tstride, uint32_t* P,
-                                                  DevState* st, uint32_t sym) {
+template <bool ZR, typename T>
+__global__ __launch_bounds__(kWBlock) void k_warm(const T* __restrict__ edges, uint64_t m, uint32_t n,
+                                                  uint64_t tstride, uint64_t tiles, uint32_t* P,
+                                                  DevState* st, uint32_t sym, Gate gate) {
+    if (gated_off(gate)) return;
     const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
-    const uint64_t i = (uint64_t)blockIdx.x * tstride * kWBlock + threadIdx.x;
-    if (i >= m) return;
-    const u32x2 e = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(edges) + i);
-    if (e.x >= n || e.y >= n) { atomicOr(&st->status, kStatusRange); return; }
-    if (sym ? e.x >= e.y : e.x == e.y) return;
-    const uint32_t pu = P[e.x], pv = P[e.y];
-    if (pu == pv || pu == e.y || pv == e.x) return;
-    (void)link<ZR, SPLIT>(P, e.x, pu, e.y, pv, z);
+    for (uint64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const uint64_t i = t * tstride * kWBlock + threadIdx.x;
+        if (i >= m) return;
+        const u32x2 e = load_entry(edges, i);
+        if (e.x >= n || e.y >= n) { atomicOr(&st->status, kStatusRange); continue; }
+        if (sym ? e.x >= e.y : e.x == e.y) continue;
+        const uint32_t pu = P[e.x], pv = P[e.y];
+        if (pu == pv || pu == e.y || pv == e.x) continue;
+        (void)link<ZR, 0>(P, e.x, pu, e.y, pv, z);
+    }
 }
 
-// ---- the bitmap of one root's component -------------------------------------------
-// Runs on a flat forest (after compress). The root is, on a zero-root solve, the
-// zero root z: a vertex is a member when its root is z, or it or its root is
-// marked. On a plain solve (PICK) it is the root most often seen above kGSample
-// entries' endpoints (ties to the lowest ID), found by every block for itself
-// from the same reads, so that no launch of its own is needed; block 0 records
-// it in DevState, where the kernels after this one read it as the zero root.
-// Each wave writes the two words of 64 consecutive vertices from a ballot.
+// ---- is there a giant component ----------------------------------------------------------
+// One block walks kGSample sampled entries' endpoints (both ends alternating) to
+// their roots. A plain solve (PICK) takes the root met most often (ties to the
+// lowest ID) as the one whose component the bitmap describes; with a zero root
+// it is z. At least a quarter of the endpoints in that component make it giant.
+// Below that the filter would leave most entries to be hooked with one workgroup
+// per CU, and the direct hook is the better one (grid of 4 M vertices, 8 M
+// entries: 1.05 ms direct, 9 ms through the filter).
 constexpr int kGBlock = 1024;
 constexpr uint32_t kGSample = kGBlock;        // one sampled entry per thread
 constexpr uint32_t kGTable = 2 * kGSample;
+static_assert(kGTable == 1u << 11, "the sample's hash yields 11 bits");
 
-template <bool PICK>
-__global__ __launch_bounds__(kGBlock) void k_giant_bits(const uint32_t* __restrict__ edges,
-                                                        uint64_t m, const uint32_t* P, uint64_t n,
-                                                        uint32_t* zbits, DevState* st) {
-    uint32_t g;
-    if (PICK) {
-        __shared__ uint32_t s_key[kGTable], s_cnt[kGTable];
-        __shared__ uint64_t s_best[kGBlock / 64];
-        for (uint32_t i = threadIdx.x; i < kGTable; i += kGBlock) { s_key[i] = kEmpty; s_cnt[i] = 0; }
-        __syncthreads();
-        const uint64_t cnt = m < kGSample ? m : kGSample;
-        if (threadIdx.x < cnt) {
-            const uint64_t q = m / cnt, r = m % cnt;
-            const uint64_t i = threadIdx.x * q + threadIdx.x * r / cnt;
-            const uint32_t x = edges[2 * i + (threadIdx.x & 1)];
-            if (x < n) {
-                const uint32_t root = ld_agent(&P[x]);
-                uint32_t h = (root * 0x9E3779B1u) >> (32 - 11);
-                while (true) {
-                    const uint32_t k = atomicCAS(&s_key[h], kEmpty, root);
-                    if (k == kEmpty || k == root) break;
-                    h = (h + 1) & (kGTable - 1);
-                }
-                atomicAdd(&s_cnt[h], 1u);
+// The root that kGSample sampled endpoints have most often, by one block of
+// kGBlock threads; *count receives how many of *total have it (without pick, how
+// many have the root g).
+// root_of(x) gives a vertex's root.
+template <typename T, class Root>
+__device__ __forceinline__ uint32_t sample_root(const T* edges, uint64_t m, uint64_t n, bool pick,
+                                                uint32_t g, uint32_t* count, uint32_t* total,
+                                                const Root& root_of) {
+    __shared__ uint32_t s_key[kGTable], s_cnt[kGTable];
+    __shared__ uint64_t s_best[kGBlock / 64];
+    __shared__ uint32_t s_tot, s_in;
+    if (threadIdx.x == 0) { s_tot = 0; s_in = 0; }
+    for (uint32_t i = threadIdx.x; i < kGTable; i += kGBlock) { s_key[i] = kEmpty; s_cnt[i] = 0; }
+    __syncthreads();
+    const uint64_t cnt = m < kGSample ? m : kGSample;
+    uint32_t root = kEmpty;
+    if (threadIdx.x < cnt) {
+        const uint64_t q = m / cnt, r = m % cnt;
+        const u32x2 e = load_entry(edges, threadIdx.x * q + threadIdx.x * r / cnt);
+        const uint32_t x = threadIdx.x & 1 ? e.y : e.x;
+        if (x < n) root = root_of(x);
+    }
+    if (root != kEmpty) {
+        atomicAdd(&s_tot, 1u);
+        if (!pick && root == g) atomicAdd(&s_in, 1u);
+        if (pick) {
+            uint32_t h = (root * 0x9E3779B1u) >> (32 - 11);
+            while (true) {
+                const uint32_t k = atomicCAS(&s_key[h], kEmpty, root);
+                if (k == kEmpty || k == root) break;
+                h = (h + 1) & (kGTable - 1);
             }
+            atomicAdd(&s_cnt[h], 1u);
         }
-        static_assert(kGTable == 1u << 11, "the hash above yields 11 bits");
-        __syncthreads();
+    }
+    __syncthreads();
+    uint32_t in = s_in;
+    if (pick) {
         uint64_t best = 0;
         for (uint32_t i = threadIdx.x; i < kGTable; i += kGBlock)
             if (s_cnt[i]) best = max(best, ((uint64_t)s_cnt[i] << 32) | (0xFFFFFFFFu - s_key[i]));
@@ -87,8 +103,65 @@ __global__ __launch_bounds__(kGBlock) void k_giant_bits(const uint32_t* __restri
         __syncthreads();
         best = s_best[0];
         for (int w = 1; w < kGBlock / 64; ++w) best = max(best, s_best[w]);
-        g = best ? 0xFFFFFFFFu - (uint32_t)best : ld_agent(&P[0]);
-        if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&st->zroot, g);
+        g = best ? 0xFFFFFFFFu - (uint32_t)best : root_of(0);
+        in = (uint32_t)(best >> 32);
+    }
+    *count = in;
+    *total = s_tot;
+    return g;
+}
+
+__device__ __forceinline__ uint32_t giant_enough(uint32_t in, uint32_t total) {
+    return total && 4 * in >= total;
+}
+
+template <bool PICK, typename T>
+__global__ __launch_bounds__(kGBlock) void k_find_giant(const T* __restrict__ edges, uint64_t m,
+                                                        uint32_t* P, uint64_t n,
+                                                        const uint32_t* zbits, DevState* st,
+                                                        int first, Gate gate) {
+    if (gated_off(gate)) return;
+    uint32_t in, tot;
+    const uint32_t z = PICK ? 0u : ld_agent(&st->zroot);
+    const uint32_t g = sample_root(edges, m, n, PICK, z, &in, &tot, [&](uint32_t x) {
+        if (!PICK && (ld_agent(&zbits[x >> 5]) >> (x & 31) & 1u)) return z;
+        uint32_t p = ld_agent(&P[x]);
+        while (p != x) { x = p; p = ld_agent(&P[x]); }
+        return x;
+    });
+    if (threadIdx.x == 0) {
+        const uint32_t giant = giant_enough(in, tot);
+        if (PICK) st_agent(&st->zroot, g);
+        if (first) st_agent(&st->giant1, giant);
+        st_agent(&st->giant, giant);
+        st_agent(&st->rebuild, first ? 0u : giant);
+    }
+}
+
+// ---- the bitmap of one root's component -------------------------------------------
+// Runs on a flat forest (after compress). A vertex is a member when its root is
+// st->zroot, or (ZR) when it or its root is marked. With PICK the root is found
+// here, as k_find_giant would, by every block for itself from the same reads (one
+// launch less); block 0 records it, and with `first` whether it is a giant
+// component's (st->giant1). Each wave
+// writes the two words of 64 consecutive vertices from a ballot.
+template <int MODE, typename T>
+__global__ __launch_bounds__(kGBlock) void k_giant_bits(const T* __restrict__ edges, uint64_t m,
+                                                        const uint32_t* P, uint64_t n,
+                                                        uint32_t* zbits, DevState* st, int first,
+                                                        Gate gate) {
+    if (gated_off(gate)) return;
+    constexpr bool ZR = MODE == kBitsZr;
+    uint32_t g;
+    if (MODE == kBitsPick || (first && blockIdx.x == 0)) {
+        uint32_t in, tot;
+        const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
+        g = sample_root(edges, m, n, MODE == kBitsPick, z, &in, &tot,
+                        [&](uint32_t x) { return ld_agent(&P[x]); });
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (MODE == kBitsPick) st_agent(&st->zroot, g);
+            if (first) st_agent(&st->giant1, giant_enough(in, tot));
+        }
     } else {
         g = ld_agent(&st->zroot);
     }
@@ -103,13 +176,13 @@ __global__ __launch_bounds__(kGBlock) void k_giant_bits(const uint32_t* __restri
         for (int k = 0; k < kR; ++k) {
             const uint64_t v = v0 + k * stride;
             p[k] = v < n ? ld_agent(&P[v]) : kEmpty;
-            b[k] = (!PICK && v < n) ? ld_agent(&zbits[v >> 5]) >> (v & 31) & 1u : 0u;
+            b[k] = (ZR && v < n) ? ld_agent(&zbits[v >> 5]) >> (v & 31) & 1u : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kR; ++k) {
             const uint64_t v = v0 + k * stride;
             bool in = v < n && (p[k] == g || b[k]);
-            if (!PICK && v < n && !in && p[k] != (uint32_t)v)
+            if (ZR && v < n && !in && p[k] != (uint32_t)v)
                 in = ld_agent(&zbits[p[k] >> 5]) >> (p[k] & 31) & 1u;
             const uint64_t ball = __ballot(in);
             const uint64_t w = (v - lane) >> 5;
@@ -125,67 +198,68 @@ __global__ __launch_bounds__(kGBlock) void k_giant_bits(const uint32_t* __restri
 // them once, each thread keeping kLEPT loads in flight (an entry's register is
 // reloaded with the next round's as soon as it is tested).
 //  - both endpoints marked: dropped;
-//  - otherwise the entry goes to its wave's queue, and each time 64 are queued
-//    they are settled together, one per lane: one endpoint marked, the other is
-//    marked too (LDS, and the global word when this set the bit); neither, the
-//    entry is hooked in P as in the direct hook.
+//  - otherwise the entry goes to its wave's queues (cc_link.h): one endpoint
+//    marked, the other is marked too (LDS, and the global word when this set the
+//    bit); neither, the entry is hooked in P as in the direct hook.
 // The bits set since by other workgroups are not seen; a clear bit only sends an
 // entry to P.
 constexpr int kLBlock = 1024;
 constexpr int kLWaves = kLBlock / 64;
-constexpr int kLQueue = 127;
-constexpr uint32_t kLdsBitsWords = 36864;      // 144 KB; the queues take 15.9 KB of the 160
+constexpr uint32_t kMarkGrid = 128;            // workgroups of the marking pass
+constexpr uint32_t kLdsBitsWords = 36864;      // 144 KB; the queues take the rest of the 160
 
-template <int SPLIT, int kLEPT>
-__global__ __launch_bounds__(kLBlock) void k_hook_lds(const uint32_t* __restrict__ edges, uint64_t m,
+template <int SPLIT, int kLEPT, bool MARK, typename T>
+__global__ __launch_bounds__(kLBlock) void k_hook_lds(const T* __restrict__ edges, uint64_t m,
                                                       uint32_t n, uint32_t* P, uint32_t* zbits,
-                                                      DevState* st, uint32_t sym) {
+                                                      DevState* st, uint32_t sym, uint32_t tstride) {
     extern __shared__ uint32_t bits[];
-    __shared__ u32x2 s_q[kLWaves * kLQueue];
+    __shared__ u32x2 s_queue[kLWaves * 2 * kQueueCap];
     const uint32_t z = ld_agent(&st->zroot);
     const uint32_t words = (n + 31) / 32;
-    for (uint32_t i = threadIdx.x; i < words; i += kLBlock) bits[i] = ld_agent(&zbits[i]);
+    // Plain loads: the copies of an XCD's workgroups come out of its L2 (run_hook_lds
+    // sees to it that no older line is there). Each workgroup starts elsewhere, so
+    // that they do not all want the same channel at once.
+    constexpr int kW = 8;                              // words in flight per thread
+    const uint32_t rot = (uint32_t)((uint64_t)words * (blockIdx.x & 31) / 32);
+    auto turn = [&](uint32_t i) { return i + rot < words ? i + rot : i + rot - words; };
+    for (uint32_t i0 = threadIdx.x; i0 < words; i0 += kW * kLBlock) {
+        uint32_t w[kW];
+#pragma unroll
+        for (int k = 0; k < kW; ++k) w[k] = i0 + k * kLBlock < words ? zbits[turn(i0 + k * kLBlock)] : 0u;
+#pragma unroll
+        for (int k = 0; k < kW; ++k)
+            if (i0 + k * kLBlock < words) bits[turn(i0 + k * kLBlock)] = w[k];
+    }
     const int lane = threadIdx.x & 63;
-    u32x2* q = s_q + (threadIdx.x >> 6) * kLQueue;
-    const u32x2* E = reinterpret_cast<const u32x2*>(edges);
+    WaveQueues q;
+    q.pq = s_queue + (threadIdx.x >> 6) * 2 * kQueueCap;
+    q.lq = q.pq + kQueueCap;
     constexpr uint64_t kTile = (uint64_t)kLBlock * kLEPT;
-    const uint64_t step = (uint64_t)gridDim.x * kTile;
+    const uint64_t step = (uint64_t)gridDim.x * kTile * tstride;
     auto bit = [&](uint32_t x) { return (bits[x >> 5] >> (x & 31)) & 1u; };
     auto mark = [&](uint32_t x) {
         const uint32_t b = 1u << (x & 31);
-        if (!(atomicOr(&bits[x >> 5], b) & b)) atomicOr(&zbits[x >> 5], b);
+        const uint32_t old = atomicOr(&bits[x >> 5], b);
+        if (!MARK && !(old & b)) atomicOr(&zbits[x >> 5], b);
     };
-    auto settle = [&](uint32_t cnt) {
-        if ((uint32_t)lane < cnt) {
-            const u32x2 e = q[lane];
-            const uint32_t mu = bit(e.x), mv = bit(e.y);
-            if (mu != mv) {
-                mark(mu ? e.y : e.x);
-            } else if (!mu) {
-                const uint32_t pu = P[e.x], pv = P[e.y];
-                uint32_t r;
-                if (pu == pv) r = pu;
-                else if (pu == e.y) r = e.y;
-                else if (pv == e.x) r = e.x;
-                else r = link<true, SPLIT>(P, e.x, pu, e.y, pv, z);
-                if (r == z) { mark(e.x); mark(e.y); }
-            }
-        }
+    auto settle = [&](u32x2 e) {
+        const uint32_t mu = bit(e.x), mv = bit(e.y);
+        if (mu != mv) mark(mu ? e.y : e.x);
+        return !mu && !mv;
     };
-    auto wsync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    auto hook = [&](u32x2 e) {
+        const uint32_t pu = P[e.x], pv = P[e.y];
+        if (pu == pv || pu == e.y || pv == e.x) return;
+        (void)link<true, SPLIT>(P, e.x, pu, e.y, pv, z);
     };
     u32x2 e[kLEPT];
-    const uint64_t t0 = (uint64_t)blockIdx.x * kTile + threadIdx.x;
+    const uint64_t t0 = (uint64_t)blockIdx.x * tstride * kTile + threadIdx.x;
 #pragma unroll
     for (int k = 0; k < kLEPT; ++k) {
         const uint64_t i = t0 + (uint64_t)k * kLBlock;
-        e[k] = __builtin_nontemporal_load(E + (i < m ? i : m - 1));
+        e[k] = load_entry(edges, i < m ? i : m - 1);
     }
     __syncthreads();
-    uint32_t qn = 0;                                   // wave-uniform
     bool bad = false;
     for (uint64_t t = t0; t - threadIdx.x < m; t += step) {
         // the last round reloads the last entry: an in-bounds address, never tested
@@ -195,31 +269,35 @@ __global__ __launch_bounds__(kLBlock) void k_hook_lds(const uint32_t* __restrict
             const u32x2 x = e[k];
             const uint64_t i = t + (uint64_t)k * kLBlock;
             const uint64_t j = i + step;
-            e[k] = __builtin_nontemporal_load(E + (full || j < m ? j : m - 1));
+            e[k] = load_entry(edges, full || j < m ? j : m - 1);
             const bool ok = (x.x < n) & (x.y < n), in = i < m;
             bad |= in & !ok;
             const uint32_t u = ok ? x.x : 0u, v = ok ? x.y : 0u;
             const bool live = in & (sym ? u < v : u != v);
             const bool pend = live & !(bit(u) & bit(v));
-            const uint64_t ball = __ballot(pend);
-            if (ball) {
-                if (pend) q[qn + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] = x;
-                qn += (uint32_t)__popcll(ball);
-                if (qn >= 64) {
-                    wsync();
-                    settle(64);
-                    const u32x2 rest = (uint32_t)lane < qn - 64 ? q[64 + lane] : u32x2{0u, 0u};
-                    wsync();
-                    if ((uint32_t)lane < qn - 64) q[lane] = rest;
-                    qn -= 64;
-                    wsync();
-                }
+            if (MARK) {
+                if (pend) (void)settle(x);
+            } else {
+                queue_push(q, lane, pend, x, settle, hook);
             }
         }
     }
-    if (qn) {
-        wsync();
-        settle(qn);
+    if (!MARK) queue_finish(q, lane, settle, hook);
+    if (MARK) {
+        // the new marks, one atomic per word that gained any
+        __syncthreads();
+        for (uint32_t i0 = threadIdx.x; i0 < words; i0 += kW * kLBlock) {
+            uint32_t w[kW];
+#pragma unroll
+            for (int k = 0; k < kW; ++k)
+                w[k] = i0 + k * kLBlock < words ? ld_agent(&zbits[turn(i0 + k * kLBlock)]) : 0u;
+#pragma unroll
+            for (int k = 0; k < kW; ++k) {
+                if (i0 + k * kLBlock >= words) continue;
+                const uint32_t i = turn(i0 + k * kLBlock);
+                if (bits[i] & ~w[k]) atomicOr(&zbits[i], bits[i] & ~w[k]);
+            }
+        }
     }
     if (bad) atomicOr(&st->status, kStatusRange);
 }
@@ -228,33 +306,52 @@ __global__ __launch_bounds__(kLBlock) void k_hook_lds(const uint32_t* __restrict
 
 uint64_t lds_bits_max_n() { return (uint64_t)kLdsBitsWords * 32; }
 
-int run_warm(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, DevState* st, bool zr,
-             bool split, bool sym, uint64_t want, hipStream_t stream) {
-    const uint64_t tiles = (m + kWBlock - 1) / kWBlock;
+int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool zr, bool sym,
+             uint64_t want, Gate gate, hipStream_t stream) {
     const uint64_t ts = std::max<uint64_t>(m / std::max<uint64_t>(want, 1), 1);
-    const uint64_t g = (tiles + ts - 1) / ts;
-    if (g > 0x7FFFFFFFull) return fail(CC_EINVAL, "edge count too large for one launch");
+    const uint64_t tiles = ((m + kWBlock - 1) / kWBlock + ts - 1) / ts;
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
-    if (zr && split) k_warm<true, 1><<<(uint32_t)g, kWBlock, 0, stream>>>(edges, m, n32, ts, P, st, sy);
-    else if (zr) k_warm<true, 0><<<(uint32_t)g, kWBlock, 0, stream>>>(edges, m, n32, ts, P, st, sy);
-    else if (split) k_warm<false, 1><<<(uint32_t)g, kWBlock, 0, stream>>>(edges, m, n32, ts, P, st, sy);
-    else k_warm<false, 0><<<(uint32_t)g, kWBlock, 0, stream>>>(edges, m, n32, ts, P, st, sy);
+    const uint32_t g = (uint32_t)std::min<uint64_t>(tiles, kWGrid);
+    auto launch = [&](auto* e) {
+        if (zr) k_warm<true><<<g, kWBlock, 0, stream>>>(e, m, n32, ts, tiles, P, st, sy, gate);
+        else k_warm<false><<<g, kWBlock, 0, stream>>>(e, m, n32, ts, tiles, P, st, sy, gate);
+    };
+    if (E.wide) launch((const uint64_t*)E.p);
+    else launch((const uint32_t*)E.p);
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
 
-int run_giant_bits(uint64_t n, uint64_t m, const uint32_t* edges, const uint32_t* P, uint32_t* zbits,
-                   DevState* st, bool pick, hipStream_t stream) {
+int run_find_giant(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, const uint32_t* zbits, DevState* st,
+                   bool zr, bool first, hipStream_t stream) {
+    const Gate gate = first ? Gate{} : Gate{&st->giant1, 0u};
+    auto launch = [&](auto* e) {
+        if (zr) k_find_giant<false><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+        else k_find_giant<true><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+    };
+    if (E.wide) launch((const uint64_t*)E.p);
+    else launch((const uint32_t*)E.p);
+    CCM_HIP(hipGetLastError());
+    return CC_OK;
+}
+
+int run_giant_bits(uint64_t n, uint64_t m, EdgeList E, const uint32_t* P, uint32_t* zbits,
+                   DevState* st, int mode, int first, Gate gate, hipStream_t stream) {
     const uint64_t blocks = (n + 4 * kGBlock - 1) / (4 * kGBlock);
     const uint32_t g = (uint32_t)std::min<uint64_t>(blocks, 2048);
-    if (pick) k_giant_bits<true><<<g, kGBlock, 0, stream>>>(edges, m, P, n, zbits, st);
-    else k_giant_bits<false><<<g, kGBlock, 0, stream>>>(edges, m, P, n, zbits, st);
+    const uint32_t* e32 = (const uint32_t*)E.p;
+    if (mode == kBitsZr) k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(e32, m, P, n, zbits, st, first, gate);
+    else if (mode == kBitsPlain)
+        k_giant_bits<kBitsPlain><<<g, kGBlock, 0, stream>>>(e32, m, P, n, zbits, st, first, gate);
+    else if (E.wide)
+        k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>((const uint64_t*)E.p, m, P, n, zbits, st, first, gate);
+    else k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>(e32, m, P, n, zbits, st, first, gate);
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
 
-int run_hook_lds(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, uint32_t* zbits,
-                 DevState* st, bool split, bool sym, int device, hipStream_t stream) {
+int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, DevState* st,
+                 bool split, bool sym, int device, hipStream_t stream) {
     const size_t lds = 4 * ((n + 31) / 32);
     const uint64_t cus = device_cu_count(device);
     // two workgroups per CU where two bitmaps fit; on short lists fewer entries
@@ -264,18 +361,32 @@ int run_hook_lds(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, uin
     const uint64_t tile = (uint64_t)kLBlock * (wide ? 8 : 2);
     const uint32_t g = (uint32_t)std::min<uint64_t>((m + tile - 1) / tile, wgs);
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
-    auto launch = [&](auto kernel) -> int {
+    auto launch = [&](auto kernel, auto* e, uint32_t ts, uint32_t blocks) -> int {
         // the largest size, whatever this call needs: the attribute belongs to the
         // kernel, and another thread's call may need more than this one
         CCM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                     4 * (int)kLdsBitsWords));
-        kernel<<<g, kLBlock, lds, stream>>>(edges, m, n32, P, zbits, st, sy);
+        kernel<<<blocks, kLBlock, lds, stream>>>(e, m, n32, P, zbits, st, sy, ts);
         CCM_HIP(hipGetLastError());
         return CC_OK;
     };
-    if (split) return wide ? launch(&k_hook_lds<1, 8>) : launch(&k_hook_lds<1, 2>);
-    return wide ? launch(&k_hook_lds<0, 8>) : launch(&k_hook_lds<0, 2>);
+    auto pick = [&](auto* e) -> int {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(e)>>;
+        // Every fourth round by few workgroups, marks only: what each learns about
+        // its copy, all know in the full pass, instead of hooking in P what the
+        // others have marked (R-MAT n = 1,000,003, 15 M entries, whole solve: 332 us
+        // without, 185 with 128 workgroups, 201 with 32, 204 with 256).
+        int rc = launch(wide ? &k_hook_lds<0, 8, true, T> : &k_hook_lds<0, 2, true, T>, e, 4u,
+                        std::min<uint32_t>(g, kMarkGrid));
+        if (rc) return rc;
+        // the copies above left lines of the bitmap in the XCDs' L2s
+        if ((rc = cohere(stream))) return rc;
+        if (split)
+            return launch(wide ? &k_hook_lds<1, 8, false, T> : &k_hook_lds<1, 2, false, T>, e, 1u, g);
+        return launch(wide ? &k_hook_lds<0, 8, false, T> : &k_hook_lds<0, 2, false, T>, e, 1u, g);
+    };
+    return E.wide ? pick((const uint64_t*)E.p) : pick((const uint32_t*)E.p);
 }
 
 }  // namespace ccm

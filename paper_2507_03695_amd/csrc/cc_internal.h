@@ -26,7 +26,11 @@ struct DevState {
     uint32_t mpub;      // smallest member of zpub's component (zero-root compress; cc_canon)
     uint64_t zsel;      // packed argmax (count << 32) | (0xFFFFFFFF - id); 0 = none
     uint64_t log_count; // messages of a drained update log (cc_hook_log_drain)
-    uint64_t pad1[4];
+    uint32_t giant1;    // after the first sample: its entries show a giant component
+    uint32_t giant;     // the filter's kernels run (else the direct hook's)
+    uint32_t rebuild;   // the bitmap is to be written after the second sample
+    uint32_t pad1;
+    uint64_t pad2[2];
 };
 static_assert(sizeof(DevState) == 64, "DevState is one 64-byte block");
 
@@ -126,6 +130,19 @@ struct Slot {
 int slot_create(Slot* s, int device, uint32_t samples);
 void slot_destroy(Slot* s);
 
+// A COO list: 2m IDs of 32 bits, or 64 (wide).
+struct EdgeList {
+    const void* p;
+    bool wide;
+};
+
+// Which launches of a solve run is in part decided on the device: a kernel given
+// a gate leaves at once unless *word == want (word NULL: always runs).
+struct Gate {
+    const uint32_t* word;
+    uint32_t want;
+};
+
 // Enqueue steps (arguments already validated by the caller).
 int run_init(Slot* s, uint64_t n, uint32_t* P, hipStream_t stream);
 int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t flags,
@@ -178,6 +195,9 @@ int run_pack_ids(Slot* s, uint64_t count, const uint32_t* ids, uint32_t k, uint8
                  hipStream_t stream);
 int run_unpack_ids(Slot* s, uint64_t count, const uint8_t* in, uint32_t k, uint32_t* ids,
                    hipStream_t stream);
+int run_giant(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* bits, int passes,
+              bool p32, uint32_t flags, hipStream_t stream);
+bool lds_eligible(uint64_t n, uint64_t m);
 int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* L,
               uint32_t flags, uint32_t hint, hipStream_t stream);
 // Whole path on CSR input (m = off[n], read by the caller).
@@ -192,28 +212,49 @@ int zbits_reset(Slot* s, uint64_t n, hipStream_t stream);
 // CC_ERANGE, CC_ENOMEM (a full update log) or CC_EINVAL (bad CSR offsets).
 int slot_sync(Slot* s, hipStream_t stream);
 
-// Tiled zero-root hook (cc_tiled.hip): both membership tests in LDS.
+// Regrouped hooks (cc_tiled.hip). The plain hook of first-endpoint buckets
+// applies to (n, m); with zr, the sizes at which the zero-root hook has always
+// been regrouped (it fails rather than run direct when its scratch cannot grow).
 bool tiled_eligible(uint64_t n, uint64_t m, bool zr);
-// Bytes of the regrouped hook's buffers for n vertices and m COO entries.
-uint64_t tiled_scratch_bytes(uint64_t n, uint64_t m, bool plain);
+// The filter over (first slice, second slice) tiles, both membership tests in
+// LDS: 0 = not for these sizes, else its partition passes (1 or 2).
+int filter_passes(uint64_t n, uint64_t m);
+uint64_t filter_scratch_bytes(uint64_t n, uint64_t m, int passes, bool bits, bool p32);
+uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m);
+// Size the slot's scratch for the filter (passes 0: only the arrays asked for):
+// with a bitmap of its own (bits), with a 32-bit parent array (p32). CC_ENOMEM
+// where it cannot grow now (fixed scratch, capture, no memory).
+struct FilterScratch {
+    char* buf;
+    uint32_t* bits;
+    uint32_t* p32;
+};
+int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool p32,
+                   hipStream_t stream, FilterScratch* out);
+// The filter on scratch sized by filter_scratch with the same arguments: every
+// entry tested against zbits, the rest hooked in P (key order of DevState::zroot).
+int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, int passes,
+               bool bits, bool p32, bool sym, Gate gate, hipStream_t stream);
+// The plain hook (key = ID) over first-endpoint buckets.
+int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, bool sym,
+                     hipStream_t stream);
 // Device bytes a whole-path solve (run_solve) grows in its slot for these
-// arguments: the bitmap, exact degrees, the regrouped hook's buffers.
-uint64_t solve_scratch_bytes(uint64_t n, uint64_t m, uint32_t flags);
-// Lend a block of device memory (at least solve_scratch_bytes(n, m, flags)) to
-// a slot for one run_solve: its grown buffers point into the block and nothing
-// is allocated; slot_return_scratch gives the slot its own buffers back.
+// arguments: the bitmap, exact degrees, the regrouped hooks' buffers. lean: the
+// least it can do with (the filter on a plain solve, and below the sizes of
+// tiled_eligible, is left out).
+uint64_t solve_scratch_bytes(uint64_t n, uint64_t m, uint32_t flags, bool lean);
+// Lend a block of device memory of `bytes` (solve_scratch_bytes of the same
+// arguments, lean or not) to a slot for one run_solve: its grown buffers point
+// into the block and nothing is allocated; slot_return_scratch gives the slot
+// its own buffers back.
 struct LentScratch {
     uint32_t* zbits; uint64_t zbits_cap;
     uint32_t* deg; uint64_t deg_cap;
     TiledScratch tiled;
 };
-void slot_lend_scratch(Slot* s, char* block, uint64_t n, uint64_t m, uint32_t flags, LentScratch* saved);
+void slot_lend_scratch(Slot* s, char* block, uint64_t bytes, uint64_t n, uint32_t flags,
+                       LentScratch* saved);
 void slot_return_scratch(Slot* s, const LentScratch* saved);
-// plain = true: the plain path (key = ID) hooks the first-endpoint buckets in
-// order instead (better locality for the first endpoints' parent reads).
-// sym: the list holds every pair in both orders; only u < v is hooked.
-int run_hook_tiled(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P,
-                   hipStream_t stream, bool plain = false, bool sym = false);
 void tiled_free(TiledScratch* t);
 // The same on CSR input, where the rows already are the first-endpoint buckets.
 int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
@@ -222,16 +263,23 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
 // Hooks that test a bitmap in LDS (cc_filter.hip).
 // Largest n whose whole bitmap fits a workgroup's LDS.
 uint64_t lds_bits_max_n();
-// The bitmap of one root's component, from a flat forest: the zero root's, or
-// (pick) that of the root most often seen above sampled endpoints.
-int run_giant_bits(uint64_t n, uint64_t m, const uint32_t* edges, const uint32_t* P, uint32_t* zbits,
-                   DevState* st, bool pick, hipStream_t stream);
+// The bitmap of st->zroot's component, from a flat forest; kBitsPick finds the
+// root first (the one most often seen above sampled endpoints). first: records
+// st->giant1.
+enum BitsMode { kBitsPick, kBitsPlain, kBitsZr };
+int run_giant_bits(uint64_t n, uint64_t m, EdgeList E, const uint32_t* P, uint32_t* zbits,
+                   DevState* st, int mode, int first, Gate gate, hipStream_t stream);
+// Whether the forest shows a giant component (the zero root's, by P and zbits,
+// with zr): st->giant, after the first sample st->giant1 too, after the second
+// (which runs where giant1 is 0) st->rebuild. A plain solve's root: st->zroot.
+int run_find_giant(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, const uint32_t* zbits, DevState* st,
+                   bool zr, bool first, hipStream_t stream);
 // About `want` entries hooked in P (no bitmap), spread evenly over the list.
-int run_warm(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, DevState* st, bool zr,
-             bool split, bool sym, uint64_t want, hipStream_t stream);
+int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool zr, bool sym,
+             uint64_t want, Gate gate, hipStream_t stream);
 // Every entry tested against the whole bitmap in LDS, the rest hooked in P.
-int run_hook_lds(uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, uint32_t* zbits,
-                 DevState* st, bool split, bool sym, int device, hipStream_t stream);
+int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, DevState* st,
+                 bool split, bool sym, int device, hipStream_t stream);
 
 // Batched path (cc_batch.hip).
 // The schedule taken when nothing else is known about a batch.
@@ -280,6 +328,7 @@ int device_cu_count(int device);
 int cohere(hipStream_t stream);
 
 // Coherent (agent-scope) accesses to the small shared words of DevState.
+
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -23,8 +23,6 @@
 
 namespace ccm {
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kBlock = 256;
 
 // ---- init --------------------------------------------------------------------
@@ -352,6 +350,29 @@ __global__ __launch_bounds__(kBlock) void k_hook(const uint32_t* __restrict__ ed
                                         sym != 0);
 }
 
+// The direct hook of a solve whose sample showed no giant component: k_hook's
+// tiles on a resident grid, which leaves at once where the filter runs instead.
+template <bool ZR, int SPLIT, bool LINKZ, typename T>
+__global__ __launch_bounds__(kBlock) void k_hook_gated(const T* __restrict__ edges, uint64_t m,
+                                                       uint32_t n, uint32_t* P, uint32_t* zbits,
+                                                       DevState* st, uint32_t sym, Gate gate) {
+    if (gated_off(gate)) return;
+    const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
+    for (uint64_t tile = (uint64_t)blockIdx.x * (kBlock * kEPT); tile < m;
+         tile += (uint64_t)gridDim.x * (kBlock * kEPT)) {
+        uint32_t u[kEPT], v[kEPT];
+#pragma unroll
+        for (int k = 0; k < kEPT; ++k) {
+            const uint64_t e = tile + (uint64_t)k * kBlock + threadIdx.x;
+            u32x2 uv = {0u, 0u};
+            if (e < m) uv = load_entry(edges, e);
+            u[k] = uv.x;
+            v[k] = uv.y;
+        }
+        hook_entries<ZR, SPLIT, false, LINKZ>(u, v, n, z, P, zbits, st, nullptr, 0, nullptr, sym != 0);
+    }
+}
+
 // ---- CSR input -------------------------------------------------------------------
 // Row u of a CSR graph holds the entries (u, adj[j]) for j in [off[u], off[u+1]);
 // these are the same unordered pairs as a COO list, sorted by first endpoint,
@@ -564,7 +585,9 @@ constexpr int kVPT = 4;
 
 template <bool ZR>
 __global__ __launch_bounds__(kBlock) void k_compress(uint32_t* P, uint64_t n, DevState* st,
-                                                     uint32_t* zbits, uint32_t* bmin) {
+                                                     uint32_t* zbits, uint32_t* bmin,
+                                                     Gate gate = Gate{nullptr, 0u}) {
+    if (gated_off(gate)) return;
     const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     uint32_t local_min = kEmpty;
@@ -643,7 +666,8 @@ __global__ __launch_bounds__(kBlock) void k_compress(uint32_t* P, uint64_t n, De
 template <bool FINAL>
 __global__ __launch_bounds__(kBlock) void k_resolve(uint32_t* P, uint64_t n, DevState* st,
                                                     const uint32_t* zbits, const uint32_t* bmin,
-                                                    uint32_t nb, int pub) {
+                                                    uint32_t nb, int pub, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ uint32_t s_min[kBlock / 64];
     const uint32_t z = ld_agent(&st->zroot);
     uint32_t lab = z;
@@ -735,17 +759,12 @@ int run_init(Slot* s, uint64_t n, uint32_t* P, hipStream_t stream) {
 // (cc_filter.hip) instead of hooking each in P. It needs a sample, two more
 // passes over P and the bitmap, about 40 us in all, and drops little where the
 // sample (n entries at most) leaves no giant component. Whole solves, direct
-// against LDS (us): R-MAT n = 2^16, 2^20 entries 128 against 120 (plain); n =
-// 1,000,003, 15 M entries 924 against 258 (zero root), 511 against 262 (plain);
-// ER n = 1.1 M, 2.5 M entries (zero root) 1172 against 621.
-static bool lds_eligible(uint64_t n, uint64_t m) {
+// against LDS (us): R-MAT n = 2^16, 2^20 entries 128 against 94 (plain); n =
+// 1,000,003, 15 M entries 924 against 193 (zero root); ER n = 1 M, 4 M entries
+// 277 against 271 (plain), 691 against 323 (zero root).
+bool lds_eligible(uint64_t n, uint64_t m) {
     return n <= lds_bits_max_n() && m >= (1ull << 18) && m >= 2 * n;
 }
-// Entries of the sample: one per vertex (R-MAT n = 1,000,003, 15 M entries, whole
-// solve with n/4, n/2, n and 2n: 341, 283, 254, 271 us), at most a quarter of all.
-static uint64_t warm_entries(uint64_t n, uint64_t m) { return std::min<uint64_t>(m / 4, n); }
-// Internal flag of run_compress: the bitmap is the giant component's of a plain solve.
-constexpr uint32_t kGiant = 0x40000000u;
 // Blocks of the zero root's compress and resolve (8 per CU).
 constexpr uint32_t kZrGrid = 2048;
 
@@ -827,6 +846,90 @@ int run_push(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
     return CC_OK;
 }
 
+// The hook against the bitmap of one root's component (cc_filter.hip,
+// cc_tiled.hip), in P after init, or with zr after zroot and push too: a sample
+// hooked by Algorithm 1 / 3, pointer jumping, the bitmap, every entry against it.
+// On a plain solve the most frequent root plays the zero root's part from there
+// on (it is a root, so its key can become the smallest one).
+//
+// A skewed graph's giant component shows in a small sample; a uniform one's needs
+// about n / 2 entries, so where the device finds none in the small sample, one of
+// up to n entries is tried (lists of two entries per vertex and more). If that
+// shows none either, the whole-bitmap pass (passes 0) hooks what it must in P,
+// which costs it little; the tiles are not built and the direct hook takes the
+// list. Whole solves, always filtering / direct / as decided here (us): R-MAT
+// n = 3 M, 12 M entries 301 / 1412 / 285; ER n = 16 M, 60 M entries 4872 / 3970 /
+// 2353; grid n = 4 M, 8 M entries 9024 / 1050 / 1144.
+//
+// The regrouped zero-root hook of two partition passes takes its small sample by
+// the linking form instead, the first 1/1024 of the entries, which sets the bits
+// itself: rewriting a bitmap of that size would cost more than it saves (0.5 ms
+// of R-MAT-26's 10.2).
+constexpr uint64_t kSampleSmall = 1ull << 20;
+
+static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* bits,
+                        int passes, bool zr, bool own_bits, bool p32, uint32_t flags,
+                        hipStream_t stream) {
+    const bool split = split_walks(flags, n);
+    const bool sym = flags & CC_F_SYMMETRIC;
+    DevState* st = s->st;
+    const Gate always{}, again{&st->giant1, 0u}, on{passes ? &st->giant : nullptr, 1u};
+    const uint64_t full = std::min<uint64_t>(m / 4, n);
+    const uint64_t small = std::min({full, n / 16, kSampleSmall});
+    int rc;
+    auto compress = [&](Gate g) -> int {
+        if (zr)
+            k_compress<true><<<grid_for(n, kBlock, kZrGrid), kBlock, 0, stream>>>(P, n, st, bits, s->bmin, g);
+        else
+            k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, st, nullptr,
+                                                                                 nullptr, g);
+        CCM_HIP(hipGetLastError());
+        return CC_OK;
+    };
+    if (!passes) {
+        const int mode = zr ? kBitsZr : kBitsPick;
+        if ((rc = run_warm(n, m, E, P, st, zr, sym, small, always, stream))) return rc;
+        if ((rc = compress(always))) return rc;
+        if ((rc = run_giant_bits(n, m, E, P, bits, st, mode, 1, always, stream))) return rc;
+        if ((rc = run_warm(n, m, E, P, st, zr, sym, full, again, stream))) return rc;
+        if ((rc = compress(again))) return rc;
+        if ((rc = run_giant_bits(n, m, E, P, bits, st, mode, 0, again, stream))) return rc;
+        return run_hook_lds(n, m, E, P, bits, st, split, sym, s->device, stream);
+    }
+    const bool link_first = zr && passes == 2;
+    if (link_first) {
+        const uint64_t m0 = m >> 10;
+        if (m0 && (rc = run_hook(s, n, m0, (const uint32_t*)E.p, P,
+                                 CC_F_ZROOT | CC_F_NO_TILE | kHookLinkZ | (flags & CC_F_SYMMETRIC), stream)))
+            return rc;
+    } else if ((rc = run_warm(n, m, E, P, st, zr, sym, small, always, stream))) {
+        return rc;
+    }
+    if ((rc = run_find_giant(n, m, E, P, bits, st, zr, true, stream))) return rc;
+    const bool dense = m >= 2 * n;
+    if (dense || link_first) {
+        if ((rc = run_warm(n, m, E, P, st, zr, sym, dense ? full : small, again, stream))) return rc;
+        if ((rc = run_find_giant(n, m, E, P, bits, st, zr, false, stream))) return rc;
+    }
+    const Gate write = link_first ? Gate{&st->rebuild, 1u} : on;
+    if ((rc = compress(write))) return rc;
+    if ((rc = run_giant_bits(n, m, E, P, bits, st, zr ? kBitsZr : kBitsPlain, 0, write, stream))) return rc;
+    if ((rc = run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, on, stream))) return rc;
+    const Gate off{&st->giant, 0u};
+    const uint32_t g = grid_for(m, kBlock * kEPT, kGridCap);
+    const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
+    auto direct = [&](auto* e) {
+        if (!zr) k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);
+        else if (hook_links_z(flags, n))
+            k_hook_gated<true, 1, true><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);
+        else k_hook_gated<true, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);
+    };
+    if (E.wide) direct((const uint64_t*)E.p);
+    else direct((const uint32_t*)E.p);
+    CCM_HIP(hipGetLastError());
+    return CC_OK;
+}
+
 int run_hook(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P,
              uint32_t flags, hipStream_t stream) {
     if (!m) return CC_OK;
@@ -837,20 +940,22 @@ int run_hook(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
     const uint32_t sym = (flags & CC_F_SYMMETRIC) ? 1u : 0u;
     if (zr && (!s->zr_ready || s->cur_n != n))
         return fail(CC_EINVAL, "a CC_F_ZROOT hook needs cc_init then cc_zroot on the same n");
-    if (!(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE)) && !s->no_tiled && tiled_eligible(n, m, zr))
-        return run_hook_tiled(s, n, m, edges, P, stream, /*plain=*/!zr, sym != 0);
+    const bool regroup = !(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE)) && !s->no_tiled;
+    if (!zr && regroup && tiled_eligible(n, m, false))
+        return run_hook_buckets(s, n, m, edges, P, sym != 0, stream);
     const bool split = split_walks(flags, n);
     const uint32_t n32 = (uint32_t)n;
     uint32_t* zb = s->zbits;
     const uint32_t g = (uint32_t)blocks;
     const bool linkz = hook_links_z(flags, n);
-    if (zr && !(flags & CC_F_NO_SPLIT) && lds_eligible(n, m)) {
-        int rc = run_warm(n, m, edges, P, s->st, true, split, sym != 0, warm_entries(n, m), stream);
-        if (rc) return rc;
-        k_compress<true><<<grid_for(n, kBlock, kZrGrid), kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin);
-        CCM_HIP(hipGetLastError());
-        if ((rc = run_giant_bits(n, m, edges, P, zb, s->st, false, stream))) return rc;
-        return run_hook_lds(n, m, edges, P, zb, s->st, split, sym != 0, s->device, stream);
+    const bool lds = !(flags & CC_F_NO_SPLIT) && lds_eligible(n, m);
+    int passes = regroup ? filter_passes(n, m) : 0;
+    if (zr && (lds || passes)) {
+        const EdgeList E{edges, false};
+        FilterScratch fs{};
+        int rc = passes ? filter_scratch(s, n, m, passes, false, false, stream, &fs) : CC_OK;
+        if (!rc) return hook_by_bits(s, n, m, E, P, zb, passes, true, false, false, flags, stream);
+        if (tiled_eligible(n, m, true)) return rc;
     }
     if (!zr && !(flags & CC_F_NO_SPLIT) && hook_in_two_parts(n, m, split)) {
         // in two parts (ER n = 2^16 with 2^20 entries, whole solve: 0.150 -> 0.115 ms)
@@ -925,23 +1030,29 @@ int log_count_snap(Slot* s, uint64_t* host_word, hipStream_t stream) {
     return CC_OK;
 }
 
+// Compress and resolve against the bitmap of st->zroot's component. pub: it is the
+// caller's zero root (cc_canon reads what is recorded).
+static int zr_labels(Slot* s, uint64_t n, uint32_t* P, uint32_t* bits, bool final_labels, int pub,
+                     Gate gate, hipStream_t stream) {
+    const uint32_t g = grid_for(n, kBlock, kZrGrid);
+    k_compress<true><<<g, kBlock, 0, stream>>>(P, n, s->st, bits, s->bmin, gate);
+    CCM_HIP(hipGetLastError());
+    if (final_labels)
+        k_resolve<true><<<g, kBlock, 0, stream>>>(P, n, s->st, bits, s->bmin, g, pub, gate);
+    else
+        k_resolve<false><<<g, kBlock, 0, stream>>>(P, n, s->st, bits, s->bmin, g, pub, gate);
+    CCM_HIP(hipGetLastError());
+    return CC_OK;
+}
+
 int run_compress(Slot* s, uint64_t n, uint32_t* P, uint32_t flags, hipStream_t stream,
                  bool final_labels) {
-    uint32_t* zb = (flags & kGiant) ? s->gbits : s->zbits;
-    final_labels = final_labels || (flags & CC_F_CANON);
     if (flags & CC_F_ZROOT) {
-        const int pub = !(flags & kGiant);
-        if (pub && (!s->zr_ready || s->cur_n != n))
+        if (!s->zr_ready || s->cur_n != n)
             return fail(CC_EINVAL, "a CC_F_ZROOT compress needs cc_init then cc_zroot on the same n");
-        const uint32_t g = grid_for(n, kBlock, kZrGrid);
-        k_compress<true><<<g, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin);
-        CCM_HIP(hipGetLastError());
-        if (final_labels) k_resolve<true><<<g, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin, g, pub);
-        else k_resolve<false><<<g, kBlock, 0, stream>>>(P, n, s->st, zb, s->bmin, g, pub);
-    } else {
-        k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, s->st, nullptr,
-                                                                             nullptr);
+        return zr_labels(s, n, P, s->zbits, final_labels || (flags & CC_F_CANON), 1, Gate{}, stream);
     }
+    k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, s->st, nullptr, nullptr);
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -1067,17 +1178,22 @@ int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const ui
 
 static uint64_t al256(uint64_t x) { return (x + 255) & ~255ull; }
 
-uint64_t solve_scratch_bytes(uint64_t n, uint64_t m, uint32_t flags) {
+uint64_t solve_scratch_bytes(uint64_t n, uint64_t m, uint32_t flags, bool lean) {
     const bool zr = flags & CC_F_ZROOT;
     uint64_t b = 0;
     if (zr) b += al256(4 * ((n + 31) / 32));
     if (zr && (flags & CC_F_ZROOT_EXACT)) b += al256(4 * n);
-    if (m && !(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE)) && tiled_eligible(n, m, zr))
-        b += al256(tiled_scratch_bytes(n, m, !zr));
+    if (m && !(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE))) {
+        const int passes = filter_passes(n, m);
+        if (passes && (!lean || (zr && tiled_eligible(n, m, true))))
+            b += filter_scratch_bytes(n, m, passes, !zr, false);
+        else if (!zr && tiled_eligible(n, m, false))
+            b += bucket_scratch_bytes(n, m);
+    }
     return b;
 }
 
-void slot_lend_scratch(Slot* s, char* block, uint64_t n, uint64_t m, uint32_t flags,
+void slot_lend_scratch(Slot* s, char* block, uint64_t bytes, uint64_t n, uint32_t flags,
                        LentScratch* saved) {
     saved->zbits = s->zbits;
     saved->zbits_cap = s->zbits_cap;
@@ -1102,10 +1218,8 @@ void slot_lend_scratch(Slot* s, char* block, uint64_t n, uint64_t m, uint32_t fl
         s->deg_cap = n;
         q += al256(4 * n);
     }
-    if (m && !(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE)) && tiled_eligible(n, m, zr)) {
-        s->tiled.buf = q;
-        s->tiled.cap = tiled_scratch_bytes(n, m, !zr);
-    }
+    s->tiled.buf = q;
+    s->tiled.cap = bytes - (uint64_t)(q - block);
     s->no_grow = true;
 }
 
@@ -1119,20 +1233,20 @@ void slot_return_scratch(Slot* s, const LentScratch* saved) {
     s->zr_ready = false;
 }
 
-// The hook of a plain whole solve whose bitmap fits LDS: a sample hooked by
-// Algorithm 1, pointer jumping, the bitmap of the giant component's root, every
-// entry against it. From there on the giant component's root plays the zero
-// root's part (it is a root, so its key can become the smallest one).
-static int run_hook_giant(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P,
-                          uint32_t flags, hipStream_t stream) {
-    const bool split = split_walks(flags, n);
-    const bool sym = flags & CC_F_SYMMETRIC;
-    int rc = run_warm(n, m, edges, P, s->st, false, split, sym, warm_entries(n, m), stream);
+// A plain whole solve after init by the giant component.
+int run_giant(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* bits, int passes,
+              bool p32, uint32_t flags, hipStream_t stream) {
+    int rc = hook_by_bits(s, n, m, E, P, bits, passes, false, true, p32, flags, stream);
     if (rc) return rc;
-    k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(P, n, s->st, nullptr, nullptr);
-    CCM_HIP(hipGetLastError());
-    if ((rc = run_giant_bits(n, m, edges, P, s->gbits, s->st, true, stream))) return rc;
-    return run_hook_lds(n, m, edges, P, s->gbits, s->st, split, sym, s->device, stream);
+    const Gate on{passes ? &s->st->giant : nullptr, 1u};
+    if ((rc = zr_labels(s, n, P, bits, true, 0, on, stream))) return rc;
+    if (passes) {
+        // hooked direct: no root plays the zero root's part, the bitmap is unset
+        k_compress<false><<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(
+            P, n, s->st, nullptr, nullptr, Gate{&s->st->giant, 0u});
+        CCM_HIP(hipGetLastError());
+    }
+    return CC_OK;
 }
 
 int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* L,
@@ -1145,13 +1259,19 @@ int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* 
         if ((rc = run_push(s, n, m, edges, L, stream))) return rc;
     }
     if ((rc = cohere(stream))) return rc;
-    const bool giant = !(flags & (CC_F_ZROOT | CC_F_NO_SPLIT)) && lds_eligible(n, m);
-    if (giant) {
-        if ((rc = run_hook_giant(s, n, m, edges, L, flags, stream))) return rc;
-        flags |= CC_F_ZROOT | kGiant;
-    } else if ((rc = run_hook(s, n, m, edges, L, flags, stream))) {
-        return rc;
+    if (!(flags & (CC_F_ZROOT | CC_F_NO_SPLIT))) {
+        const EdgeList E{edges, false};
+        FilterScratch fs;
+        const int passes = (flags & CC_F_NO_TILE) || s->no_tiled ? 0 : filter_passes(n, m);
+        uint32_t* bits = nullptr;
+        if (lds_eligible(n, m)) bits = s->gbits;
+        else if (passes && !filter_scratch(s, n, m, passes, true, false, stream, &fs)) bits = fs.bits;
+        if (bits) {
+            if ((rc = run_giant(s, n, m, E, L, bits, passes, false, flags, stream))) return rc;
+            return cohere(stream);
+        }
     }
+    if ((rc = run_hook(s, n, m, edges, L, flags, stream))) return rc;
     if ((rc = run_compress(s, n, L, flags, stream, true))) return rc;
     return cohere(stream);
 }

@@ -6,6 +6,21 @@
 
 namespace ccm {
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+
+// Entry i of a COO list as 32-bit IDs, streamed past the caches' reuse. A 64-bit
+// ID above 2^32 - 2 reads as 2^32 - 1, which is out of range for every n here.
+__device__ __forceinline__ u32x2 load_entry(const uint32_t* edges, uint64_t i) {
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(edges) + i);
+}
+__device__ __forceinline__ u32x2 load_entry(const uint64_t* edges, uint64_t i) {
+    const u64x2 x = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(edges) + i);
+    return u32x2{x.x < kEmpty ? (uint32_t)x.x : kEmpty, x.y < kEmpty ? (uint32_t)x.y : kEmpty};
+}
+
+__device__ __forceinline__ bool gated_off(Gate g) { return g.word && ld_agent(g.word) != g.want; }
+
 // ---- keys: Formula 1's R used as an order while P stores vertex IDs ----------
 // key(x) = x on the plain path; with a zero root z, key(z) = 0 and key(x) = x+1.
 template <bool ZR>
@@ -109,6 +124,77 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
         x = y < x ? y : x;
     }
     return x;
+}
+
+
+// ---- per-wave queues of the hooks that test a bitmap in LDS -----------------------
+// Entries that are not dropped at once gather in a wave's first queue and are
+// looked at again together, one per lane, when the next ones would not fit: most
+// then only mark an endpoint (settle). The few with neither endpoint marked
+// gather in the second queue, so that the walks and CASes of up to 64 of them
+// overlap; linked where they are found, a handful of lanes would hold the wave
+// for several memory round trips at nearly every settling (R-MAT n = 2^22,
+// 2^26 entries: filter 472 -> 330 us).
+constexpr uint32_t kQueueCap = 64;
+struct WaveQueues {
+    u32x2 *pq, *lq;          // kQueueCap slots each, in LDS
+    uint32_t pn = 0, ln = 0; // wave-uniform
+};
+
+// Keeps the compiler from moving LDS accesses across it; the lanes of a wave
+// execute together and its LDS operations complete in issue order.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// settle(x): marks the other endpoint when exactly one is marked; true when
+// neither is. hook(x): hooks x in P. Both are called for one entry per lane;
+// every function here is called by the whole wave.
+template <class Settle, class Hook>
+__device__ __forceinline__ void queue_hook(WaveQueues& q, int lane, const Settle& settle,
+                                           const Hook& hook) {
+    wave_order();
+    if ((uint32_t)lane < q.ln) {
+        const u32x2 x = q.lq[lane];
+        if (settle(x)) hook(x);      // it may have been marked since
+    }
+    q.ln = 0;
+    wave_order();
+}
+template <class Settle, class Hook>
+__device__ __forceinline__ void queue_settle(WaveQueues& q, int lane, const Settle& settle,
+                                             const Hook& hook) {
+    wave_order();
+    const bool act = (uint32_t)lane < q.pn;
+    const u32x2 x = act ? q.pq[lane] : u32x2{0u, 0u};
+    const bool keep = act && settle(x);
+    const uint64_t ball = __ballot(keep);
+    const uint32_t c = (uint32_t)__popcll(ball);
+    q.pn = 0;
+    if (c) {
+        if (q.ln + c > kQueueCap) queue_hook(q, lane, settle, hook);
+        if (keep) q.lq[q.ln + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] = x;
+        q.ln += c;
+    }
+    wave_order();
+}
+template <class Settle, class Hook>
+__device__ __forceinline__ void queue_push(WaveQueues& q, int lane, bool pend, u32x2 x,
+                                           const Settle& settle, const Hook& hook) {
+    const uint64_t ball = __ballot(pend);
+    if (!ball) return;
+    const uint32_t c = (uint32_t)__popcll(ball);
+    if (q.pn + c > kQueueCap) queue_settle(q, lane, settle, hook);
+    if (pend) q.pq[q.pn + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] = x;
+    q.pn += c;
+}
+template <class Settle, class Hook>
+__device__ __forceinline__ void queue_finish(WaveQueues& q, int lane, const Settle& settle,
+                                             const Hook& hook) {
+    if (q.pn) queue_settle(q, lane, settle, hook);
+    if (q.ln) queue_hook(q, lane, settle, hook);
 }
 
 }  // namespace ccm

@@ -173,7 +173,7 @@ int run_large(cc_server* s, Worker& w, Req* r) {
     if (r->m)
         CCM_HIP(hipMemcpyAsync(d_edges, r->eh, 8 * r->m, hipMemcpyHostToDevice, w.stream));
     LentScratch own;
-    slot_lend_scratch(&w.slot, d_scratch, r->n, r->m, r->flags, &own);
+    slot_lend_scratch(&w.slot, d_scratch, r->scratch, r->n, r->flags, &own);
     int rc = run_solve(&w.slot, r->n, r->m, d_edges, d_L, r->flags, 0, w.stream);
     if (!rc) {
         const hipError_t e = hipMemcpyAsync(r->Lh, d_L, 4 * r->n, hipMemcpyDeviceToHost, w.stream);
@@ -376,8 +376,10 @@ extern "C" int cc_serve_submit(cc_server* s, uint64_t n, uint64_t m, const uint3
         return fail(CC_EINVAL, "flag not accepted by the server (CC_F_ZROOT_HINT, unknown)");
     Req* r = new Req();
     r->n = n; r->m = m; r->eh = edges_host; r->Lh = L_host; r->flags = flags;
-    r->scratch = solve_scratch_bytes(n, m, flags);
-    r->foot = align_up(8 * m) + align_up(4 * n) + r->scratch;
+    r->scratch = solve_scratch_bytes(n, m, flags, false);
+    const uint64_t base = align_up(8 * m) + align_up(4 * n);
+    if (base + r->scratch > s->arena.size) r->scratch = solve_scratch_bytes(n, m, flags, true);
+    r->foot = base + r->scratch;
     const uint64_t stage_need = align_up(8 * m) + align_up(4 * n) + 512;
     r->small = n <= s->opts.small_n && n < (1ull << 31) && stage_need <= s->stage_cap;
     if (!r->small && r->foot > s->arena.size) {

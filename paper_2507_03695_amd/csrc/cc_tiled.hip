@@ -37,8 +37,6 @@
 
 namespace ccm {
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
 constexpr int kSliceBits = 19;                       // 2^19 vertices per slice
 constexpr uint32_t kSliceWords = (1u << kSliceBits) / 32;   // 16384 words = 64 KB
 constexpr uint32_t kLoMask = (1u << kSliceBits) - 1;
@@ -68,15 +66,16 @@ constexpr int kC2 = 8192;                            // level-2 chunk (entries)
 constexpr int kPartBlock = 1024;
 constexpr int kPartEPT = kC1 / kPartBlock;           // 8
 
-// Exclusive scan of cnt[0..R) into start[0..R] by the first wave (R <= 256);
+// Exclusive scan of cnt[0..R) into start[0..R] by the first wave (R <= 64 * PER);
 // start[R] is the total.
-__device__ __forceinline__ void wave_scan_256(const uint32_t* cnt, uint32_t* start, int R) {
+template <int PER>
+__device__ __forceinline__ void wave_scan(const uint32_t* cnt, uint32_t* start, int R) {
     const int lane = threadIdx.x & 63;
     if (threadIdx.x < 64) {
-        uint32_t c[4], s = 0;
+        uint32_t c[PER], s = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int d = lane * 4 + j;
+        for (int j = 0; j < PER; ++j) {
+            const int d = lane * PER + j;
             c[j] = d < R ? cnt[d] : 0u;
             s += c[j];
         }
@@ -88,8 +87,8 @@ __device__ __forceinline__ void wave_scan_256(const uint32_t* cnt, uint32_t* sta
         }
         uint32_t run = incl - s;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int d = lane * 4 + j;
+        for (int j = 0; j < PER; ++j) {
+            const int d = lane * PER + j;
             if (d < R) start[d] = run;
             run += c[j];
         }
@@ -98,20 +97,21 @@ __device__ __forceinline__ void wave_scan_256(const uint32_t* cnt, uint32_t* sta
 }
 
 // ---- 1. level-1 partition by the first endpoint's slice -----------------------------
-__global__ __launch_bounds__(kPartBlock) void k_t1_part(const uint32_t* __restrict__ edges,
+template <typename T>
+__global__ __launch_bounds__(kPartBlock) void k_t1_part(const T* __restrict__ edges,
                                                         uint64_t m, uint32_t n, int R,
                                                         uint64_t nch1, uint32_t* __restrict__ t1w,
                                                         uint16_t* __restrict__ t1h,
                                                         uint16_t* __restrict__ segT,
                                                         uint32_t* __restrict__ cnt1,
-                                                        DevState* st, uint32_t sym) {
+                                                        DevState* st, uint32_t sym, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ u32x2 stage[kC1];
     __shared__ uint32_t hist[kMaxSlices + 1];
     __shared__ uint32_t start[kMaxSlices + 1];
     const uint64_t c = blockIdx.x;
     for (int i = threadIdx.x; i <= kMaxSlices; i += kPartBlock) hist[i] = 0;
     __syncthreads();
-    const u32x2* E = reinterpret_cast<const u32x2*>(edges);
     u32x2 e[kPartEPT];
     uint16_t rank[kPartEPT];
     bool bad = false;
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t1_part(const uint32_t* __restri
     for (int k = 0; k < kPartEPT; ++k) {
         // unconditional load (clamped index): keeps all loads of the thread in flight
         const uint64_t i = c * kC1 + (uint64_t)k * kPartBlock + threadIdx.x;
-        e[k] = __builtin_nontemporal_load(E + (i < m ? i : m - 1));
+        e[k] = load_entry(edges, i < m ? i : m - 1);
     }
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k) {
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t1_part(const uint32_t* __restri
         if (live) rank[k] = (uint16_t)atomicAdd(&hist[e[k].x >> kSliceBits], 1u);
     }
     __syncthreads();
-    wave_scan_256(hist, start, R);
+    wave_scan<4>(hist, start, R);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k)
@@ -164,7 +164,8 @@ constexpr int kScanBlock = 256;
 
 __global__ __launch_bounds__(kScanBlock) void k_t1_tsum(const uint32_t* __restrict__ cnt1,
                                                         uint64_t nch1, uint32_t ntile,
-                                                        uint32_t* __restrict__ tsum) {
+                                                        uint32_t* __restrict__ tsum, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ uint32_t ws[kScanBlock / 64];
     const uint64_t a = blockIdx.x / ntile, tile = blockIdx.x % ntile;
     const uint32_t* row = cnt1 + a * nch1;
@@ -186,7 +187,8 @@ __global__ __launch_bounds__(kScanBlock) void k_t1_tsum(const uint32_t* __restri
 __global__ __launch_bounds__(kScanBlock) void k_t1_scan(const uint32_t* __restrict__ cnt1,
                                                         uint64_t nch1, uint32_t ntile,
                                                         const uint32_t* __restrict__ tsum,
-                                                        uint32_t* __restrict__ pre1) {
+                                                        uint32_t* __restrict__ pre1, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ uint32_t ws[kScanBlock / 64];
     __shared__ uint32_t s_off;
     const uint64_t a = blockIdx.x / ntile, tile = blockIdx.x % ntile;
@@ -233,7 +235,8 @@ __global__ __launch_bounds__(kScanBlock) void k_t1_scan(const uint32_t* __restri
 // chunk of bucket a; cbase[R] is the total.
 __global__ __launch_bounds__(256) void k_t1_bases(const uint32_t* __restrict__ pre1, uint64_t nch1,
                                                   int R, uint64_t* __restrict__ base2,
-                                                  uint32_t* __restrict__ cbase) {
+                                                  uint32_t* __restrict__ cbase, Gate gate) {
+    if (gated_off(gate)) return;
     // one thread per slice (R <= 256): sizes, then block-wide exclusive prefixes
     __shared__ uint64_t s_b[256];
     __shared__ uint32_t s_c[256];
@@ -270,7 +273,8 @@ __global__ __launch_bounds__(256) void k_t1_bases(const uint32_t* __restrict__ p
 __global__ __launch_bounds__(256) void k_t2_bounds(const uint32_t* __restrict__ pre1, uint64_t nch1,
                                                    int R, const uint32_t* __restrict__ cbase,
                                                    const uint64_t* __restrict__ base2,
-                                                   uint32_t* __restrict__ desc) {
+                                                   uint32_t* __restrict__ desc, Gate gate) {
+    if (gated_off(gate)) return;
     const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     if (id >= (uint64_t)R * nch1) return;
     const uint64_t a = id / nch1, c = id % nch1;
@@ -312,7 +316,7 @@ __device__ __forceinline__ void t2_sort_write(const u32x2 (&e)[kPartEPT], uint32
         if (i < cnt) rank[k] = (uint16_t)atomicAdd(&hist[e[k].y >> kSliceBits], 1u);
     }
     __syncthreads();
-    wave_scan_256(hist, start, R);
+    wave_scan<4>(hist, start, R);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k)
@@ -394,7 +398,8 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_part(const uint32_t* __restri
                                                         const uint32_t* __restrict__ cbase,
                                                         const uint32_t* __restrict__ desc,
                                                         L2Buf tmp2, uint16_t* __restrict__ run2T,
-                                                        uint64_t nch2) {
+                                                        uint64_t nch2, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ u32x2 stage[kC2];
     __shared__ uint8_t owner[kC2];
     __shared__ uint32_t s_pre[kWin2 + 1];
@@ -669,9 +674,8 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_csr(const uint64_t* __restric
 // does not consult the bitmap.
 constexpr int kHook3Block = 1024;
 constexpr int kWaves3 = kHook3Block / 64;
-constexpr int kWin3 = 2000;      // level-2 chunks per window
+constexpr int kWin3 = 1900;      // level-2 chunks per window
 constexpr int kRunsInFlight = 12; // entries a lane loads at once (a wave: 12 x 64 consecutive)
-constexpr int kPendQueue = 127;  // per-wave LDS staging of entries that need a second look
 
 // Exclusive scan in place of n <= 2 * kHook3Block values (x[n] receives the
 // total); every thread of the workgroup calls it.
@@ -711,7 +715,8 @@ constexpr int kBPerBlock = 2;    // second-endpoint slices handled by one workgr
 __global__ __launch_bounds__(256) void k_t3_regions(const uint16_t* __restrict__ run2T,
                                                     uint64_t nch2, int R,
                                                     const uint32_t* __restrict__ cbase,
-                                                    uint32_t* __restrict__ wgsize) {
+                                                    uint32_t* __restrict__ wgsize, Gate gate) {
+    if (gated_off(gate)) return;
     // one block per (a, bg): the group's entries summed over bucket a's chunks
     __shared__ uint32_t ws[4];
     const int nbg = (R + kBPerBlock - 1) / kBPerBlock;
@@ -731,7 +736,8 @@ __global__ __launch_bounds__(256) void k_t3_regions(const uint16_t* __restrict__
 // before bg. One thread per a.
 __global__ __launch_bounds__(256) void k_t3_offsets(const uint32_t* __restrict__ wgsize, int R,
                                                     const uint64_t* __restrict__ base2,
-                                                    uint64_t* __restrict__ wgoff) {
+                                                    uint64_t* __restrict__ wgoff, Gate gate) {
+    if (gated_off(gate)) return;
     const int a = blockIdx.x * 256 + threadIdx.x;
     if (a >= R) return;
     const int nbg = (R + kBPerBlock - 1) / kBPerBlock;
@@ -777,127 +783,226 @@ __device__ __forceinline__ uint32_t t3_offset(const uint32_t* s_pre, const uint3
     return off;
 }
 
-// Second look at up to 64 pending entries of this wave (lane l takes pq[l],
-// endpoints relative to the slices' first IDs), with the bits as they are now:
-// both marked, dropped; one marked, the other is marked (LDS, and the global
-// word when this set the bit); neither, kept: written to the workgroup's
-// survivor region (level-1 packing, its place from an LDS counter).
-__device__ __forceinline__ void t3_settle(const u32x2* pq, uint32_t cnt, int lane, uint32_t* sa,
-                                          uint32_t* lb, uint32_t abase, uint32_t bbase,
-                                          uint32_t* zbits, uint32_t* ow, uint16_t* oh,
-                                          uint32_t cap, uint32_t* s_used, DevState* st) {
-    const bool act = (uint32_t)lane < cnt;
-    const u32x2 x = act ? pq[lane] : u32x2{0u, 0u};
-    const uint32_t iu = x.x >> 5, iv = x.y >> 5;
-    const uint32_t bu = 1u << (x.x & 31), bv = 1u << (x.y & 31);
-    const bool mu = (sa[iu] & bu) != 0u, mv = (lb[iv] & bv) != 0u;
-    if (act && mu != mv) {
-        // the entry's whole effect: mark the unmarked endpoint
-        uint32_t* w = mu ? &lb[iv] : &sa[iu];
-        const uint32_t bit = mu ? bv : bu;
-        const uint32_t y = mu ? bbase + x.y : abase + x.x;
-        if (!(atomicOr(w, bit) & bit)) atomicOr(&zbits[y >> 5], 1u << (y & 31));
-    }
-    const bool keep = act && !mu && !mv;
-    const uint64_t ball = __ballot(keep);
-    if (ball) {
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(s_used, (uint32_t)__popcll(ball));
-        base = __shfl(base, 0, 64);
-        if (keep) {
-            const uint32_t i = base + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull));
-            if (i < cap) {
-                const uint32_t v = bbase + x.y;
-                ow[i] = pk_w(x.x, v);
-                oh[i] = (uint16_t)(v >> (32 - kSliceBits));
-            } else {
-                // cannot happen (the region holds all of the workgroup's entries)
-                atomicOr(&st->status, kStatusInternal);
-            }
+// The marks a workgroup added to its copy of a slice go to the global bitmap in
+// one pass over the words, with one atomic per word that gained bits there (an
+// atomic per mark would repeat every mark in each of the slice's workgroups:
+// R-MAT n = 2^22, 2^26 entries: filter 782 -> 472 us).
+__device__ __forceinline__ void t3_flush(const uint32_t* w, uint32_t* zbits, uint64_t w0,
+                                         uint64_t words) {
+    constexpr int PER = 4;
+    for (uint32_t at = threadIdx.x; at < kSliceWords; at += PER * kHook3Block) {
+        uint32_t g[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint64_t i = w0 + at + (uint32_t)k * kHook3Block;
+            g[k] = i < words ? ld_agent(&zbits[i]) : kEmpty;
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t i = at + (uint32_t)k * kHook3Block;
+            const uint32_t add = w[i] & ~g[k];
+            if (add) atomicOr(&zbits[w0 + i], add);
         }
     }
 }
 
+// What a launch of the filter does with the entries that neither bit settles.
+//  kMarkTiles  only marks (the first eighth of each workgroup's entries of the
+//              one-pass tiles): the entries all come again in the full pass. Each
+//              workgroup knows only the marks its copies held at the start and
+//              those of its own entries; this launch's flush shows every workgroup
+//              the others' marks before any entry is hooked (R-MAT n = 2^22, 2^26
+//              entries: both passes 335 us, the full one alone 472).
+//  kFullTiles  the one-pass tiles: hooked in P from the wave's queue
+//  The one-pass tiles are one index space, tile after tile, cut into equal parts,
+//  one per workgroup: lists whose first endpoints lie in few slices (a share of a
+//  larger graph, sorted rows) fill few tiles.
+//  kFullRuns   the two-pass tiles: kept for the survivor hook (a tile is short,
+//              2^16 entries on R-MAT-26, and hooking its rest at its end
+//              would leave the CU waiting: filter 4.2 ms against 2.9 + 0.4)
+enum FilterMode { kMarkTiles, kFullTiles, kFullRuns };
+constexpr uint32_t kMarkPart = 8;
+constexpr uint32_t kTileCost = 8192;  // entries' worth of a tile's fixed time (8 us)
+
+template <int MODE>
 __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                                                            const uint16_t* __restrict__ run2T,
                                                            uint64_t nch2, int R,
+                                                           const uint32_t* __restrict__ wcnt,
                                                            const uint64_t* __restrict__ base2,
                                                            const uint32_t* __restrict__ cbase,
                                                            uint32_t* zbits, uint64_t words,
-                                                           uint32_t* __restrict__ sw,
+                                                           uint32_t* P, uint32_t* __restrict__ sw,
                                                            uint16_t* __restrict__ sh,
                                                            const uint64_t* __restrict__ wgoff,
                                                            uint32_t* __restrict__ wgcnt,
-                                                           DevState* st) {
+                                                           DevState* st, Gate gate) {
+    if (gated_off(gate)) return;
+    constexpr bool TILES = MODE != kFullRuns;
     __shared__ uint32_t sa[kSliceWords];
     __shared__ uint32_t sb[kSliceWords];
     __shared__ uint32_t s_off[kWin3];
     __shared__ uint32_t s_pre[kWin3 + 1];
-    __shared__ u32x2 pqueue[kWaves3 * kPendQueue];
+    __shared__ u32x2 s_queue[kWaves3 * 2 * kQueueCap];
     __shared__ uint32_t wsum[kWaves3 + 1];
-    __shared__ uint32_t s_used;
+    const uint32_t z = ld_agent(&st->zroot);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // Launch order: consecutive workgroups take different a (and spread over
     // the b groups), so the workgroups running at the same time hold few
     // copies of any one slice and see each other's marks through the global
     // bitmap sooner. (a, bg) = (i mod R, (i div R + a) mod nbg) is a bijection.
-    const int nbg = (R + kBPerBlock - 1) / kBPerBlock;
-    const int a = (int)(blockIdx.x % (uint32_t)R);
-    const int bg = (int)((blockIdx.x / (uint32_t)R + (uint32_t)a) % (uint32_t)nbg);
-    const uint32_t wi = (uint32_t)a * (uint32_t)nbg + (uint32_t)bg;   // region index
-    const uint32_t cb = cbase[a];
-    const uint32_t nch = cbase[a + 1] - cb;
-    if (nch == 0) {
-        if (threadIdx.x == 0) wgcnt[wi] = 0;
-        return;
+    constexpr int kB = TILES ? 1 : kBPerBlock;
+    const uint32_t nbg = ((uint32_t)R + kB - 1) / kB;
+    int a = (int)(blockIdx.x % (uint32_t)R);
+    const int bg = (int)((blockIdx.x / (uint32_t)R + (uint32_t)a) % nbg);
+    uint32_t cb = 0, nch = (uint32_t)nch2;               // first chunk, chunks
+    const uint32_t* srcw = tmp2.w;
+    const uint8_t* srch = tmp2.h;
+    // one-pass tiles: this workgroup's entries [lo, hi) of the tiles' index space;
+    // d is the tile they are in now, at its index td, nd wide; a tile's width is its
+    // entries and kTileCost more, the time its slices take to load and write back
+    const uint32_t nwin = ((uint32_t)nch2 + kWin3 - 1) / kWin3;
+    uint32_t lo = 0, hi = 0, d = 0, td = 0, nd = 0;
+    if (TILES) {
+        const uint32_t tiles = (uint32_t)(R * R);
+        for (uint32_t i = threadIdx.x; i < tiles; i += kHook3Block) {
+            uint32_t t = 0;
+            for (uint32_t w = 0; w < nwin; ++w) t += wcnt[(uint64_t)i * nwin + w];
+            s_off[i] = t ? t + kTileCost : 0u;
+        }
+        __syncthreads();
+        wave_scan<8>(s_off, s_pre, (int)tiles);
+        __syncthreads();
+        const uint64_t all = s_pre[tiles];
+        lo = (uint32_t)(all * blockIdx.x / gridDim.x);
+        hi = (uint32_t)(all * (blockIdx.x + 1ull) / gridDim.x);
+        if (lo >= hi) return;
+        if (MODE == kMarkTiles) hi = lo + (hi - lo + kMarkPart - 1) / kMarkPart;
+        for (uint32_t i = threadIdx.x; i < tiles; i += kHook3Block)
+            if (s_pre[i] <= lo && lo < s_pre[i + 1]) { wsum[0] = i; wsum[1] = s_pre[i]; wsum[2] = s_off[i]; }
+        __syncthreads();
+        d = __builtin_amdgcn_readfirstlane(wsum[0]);
+        td = __builtin_amdgcn_readfirstlane(wsum[1]);
+        nd = __builtin_amdgcn_readfirstlane(wsum[2]);
+        a = (int)(d / (uint32_t)R);
+        __syncthreads();
+    } else {
+        cb = cbase[a];
+        nch = cbase[a + 1] - cb;
+        srcw = tmp2.w + base2[a];
+        srch = tmp2.h + base2[a];
     }
-    if (threadIdx.x == 0) s_used = 0;
-    uint32_t* ow = sw + wgoff[wi];
-    uint16_t* oh = sh + wgoff[wi];
-    const uint32_t cap = (uint32_t)(wgoff[wi + 1] - wgoff[wi]);
+    const uint32_t wi = (uint32_t)a * nbg + (uint32_t)bg;   // region index (kFullRuns)
+    __shared__ uint32_t s_used;
+    if (MODE == kFullRuns && threadIdx.x == 0) {
+        s_used = 0;
+        if (nch == 0) wgcnt[wi] = 0;
+    }
+    if (nch == 0) return;
+    uint32_t* ow = nullptr;
+    uint16_t* oh = nullptr;
+    uint32_t cap = 0;
+    if (MODE == kFullRuns) {
+        ow = sw + wgoff[wi];
+        oh = sh + wgoff[wi];
+        cap = (uint32_t)(wgoff[wi + 1] - wgoff[wi]);
+    }
     constexpr int PER = kSliceWords / kHook3Block;       // 16 words per thread per slice
-    {
-        const uint64_t wa = (uint64_t)a * kSliceWords;
-        uint32_t xa[PER];
+    auto load_slice = [&](uint32_t* dst, int slice) {
+        const uint64_t w0 = (uint64_t)slice * kSliceWords;
+        uint32_t x[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const uint64_t i = (uint64_t)k * kHook3Block + threadIdx.x;
-            xa[k] = wa + i < words ? zbits[wa + i] : 0u;
+            x[k] = w0 + i < words ? zbits[w0 + i] : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < PER; ++k) sa[(uint32_t)k * kHook3Block + threadIdx.x] = xa[k];
-    }
-    const uint32_t abase = (uint32_t)a << kSliceBits;
-    const uint32_t* srcw = tmp2.w + base2[a];
-    const uint8_t* srch = tmp2.h + base2[a];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    u32x2* pq = pqueue + wave * kPendQueue;
+        for (int k = 0; k < PER; ++k) dst[(uint32_t)k * kHook3Block + threadIdx.x] = x[k];
+    };
+    load_slice(sa, a);
+    WaveQueues q;
+    q.pq = s_queue + wave * 2 * kQueueCap;
+    q.lq = q.pq + kQueueCap;
     constexpr uint32_t kRange = 64 * kRunsInFlight;      // entries per wave per range
     constexpr uint32_t kStep = kWaves3 * kRange;
-    for (int bi = 0; bi < kBPerBlock; ++bi) {
-        const int b = bg * kBPerBlock + bi;
-        if (b >= R) break;
-        __syncthreads();                                  // previous slice b fully used
-        if (b != a) {
-            const uint64_t wb = (uint64_t)b * kSliceWords;
-            uint32_t xb[PER];
-#pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const uint64_t i = (uint64_t)k * kHook3Block + threadIdx.x;
-                xb[k] = wb + i < words ? zbits[wb + i] : 0u;
+    for (int bi = 0; TILES || bi < kB; ++bi) {
+        if (TILES && bi) {
+            // the next tile that holds entries (there is one: td + nd < hi)
+            if (td + nd >= hi) break;
+            do {
+                td += nd;
+                ++d;
+                nd = 0;
+                for (uint32_t w = 0; w < nwin; ++w) nd += wcnt[(uint64_t)d * nwin + w];
+                nd = nd ? nd + kTileCost : 0u;
+            } while (nd == 0);
+            const int na = (int)(d / (uint32_t)R);
+            if (na != a) {
+                __syncthreads();
+                t3_flush(sa, zbits, (uint64_t)a * kSliceWords, words);
+                __syncthreads();
+                a = na;
+                load_slice(sa, a);
             }
-#pragma unroll
-            for (int k = 0; k < PER; ++k) sb[(uint32_t)k * kHook3Block + threadIdx.x] = xb[k];
         }
+        const int b = TILES ? (int)(d % (uint32_t)R) : bg * kB + bi;
+        if (b >= R) break;
+        // the entries [jlo, jhi) of the tile are this workgroup's
+        const uint32_t jlo = TILES && lo > td ? lo - td : 0u;
+        const uint32_t jhi = TILES ? min(hi - td, nd - kTileCost) : 0xFFFFFFFFu;
+        if (TILES && jlo >= jhi) continue;                // only the cost's end of the tile
+        __syncthreads();                                  // previous slice b fully used
+        if (b != a) load_slice(sb, b);
         uint32_t* lb = (a == b) ? sa : sb;
+        const uint32_t abase = (uint32_t)a << kSliceBits;
         const uint32_t bbase = (uint32_t)b << kSliceBits;
-        uint32_t pn = 0;                                  // wave-uniform pending count
+        const uint64_t row = TILES ? d : (uint32_t)b;
+        uint32_t jw = 0;                                  // tile index of the window's first
+        // Second looks (endpoints relative to the slices' first IDs), with the bits as
+        // they are then: both marked, dropped; one marked, the other is marked (in
+        // LDS; t3_flush takes the slice's new marks to the global bitmap); neither,
+        // hooked in P (Algorithm 3, path splitting).
+        auto settle = [&](u32x2 x) {
+            const bool mu = (sa[x.x >> 5] >> (x.x & 31)) & 1u, mv = (lb[x.y >> 5] >> (x.y & 31)) & 1u;
+            if (mu && !mv) atomicOr(&lb[x.y >> 5], 1u << (x.y & 31));
+            if (mv && !mu) atomicOr(&sa[x.x >> 5], 1u << (x.x & 31));
+            return !mu && !mv;
+        };
+        auto hook = [&](u32x2 x) {
+            const uint32_t u = abase + x.x, v = bbase + x.y;
+            if (MODE == kMarkTiles) return;
+            if (MODE == kFullRuns) {
+                // one lane reserves room for all that are here
+                const uint64_t here = __ballot(true);
+                const int first = __ffsll((unsigned long long)here) - 1;
+                uint32_t at = 0;
+                if (lane == first) at = atomicAdd(&s_used, (uint32_t)__popcll(here));
+                at = __shfl(at, first, 64) + (uint32_t)__popcll(here & ((1ull << lane) - 1ull));
+                if (at < cap) {
+                    ow[at] = pk_w(x.x, v);
+                    oh[at] = (uint16_t)(v >> (32 - kSliceBits));
+                } else {
+                    // cannot happen (the region holds all of the workgroup's entries)
+                    atomicOr(&st->status, kStatusInternal);
+                }
+                return;
+            }
+            const uint32_t pu = P[u], pv = P[v];
+            if (u == v || pu == pv || pu == v || pv == u) return;
+            (void)link<true, 0>(P, u, pu, v, pv, z);
+        };
         for (uint32_t w0 = 0; w0 < nch; w0 += kWin3) {
             const uint32_t nw = min((uint32_t)kWin3, nch - w0);
+            if (TILES) {
+                if (jw >= jhi) break;
+                const uint32_t wn = wcnt[row * nwin + w0 / kWin3];
+                if (jw + wn <= jlo) { jw += wn; continue; }
+            }
             __syncthreads();
             for (uint32_t t = threadIdx.x; t < nw; t += kHook3Block) {
                 const uint64_t g = (uint64_t)cb + w0 + t;
-                const uint32_t r0 = run2T[(uint64_t)b * nch2 + g];
-                const uint32_t r1 = run2T[(uint64_t)(b + 1) * nch2 + g];
+                const uint32_t r0 = run2T[row * nch2 + g];
+                const uint32_t r1 = run2T[(row + 1) * nch2 + g];
                 s_off[t] = r0;
                 s_pre[t] = r1 - r0;
             }
@@ -908,13 +1013,44 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
             for (uint32_t t = threadIdx.x; t < nw; t += kHook3Block)
                 s_off[t] = (w0 + t) * (uint32_t)kC2 + s_off[t] - s_pre[t];
             __syncthreads();
-            const uint32_t total = s_pre[nw];
+            const uint32_t total = TILES ? min(s_pre[nw], jhi - jw) : s_pre[nw];
+            const uint32_t first = TILES && jlo > jw ? jlo - jw : 0u;
+            if (TILES) jw += s_pre[nw];
+            if (s_pre[nw] < 8 * nw) {
+                // Short runs (a slice of few vertices): following them one by one
+                // would take a step per run, empty ones too; each lane searches its own.
+                // (R-MAT n = 2^23 + 4099, 15 M entries: filter 2340 us following, 246 searching)
+                for (uint32_t jb = first + (uint32_t)wave * 64; jb < total; jb += kHook3Block) {
+                    const uint32_t j = jb + (uint32_t)lane;
+                    const bool h = j < total;
+                    uint32_t at = 0;
+                    if (h) {
+                        uint32_t t0 = 0, t1 = nw;            // s_pre[t0] <= j < s_pre[t1]
+                        while (t1 - t0 > 1) {
+                            const uint32_t tm = (t0 + t1) / 2;
+                            if (s_pre[tm] <= j) t0 = tm;
+                            else t1 = tm;
+                        }
+                        at = j + s_off[t0];
+                    }
+                    const uint32_t w = srcw[at], h8 = srch[at];
+                    const u32x2 x = {w & kLoMask, (w >> kSliceBits) | (h8 << (32 - kSliceBits))};
+                    const uint32_t both =
+                        (sa[x.x >> 5] >> (x.x & 31)) & (lb[x.y >> 5] >> (x.y & 31)) & 1u;
+                    if (MODE == kMarkTiles) {
+                        if (h && !both) (void)settle(x);
+                    } else {
+                        queue_push(q, lane, h && !both, x, settle, hook);
+                    }
+                }
+                continue;
+            }
             // The window's entries form one index space [0, total); each wave
             // takes ranges of kRange consecutive indices. Register k holds index
             // j0 + 64k + lane; right after it is tested it is reloaded with index
             // jn + 64k + lane of the next range (index 0 past the end), so the
             // next range's loads are in flight meanwhile.
-            uint32_t j0 = (uint32_t)wave * kRange;
+            uint32_t j0 = first + (uint32_t)wave * kRange;
             if (j0 >= total) continue;
             uint32_t ew[kRunsInFlight], eh[kRunsInFlight];
             uint32_t t = __builtin_amdgcn_readfirstlane(t3_find_run(s_pre, nw, j0, lane));
@@ -944,21 +1080,10 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                     const uint32_t both =
                         (sa[x.x >> 5] >> (x.x & 31)) & (lb[x.y >> 5] >> (x.y & 31)) & 1u;
                     const bool pend = h && !both;
-                    const uint64_t ball = __ballot(pend);
-                    if (pend) pq[pn + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] = x;
-                    pn += (uint32_t)__popcll(ball);
-                    if (pn >= 64) {
-                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        t3_settle(pq, 64, lane, sa, lb, abase, bbase, zbits, ow, oh, cap, &s_used,
-                                  st);
-                        const u32x2 rest = (uint32_t)lane < pn - 64 ? pq[64 + lane] : u32x2{0u, 0u};
-                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
-                        if ((uint32_t)lane < pn - 64) pq[lane] = rest;
-                        pn -= 64;
-                        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                        __builtin_amdgcn_wave_barrier();
+                    if (MODE == kMarkTiles) {
+                        if (pend) (void)settle(x);
+                    } else {
+                        queue_push(q, lane, pend, x, settle, hook);
                     }
                 }
                 if (!more) break;
@@ -967,14 +1092,15 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         }
         // this slice's pending entries are settled before the next slice's
         // bitmap replaces it
-        if (pn) {
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            t3_settle(pq, pn, lane, sa, lb, abase, bbase, zbits, ow, oh, cap, &s_used, st);
+        if (MODE != kMarkTiles) queue_finish(q, lane, settle, hook);
+        if (b != a) {
+            __syncthreads();
+            t3_flush(sb, zbits, (uint64_t)b * kSliceWords, words);
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) wgcnt[wi] = min(s_used, cap);
+    t3_flush(sa, zbits, (uint64_t)a * kSliceWords, words);
+    if (MODE == kFullRuns && threadIdx.x == 0) wgcnt[wi] = min(s_used, cap);
 }
 
 // ---- 6. the survivor hook -------------------------------------------------------------------
@@ -986,7 +1112,8 @@ constexpr uint32_t kItem = 1024;     // entries per work item (4 per thread)
 
 // ipref[w] = sum over v < w of ceil(cnt[v] / kItem); ipref[nw] = total; one block.
 __global__ __launch_bounds__(kPackBlock) void k_t4_scan(const uint32_t* __restrict__ cnt,
-                                                        uint32_t nw, uint32_t* __restrict__ ipref) {
+                                                        uint32_t nw, uint32_t* __restrict__ ipref, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ uint32_t ws[kPackBlock / 64 + 1];
     __shared__ uint32_t s_carry;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1017,8 +1144,9 @@ __global__ __launch_bounds__(kPackBlock) void k_t4_scan(const uint32_t* __restri
 }
 
 // Algorithm 3's hooking loop (keys of Formula 1 as an order, path splitting)
-// over the kept entries, with no bitmap: a mark is a link to z that is not in
-// P, so a marked vertex cannot stand in for z here.
+// over the kept entries. Their bits are tested once more first: every
+// workgroup's marks are in the bitmap by now, and most entries were kept only
+// because their own workgroup had not seen them.
 constexpr int kHook4Block = 256;
 constexpr int kHook4EPT = (int)kItem / kHook4Block;
 constexpr int kHook4Grid = 2048;     // 8 workgroups per CU
@@ -1029,7 +1157,8 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
                                                          const uint32_t* __restrict__ cnt,
                                                          const uint32_t* __restrict__ ipref,
                                                          uint32_t nw, int nbg, uint32_t* P,
-                                                         DevState* st) {
+                                                         uint32_t* zbits, DevState* st, Gate gate) {
+    if (gated_off(gate)) return;
     __shared__ uint32_t s_w;
     const uint32_t z = ld_agent(&st->zroot);
     const uint32_t items = ld_agent(&ipref[nw]);
@@ -1060,11 +1189,26 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
             u[k] = abase | (x & kLoMask);
             v[k] = pk_v1(x, sh[at]);
         }
+        uint32_t bu[kHook4EPT], bv[kHook4EPT];
+#pragma unroll
+        for (int k = 0; k < kHook4EPT; ++k) {
+            bu[k] = ld_agent(&zbits[u[k] >> 5]);
+            bv[k] = ld_agent(&zbits[v[k] >> 5]);
+        }
+#pragma unroll
+        for (int k = 0; k < kHook4EPT; ++k) {
+            const bool mu = (bu[k] >> (u[k] & 31)) & 1u, mv = (bv[k] >> (v[k] & 31)) & 1u;
+            if (h[k] && mu != mv) {
+                if (mu) atomicOr(&zbits[v[k] >> 5], 1u << (v[k] & 31));
+                else atomicOr(&zbits[u[k] >> 5], 1u << (u[k] & 31));
+            }
+            h[k] = h[k] && !mu && !mv;
+        }
         uint32_t pu[kHook4EPT], pv[kHook4EPT];
 #pragma unroll
         for (int k = 0; k < kHook4EPT; ++k) {
-            pu[k] = P[u[k]];
-            pv[k] = P[v[k]];
+            pu[k] = h[k] ? P[u[k]] : 0u;
+            pv[k] = h[k] ? P[v[k]] : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kHook4EPT; ++k) {
@@ -1075,64 +1219,207 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
     }
 }
 
-// ---- host side --------------------------------------------------------------------
+// ---- few slices: one pass over (a, b) ------------------------------------------------------
+// With at most kMaxOnePass slices the (a, b) tiles are few enough (R * R <= 484)
+// that one LDS sort of an 8192-entry chunk leaves runs of 17 entries or more per
+// tile, so the second partition pass (11 B per entry read and written, and its
+// tables) is not needed: 8 B read, 5 written, 5 read per entry in all. The tiles
+// take the filter's form at once: chunk c's entries at [c * kC2, ...) sorted by
+// tile, run2T[d * nch + c] the start of tile d's run. The filter splits each
+// tile's chunks over `parts` workgroups.
+constexpr int kMaxOnePass = 22;
+constexpr int kMaxTiles = kMaxOnePass * kMaxOnePass;
 
-struct TiledPlan {
-    int R;
-    uint64_t nch1, nch2_max;
-};
-
-static TiledPlan tiled_plan(uint64_t n, uint64_t m) {
-    TiledPlan p;
-    p.R = (int)((n + (1ull << kSliceBits) - 1) >> kSliceBits);
-    p.nch1 = (m + kC1 - 1) / kC1;
-    p.nch2_max = m / kC2 + (uint64_t)p.R + 1;
-    return p;
+template <typename T>
+__global__ __launch_bounds__(kPartBlock) void k_tile_part(const T* __restrict__ edges, uint64_t m,
+                                                          uint32_t n, int R, uint64_t nch,
+                                                          L2Buf out, uint16_t* __restrict__ run2T,
+                                                          DevState* st, uint32_t sym, Gate gate) {
+    if (gated_off(gate)) return;
+    __shared__ u32x2 stage[kC2];
+    __shared__ uint32_t hist[kMaxTiles + 1];
+    __shared__ uint32_t start[kMaxTiles + 1];
+    const uint64_t c = blockIdx.x;
+    const int tiles = R * R;
+    for (int i = threadIdx.x; i <= tiles; i += kPartBlock) hist[i] = 0;
+    __syncthreads();
+    u32x2 e[kPartEPT];
+    uint16_t rank[kPartEPT];
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < kPartEPT; ++k) {
+        const uint64_t i = c * kC2 + (uint64_t)k * kPartBlock + threadIdx.x;
+        e[k] = load_entry(edges, i < m ? i : m - 1);
+    }
+    auto tile = [&](u32x2 x) { return (x.x >> kSliceBits) * (uint32_t)R + (x.y >> kSliceBits); };
+#pragma unroll
+    for (int k = 0; k < kPartEPT; ++k) {
+        const uint64_t i = c * kC2 + (uint64_t)k * kPartBlock + threadIdx.x;
+        bool live = i < m;
+        if (live && (e[k].x >= n || e[k].y >= n)) { bad = true; live = false; }
+        live = live && (sym ? e[k].x < e[k].y : e[k].x != e[k].y);
+        rank[k] = 0xFFFF;
+        if (live) rank[k] = (uint16_t)atomicAdd(&hist[tile(e[k])], 1u);
+    }
+    if (bad) atomicOr(&st->status, kStatusRange);
+    __syncthreads();
+    wave_scan<8>(hist, start, tiles);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPartEPT; ++k)
+        if (rank[k] != 0xFFFF) stage[start[tile(e[k])] + rank[k]] = e[k];
+    __syncthreads();
+    const uint32_t kept = start[tiles];
+    for (uint32_t i = threadIdx.x; i < kept; i += kPartBlock) {
+        const u32x2 x = stage[i];
+        const uint32_t vlo = x.y & kLoMask;
+        out.w[c * kC2 + i] = (x.x & kLoMask) | (vlo << kSliceBits);
+        out.h[c * kC2 + i] = (uint8_t)(vlo >> (32 - kSliceBits));
+    }
+    for (int d = threadIdx.x; d <= tiles; d += kPartBlock)
+        run2T[(uint64_t)d * nch + c] = (uint16_t)start[d];
 }
 
-// The regrouping pays from 4 slices on the plain path (ER n = 2^21, 16 entries
-// per vertex: 1.04 ms regrouped against 1.79 ms direct) and from 8 with a zero
-// root, whose filter drops little until the root's component is large (R-MAT
-// n = 2^21: 2.3 ms regrouped against 1.5 ms direct; n = 2^22: 1.8 against 2.2).
+// wcnt[d * nwin + w]: entries of tile d in the w-th window of kWin3 chunks. One
+// block per (d, w).
+__global__ __launch_bounds__(256) void k_tile_count(const uint16_t* __restrict__ run2T, uint64_t nch,
+                                                    uint32_t nwin, uint32_t* __restrict__ wcnt,
+                                                    Gate gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t ws[4];
+    const uint64_t d = blockIdx.x / nwin, w = blockIdx.x % nwin;
+    const uint64_t c1 = min((w + 1) * kWin3, nch);
+    uint32_t t = 0;
+    for (uint64_t c = w * kWin3 + threadIdx.x; c < c1; c += 256)
+        t += (uint32_t)run2T[(d + 1) * nch + c] - (uint32_t)run2T[d * nch + c];
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) wcnt[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
+}
+
+// ---- host side --------------------------------------------------------------------
+
+static int slices(uint64_t n) { return (int)((n + (1ull << kSliceBits) - 1) >> kSliceBits); }
+
+// The plain hook of a step call takes the first-endpoint buckets from 4 slices
+// (ER n = 2^21, 16 entries per vertex: 1.04 ms regrouped against 1.79 ms direct).
 bool tiled_eligible(uint64_t n, uint64_t m, bool zr) {
     const uint64_t R = (n + (1ull << kSliceBits) - 1) >> kSliceBits;
     return R >= (zr ? 8u : 4u) && R <= (uint64_t)kMaxSlices && m >= (1ull << 24) &&
            m < (1ull << 32);
 }
 
-static int grow(Slot* s, void** p, uint64_t* cap, uint64_t bytes, hipStream_t stream) {
-    if (*cap >= bytes) return CC_OK;
+// The filter over tiles: 0 = not taken, 1 = one partition pass, 2 = two. Below one
+// entry per vertex most vertices are outside any giant component, and the direct
+// hook is faster (zero root, grid n = 33 M, 30 M entries: 2.2 ms against 3.0;
+// ER n = 30 M, 18 M entries: 2.6 against 2.5). Two passes start at the size their
+// fixed costs (16 launches) are worth; one pass was faster from 2^20 entries on
+// (R-MAT n = 3 M, 12 M entries: 918 us direct, 314 here).
+int filter_passes(uint64_t n, uint64_t m) {
+    const uint64_t R = (n + (1ull << kSliceBits) - 1) >> kSliceBits;
+    if (n <= lds_bits_max_n() || R > (uint64_t)kMaxSlices || m >= (1ull << 32)) return 0;
+    if (m < n) return 0;
+    // (below 2^31: a tile's width in the filter's index space exceeds its entries)
+    if (R <= (uint64_t)kMaxOnePass && m < (1ull << 31)) return m >= (1ull << 20) ? 1 : 0;
+    return m >= (1ull << 24) ? 2 : 0;
+}
+
+// Where everything lies in the regrouped hooks' scratch block (byte offsets).
+struct TiledLayout {
+    int R;
+    uint64_t nch1, nch2;
+    uint64_t t1w, t1h, seg, cnt1, tsum, pre1, base2, cbase, desc;   // level 1 (two passes, buckets)
+    uint64_t w, h, run2, wcnt;                                      // the filter's tiles
+    uint64_t wgoff, wgcnt, ipref;                                   // the survivors' regions
+    uint64_t bits, p32;                                             // plain whole solves
+    uint64_t total;
+};
+
+// passes: 0 = no tiles; 1, 2 = the filter's; 3 = the plain bucketed hook.
+static TiledLayout tiled_layout(uint64_t n, uint64_t m, int passes, bool bits, bool p32) {
+    TiledLayout l{};
+    l.R = slices(n);
+    const uint64_t R = (uint64_t)l.R;
+    l.nch1 = (m + kC1 - 1) / kC1;
+    l.nch2 = passes == 1 ? l.nch1 : m / kC2 + R + 1;
+    const uint64_t cap = l.nch1 * kC1;
+    const uint64_t ntile = (l.nch1 + kScanTile - 1) / kScanTile;
+    uint64_t at = 0;
+    auto take = [&](uint64_t bytes) {
+        const uint64_t o = at;
+        at += (bytes + 255) & ~255ull;
+        return o;
+    };
+    if (passes >= 2) {
+        l.t1w = take(4 * cap);
+        l.t1h = take(2 * cap);
+        l.seg = take(2 * l.nch1 * R);
+        l.cnt1 = take(4 * l.nch1 * R);
+        l.tsum = take(4 * ntile * R);
+        l.pre1 = take(4 * (l.nch1 + 1) * R);
+        l.base2 = take(8 * (R + 1));
+        l.cbase = take(4 * (R + 1));
+        l.desc = take(32 * l.nch2);
+    }
+    if (passes == 1 || passes == 2) {
+        l.w = take(4 * cap);
+        l.h = take(cap);
+        l.run2 = take(2 * l.nch2 * ((passes == 1 ? R * R : R) + 1));
+    }
+    if (passes == 1) l.wcnt = take(4 * R * R * ((l.nch1 + kWin3 - 1) / kWin3));
+    if (passes == 2) {
+        const uint64_t nwg = R * ((R + kBPerBlock - 1) / kBPerBlock);
+        l.wgoff = take(8 * (nwg + 1));
+        l.wgcnt = take(4 * nwg);
+        l.ipref = take(4 * (nwg + 1));
+    }
+    if (bits) l.bits = take(4 * ((n + 31) / 32));
+    if (p32) l.p32 = take(4 * n);
+    l.total = at;
+    return l;
+}
+
+uint64_t filter_scratch_bytes(uint64_t n, uint64_t m, int passes, bool bits, bool p32) {
+    return tiled_layout(n, m, passes, bits, p32).total;
+}
+uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m) {
+    return tiled_layout(n, m, 3, false, false).total;
+}
+
+static int grow(Slot* s, uint64_t bytes, hipStream_t stream) {
+    if (s->tiled.cap >= bytes) return CC_OK;
     if (s->no_grow) return fail(CC_ENOMEM, "regrouped-hook scratch exceeds the fixed scratch");
     CCM_HIP(hipStreamSynchronize(stream));
-    if (*p) CCM_HIP(hipFree(*p));
-    *p = nullptr;
-    *cap = 0;
-    if (hipMalloc(p, bytes) != hipSuccess) {
+    if (s->tiled.buf) CCM_HIP(hipFree(s->tiled.buf));
+    s->tiled.buf = nullptr;
+    s->tiled.cap = 0;
+    if (hipMalloc(&s->tiled.buf, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        *p = nullptr;
+        s->tiled.buf = nullptr;
         return fail(CC_ENOMEM, "tiled hook scratch allocation failed");
     }
-    *cap = bytes;
+    s->tiled.cap = bytes;
     return CC_OK;
 }
 
-// Bytes of the regrouped hook's buffers for a COO list of m entries (with the
-// zero root's warm-up taken off the front, as run_hook_tiled does); the same
-// arithmetic as the layout below.
-uint64_t tiled_scratch_bytes(uint64_t n, uint64_t m, bool plain) {
-    const uint64_t m0 = plain ? 0 : m >> 10;
-    const TiledPlan pl = tiled_plan(n, m - m0);
-    const uint64_t R = (uint64_t)pl.R;
-    auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
-    const uint64_t cap = pl.nch1 * kC1;
-    const uint64_t ntile = (pl.nch1 + kScanTile - 1) / kScanTile;
-    const uint64_t nbg = (R + kBPerBlock - 1) / kBPerBlock;
-    const uint64_t nwg = R * nbg;
-    return al(4 * cap) + al(2 * cap) + al(4 * cap) + al(cap) + al(2 * pl.nch1 * R) +
-           al(4 * pl.nch1 * R) +
-           al(4 * (pl.nch1 + 1) * R) + al(8 * (R + 1)) + al(4 * (R + 1)) +
-           al(2 * pl.nch2_max * (R + 1)) + al(32 * pl.nch2_max) + al(4 * ntile * R) +
-           al(8 * (nwg + 1)) + al(4 * nwg) + al(4 * (nwg + 1));
+int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool p32,
+                   hipStream_t stream, FilterScratch* out) {
+    const TiledLayout l = tiled_layout(n, m, passes, bits, p32);
+    if (s->tiled.cap < l.total && !s->no_grow) {
+        // growing waits for the stream, which a capture does not allow
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return fail(CC_ENOMEM, "regrouped-hook scratch cannot grow under capture");
+        }
+    }
+    int rc = grow(s, l.total, stream);
+    if (rc) return rc;
+    out->buf = s->tiled.buf;
+    out->bits = bits ? reinterpret_cast<uint32_t*>(s->tiled.buf + l.bits) : nullptr;
+    out->p32 = p32 ? reinterpret_cast<uint32_t*>(s->tiled.buf + l.p32) : nullptr;
+    return CC_OK;
 }
 
 void tiled_free(TiledScratch* t) {
@@ -1140,122 +1427,148 @@ void tiled_free(TiledScratch* t) {
     *t = TiledScratch{};
 }
 
-int run_hook_tiled(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P,
-                   hipStream_t stream, bool plain, bool sym) {
-    // Warm-up (zero root): the first 1/1024 of the entries go through the direct
-    // hook, so the membership bitmap already holds the core of the zero root's
-    // tree when the first tiles load their slices. (Measured on R-MAT-26: from
-    // 1/64 to 1/4096 the step time barely moves; a longer warm-up trades its own
-    // random accesses for marks the filter would otherwise set.)
-    const uint64_t m0 = plain ? 0 : m >> 10;
-    if (m0) {
-        int rc0 = run_hook(s, n, m0, edges, P,
-                           CC_F_ZROOT | CC_F_NO_TILE | kHookLinkZ | (sym ? CC_F_SYMMETRIC : 0u),
-                           stream);
-        if (rc0) return rc0;
-        edges += 2 * m0;
-        m -= m0;
-    }
-    const TiledPlan pl = tiled_plan(n, m);
-    const int R = pl.R;
-    auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
-    const uint64_t cap = pl.nch1 * kC1;                  // entries of each buffer
-    const uint64_t b_t1w = al(4 * cap), b_t1h = al(2 * cap), b_tmp2 = al(4 * cap) + al(cap);
-    const uint64_t b_seg1 = al(2 * pl.nch1 * R);
-    const uint32_t ntile = (uint32_t)((pl.nch1 + kScanTile - 1) / kScanTile);
-    const uint64_t b_tsum = al(4 * (uint64_t)ntile * R);
-    const uint64_t b_cnt1 = al(4 * pl.nch1 * R);
-    const uint64_t b_pre1 = al(4 * (pl.nch1 + 1) * R);
-    const uint64_t b_base2 = al(8 * (R + 1));
-    const uint64_t b_cbase = al(4 * (R + 1));
-    const uint64_t b_run2 = al(2 * pl.nch2_max * (R + 1));
-    const uint64_t b_desc = al(32 * pl.nch2_max);
-    const uint32_t nbg = (uint32_t)((R + kBPerBlock - 1) / kBPerBlock);
-    const uint32_t nwg = (uint32_t)R * nbg;
-    const uint64_t b_wgoff = al(8 * ((uint64_t)nwg + 1)), b_wgcnt = al(4 * (uint64_t)nwg);
-    const uint64_t b_ipref = al(4 * ((uint64_t)nwg + 1));
-    const uint64_t total = b_t1w + b_t1h + b_tmp2 + b_seg1 + b_cnt1 + b_pre1 + b_base2 +
-                           b_cbase + b_run2 + b_desc + b_tsum + b_wgoff + b_wgcnt + b_ipref;
-    if (total != tiled_scratch_bytes(n, m0 + m, plain))
-        return fail(CC_EDEVICE, "regrouped-hook scratch size mismatch (a bug)");
-    int rc = grow(s, reinterpret_cast<void**>(&s->tiled.buf), &s->tiled.cap, total, stream);
+// Steps 1-3 and the level-2 chunk descriptors on a COO list.
+static int level1(const TiledLayout& l, char* q, uint64_t n, uint64_t m, EdgeList E, DevState* st,
+                  bool sym, Gate gate, hipStream_t stream) {
+    auto* t1w = reinterpret_cast<uint32_t*>(q + l.t1w);
+    auto* t1h = reinterpret_cast<uint16_t*>(q + l.t1h);
+    auto* seg = reinterpret_cast<uint16_t*>(q + l.seg);
+    auto* cnt1 = reinterpret_cast<uint32_t*>(q + l.cnt1);
+    auto* tsum = reinterpret_cast<uint32_t*>(q + l.tsum);
+    auto* pre1 = reinterpret_cast<uint32_t*>(q + l.pre1);
+    auto* base2 = reinterpret_cast<uint64_t*>(q + l.base2);
+    auto* cbase = reinterpret_cast<uint32_t*>(q + l.cbase);
+    auto* desc = reinterpret_cast<uint32_t*>(q + l.desc);
+    const uint32_t ntile = (uint32_t)((l.nch1 + kScanTile - 1) / kScanTile);
+    const uint32_t R = (uint32_t)l.R;
+    const uint32_t g1 = (uint32_t)l.nch1;
+    int rc;
+    // every kernel below reads tables the previous one wrote: coherence points between
+    if ((rc = cohere(stream))) return rc;
+    if (E.wide)
+        k_t1_part<<<g1, kPartBlock, 0, stream>>>((const uint64_t*)E.p, m, (uint32_t)n, l.R, l.nch1,
+                                                 t1w, t1h, seg, cnt1, st, sym ? 1u : 0u, gate);
+    else
+        k_t1_part<<<g1, kPartBlock, 0, stream>>>((const uint32_t*)E.p, m, (uint32_t)n, l.R, l.nch1,
+                                                 t1w, t1h, seg, cnt1, st, sym ? 1u : 0u, gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t1_tsum<<<R * ntile, kScanBlock, 0, stream>>>(cnt1, l.nch1, ntile, tsum, gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t1_scan<<<R * ntile, kScanBlock, 0, stream>>>(cnt1, l.nch1, ntile, tsum, pre1, gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t1_bases<<<1, 256, 0, stream>>>(pre1, l.nch1, l.R, base2, cbase, gate);
+    if ((rc = cohere(stream))) return rc;
+    const uint64_t pairs = (uint64_t)R * l.nch1;
+    k_t2_bounds<<<(uint32_t)((pairs + 255) / 256), 256, 0, stream>>>(pre1, l.nch1, l.R, cbase, base2,
+                                                                    desc, gate);
+    return cohere(stream);
+}
+
+int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, bool sym,
+                     hipStream_t stream) {
+    const TiledLayout l = tiled_layout(n, m, 3, false, false);
+    int rc = grow(s, l.total, stream);
     if (rc) return rc;
     char* q = s->tiled.buf;
-    uint32_t* t1w = reinterpret_cast<uint32_t*>(q); q += b_t1w;
-    uint16_t* t1h = reinterpret_cast<uint16_t*>(q); q += b_t1h;
-    const L2Buf tmp2{reinterpret_cast<uint32_t*>(q), reinterpret_cast<uint8_t*>(q + al(4 * cap))};
-    q += b_tmp2;
-    uint16_t* segT = reinterpret_cast<uint16_t*>(q); q += b_seg1;
-    uint32_t* cnt1 = reinterpret_cast<uint32_t*>(q); q += b_cnt1;
-    uint32_t* pre1 = reinterpret_cast<uint32_t*>(q); q += b_pre1;
-    uint64_t* base2 = reinterpret_cast<uint64_t*>(q); q += b_base2;
-    uint32_t* cbase = reinterpret_cast<uint32_t*>(q); q += b_cbase;
-    uint16_t* run2 = reinterpret_cast<uint16_t*>(q); q += b_run2;
-    uint32_t* desc = reinterpret_cast<uint32_t*>(q); q += b_desc;
-    uint32_t* tsum = reinterpret_cast<uint32_t*>(q); q += b_tsum;
-    uint64_t* wgoff = reinterpret_cast<uint64_t*>(q); q += b_wgoff;
-    uint32_t* wgcnt = reinterpret_cast<uint32_t*>(q); q += b_wgcnt;
-    uint32_t* ipref = reinterpret_cast<uint32_t*>(q);
-    // the survivor regions live in the level-1 buffers, free once the level-2
-    // partition has read them (positions [base2[a], base2[a+1]) for slice a)
-    // every kernel below reads tables the previous one wrote: coherence points between
-    int rc1;
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t1_part<<<(uint32_t)pl.nch1, kPartBlock, 0, stream>>>(edges, m, (uint32_t)n, R, pl.nch1, t1w,
-                                                           t1h, segT, cnt1, s->st, sym ? 1u : 0u);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t1_tsum<<<(uint32_t)R * ntile, kScanBlock, 0, stream>>>(cnt1, pl.nch1, ntile, tsum);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t1_scan<<<(uint32_t)R * ntile, kScanBlock, 0, stream>>>(cnt1, pl.nch1, ntile, tsum, pre1);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t1_bases<<<1, 256, 0, stream>>>(pre1, pl.nch1, R, base2, cbase);
-    if ((rc1 = cohere(stream))) return rc1;
-    const uint64_t pairs = (uint64_t)R * pl.nch1;
-    k_t2_bounds<<<(uint32_t)((pairs + 255) / 256), 256, 0, stream>>>(pre1, pl.nch1, R, cbase, base2,
-                                                                    desc);
-    if ((rc1 = cohere(stream))) return rc1;
-    if (plain) {
-        // the plain path hooks the level-2 chunks as they are gathered
-        k_t2_hookplain<<<(uint32_t)pl.nch2_max, kPartBlock, 0, stream>>>(t1w, t1h, segT, pre1,
-                                                                        pl.nch1, R, cbase, desc, P);
-        CCM_HIP(hipGetLastError());
-        return CC_OK;
-    }
-    k_t2_part<<<(uint32_t)pl.nch2_max, kPartBlock, 0, stream>>>(t1w, t1h, segT, pre1, pl.nch1, R,
-                                                               cbase, desc, tmp2, run2, pl.nch2_max);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t3_regions<<<nwg, 256, 0, stream>>>(run2, pl.nch2_max, R, cbase, wgcnt);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t3_offsets<<<(uint32_t)((R + 255) / 256), 256, 0, stream>>>(wgcnt, R, base2, wgoff);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t3_filter<<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, pl.nch2_max, R, base2, cbase,
-                                                s->zbits, (n + 31) / 32, t1w, t1h, wgoff, wgcnt,
-                                                s->st);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t4_scan<<<1, kPackBlock, 0, stream>>>(wgcnt, nwg, ipref);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t4_hook<<<kHook4Grid, kHook4Block, 0, stream>>>(t1w, t1h, wgoff, wgcnt, ipref, nwg, (int)nbg,
-                                                      P, s->st);
+    if ((rc = level1(l, q, n, m, EdgeList{edges, false}, s->st, sym, Gate{}, stream))) return rc;
+    // the plain path hooks the level-2 chunks as they are gathered
+    k_t2_hookplain<<<(uint32_t)l.nch2, kPartBlock, 0, stream>>>(
+        reinterpret_cast<uint32_t*>(q + l.t1w), reinterpret_cast<uint16_t*>(q + l.t1h),
+        reinterpret_cast<uint16_t*>(q + l.seg), reinterpret_cast<uint32_t*>(q + l.pre1), l.nch1, l.R,
+        reinterpret_cast<uint32_t*>(q + l.cbase), reinterpret_cast<uint32_t*>(q + l.desc), P);
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
 
-// The regrouped zero-root hook on CSR input (steps 4-6 on adj's own buckets).
-int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
-                       uint32_t* P, hipStream_t stream, bool sym) {
-    const int R = (int)((n + (1ull << kSliceBits) - 1) >> kSliceBits);
-    const uint64_t nch2 = m / kC2 + (uint64_t)R + 1;
-    auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
-    const uint64_t b_sw = al(4 * m), b_sh = al(2 * m), b_tmp2 = al(4 * m) + al(m);
-    const uint64_t b_base2 = al(8 * (R + 1)), b_cbase = al(4 * (R + 1));
-    const uint64_t b_cfirst = al(4 * nch2), b_run2 = al(2 * nch2 * (R + 1));
+// Steps 5-6 on the level-2 buffers: survivors to (sw, sh), then hooked.
+static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_t* base2,
+                       uint32_t* cbase, uint32_t* sw, uint16_t* sh, uint64_t* wgoff,
+                       uint32_t* wgcnt, uint32_t* ipref, uint32_t* P, uint32_t* zbits,
+                       uint64_t words, DevState* st, Gate gate, hipStream_t stream) {
     const uint32_t nbg = (uint32_t)((R + kBPerBlock - 1) / kBPerBlock);
     const uint32_t nwg = (uint32_t)R * nbg;
-    const uint64_t b_wgoff = al(8 * ((uint64_t)nwg + 1)), b_wgcnt = al(4 * (uint64_t)nwg);
-    const uint64_t b_ipref = al(4 * ((uint64_t)nwg + 1));
-    const uint64_t total = b_sw + b_sh + b_tmp2 + b_base2 + b_cbase + b_cfirst + b_run2 + b_wgoff +
-                           b_wgcnt + b_ipref;
-    int rc = grow(s, reinterpret_cast<void**>(&s->tiled.buf), &s->tiled.cap, total, stream);
+    int rc;
+    k_t3_regions<<<nwg, 256, 0, stream>>>(run2, nch2, R, cbase, wgcnt, gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t3_offsets<<<(uint32_t)((R + 255) / 256), 256, 0, stream>>>(wgcnt, R, base2, wgoff, gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t3_filter<kFullRuns><<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, nch2, R, nullptr, base2, cbase,
+                                                            zbits, words, P, sw, sh, wgoff, wgcnt, st,
+                                                            gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t4_scan<<<1, kPackBlock, 0, stream>>>(wgcnt, nwg, ipref, gate);
+    if ((rc = cohere(stream))) return rc;
+    k_t4_hook<<<kHook4Grid, kHook4Block, 0, stream>>>(sw, sh, wgoff, wgcnt, ipref, nwg, (int)nbg, P,
+                                                      zbits, st, gate);
+    CCM_HIP(hipGetLastError());
+    return CC_OK;
+}
+
+int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, int passes,
+               bool bits, bool p32, bool sym, Gate gate, hipStream_t stream) {
+    const TiledLayout l = tiled_layout(n, m, passes, bits, p32);
+    if (s->tiled.cap < l.total) return fail(CC_EDEVICE, "regrouped-hook scratch too small (a bug)");
+    char* q = s->tiled.buf;
+    const L2Buf tmp2{reinterpret_cast<uint32_t*>(q + l.w), reinterpret_cast<uint8_t*>(q + l.h)};
+    auto* run2 = reinterpret_cast<uint16_t*>(q + l.run2);
+    const uint64_t words = (n + 31) / 32;
+    int rc;
+    if (passes == 1) {
+        const uint32_t g = (uint32_t)l.nch1;
+        if (E.wide)
+            k_tile_part<<<g, kPartBlock, 0, stream>>>((const uint64_t*)E.p, m, (uint32_t)n, l.R,
+                                                      l.nch1, tmp2, run2, s->st, sym ? 1u : 0u, gate);
+        else
+            k_tile_part<<<g, kPartBlock, 0, stream>>>((const uint32_t*)E.p, m, (uint32_t)n, l.R,
+                                                      l.nch1, tmp2, run2, s->st, sym ? 1u : 0u, gate);
+        if ((rc = cohere(stream))) return rc;
+        const uint32_t nwin = (uint32_t)((l.nch1 + kWin3 - 1) / kWin3);
+        auto* wcnt = reinterpret_cast<uint32_t*>(q + l.wcnt);
+        k_tile_count<<<(uint32_t)(l.R * l.R) * nwin, 256, 0, stream>>>(run2, l.nch1, nwin, wcnt, gate);
+        if ((rc = cohere(stream))) return rc;
+        // one workgroup per CU is resident; no more than its copies are worth
+        const uint32_t wgs = (uint32_t)std::max<uint64_t>(
+            1, std::min<uint64_t>(m >> 13, (uint64_t)device_cu_count(s->device)));
+        k_t3_filter<kMarkTiles><<<wgs, kHook3Block, 0, stream>>>(
+            tmp2, run2, l.nch1, l.R, wcnt, nullptr, nullptr, zbits, words, P, nullptr, nullptr, nullptr,
+            nullptr, s->st, gate);
+        if ((rc = cohere(stream))) return rc;
+        k_t3_filter<kFullTiles><<<wgs, kHook3Block, 0, stream>>>(
+            tmp2, run2, l.nch1, l.R, wcnt, nullptr, nullptr, zbits, words, P, nullptr, nullptr, nullptr,
+            nullptr, s->st, gate);
+        CCM_HIP(hipGetLastError());
+        return CC_OK;
+    }
+    if ((rc = level1(l, q, n, m, E, s->st, sym, gate, stream))) return rc;
+    auto* cbase = reinterpret_cast<uint32_t*>(q + l.cbase);
+    auto* base2 = reinterpret_cast<uint64_t*>(q + l.base2);
+    k_t2_part<<<(uint32_t)l.nch2, kPartBlock, 0, stream>>>(
+        reinterpret_cast<uint32_t*>(q + l.t1w), reinterpret_cast<uint16_t*>(q + l.t1h),
+        reinterpret_cast<uint16_t*>(q + l.seg), reinterpret_cast<uint32_t*>(q + l.pre1), l.nch1, l.R,
+        cbase, reinterpret_cast<uint32_t*>(q + l.desc), tmp2, run2, l.nch2, gate);
+    if ((rc = cohere(stream))) return rc;
+    // the survivor regions live in the level-1 buffers, free once the level-2
+    // partition has read them (positions [base2[a], base2[a+1]) for slice a)
+    return filter_runs(l.R, l.nch2, tmp2, run2, base2, cbase, reinterpret_cast<uint32_t*>(q + l.t1w),
+                       reinterpret_cast<uint16_t*>(q + l.t1h), reinterpret_cast<uint64_t*>(q + l.wgoff),
+                       reinterpret_cast<uint32_t*>(q + l.wgcnt), reinterpret_cast<uint32_t*>(q + l.ipref),
+                       P, zbits, words, s->st, gate, stream);
+}
+
+// The regrouped zero-root hook on CSR input (steps 4-5 on adj's own buckets).
+int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
+                       uint32_t* P, hipStream_t stream, bool sym) {
+    const int R = slices(n);
+    const uint64_t nch2 = m / kC2 + (uint64_t)R + 1;
+    auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
+    const uint64_t b_tmp2 = al(4 * m) + al(m);
+    const uint64_t b_base2 = al(8 * (R + 1)), b_cbase = al(4 * (R + 1));
+    const uint64_t b_cfirst = al(4 * nch2), b_run2 = al(2 * nch2 * (R + 1));
+    const uint64_t b_sw = al(4 * m), b_sh = al(2 * m);
+    const uint64_t nwg = (uint64_t)R * ((R + kBPerBlock - 1) / kBPerBlock);
+    const uint64_t b_wgoff = al(8 * (nwg + 1)), b_wgcnt = al(4 * nwg), b_ipref = al(4 * (nwg + 1));
+    int rc = grow(s, b_sw + b_sh + b_tmp2 + b_base2 + b_cbase + b_cfirst + b_run2 + b_wgoff + b_wgcnt +
+                         b_ipref, stream);
     if (rc) return rc;
     char* q = s->tiled.buf;
     uint32_t* sw = reinterpret_cast<uint32_t*>(q); q += b_sw;
@@ -1269,29 +1582,17 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
     uint64_t* wgoff = reinterpret_cast<uint64_t*>(q); q += b_wgoff;
     uint32_t* wgcnt = reinterpret_cast<uint32_t*>(q); q += b_wgcnt;
     uint32_t* ipref = reinterpret_cast<uint32_t*>(q);
-    int rc1;
-    if ((rc1 = cohere(stream))) return rc1;
+    if ((rc = cohere(stream))) return rc;
     k_c_bases<<<1, 256, 0, stream>>>(off, n, m, R, base2, cbase);
-    if ((rc1 = cohere(stream))) return rc1;
+    if ((rc = cohere(stream))) return rc;
     const uint64_t gv = std::min<uint64_t>((n + 255) / 256, 8192);
     k_c_first<<<(uint32_t)gv, 256, 0, stream>>>(off, n, base2, cbase, cfirst);
-    if ((rc1 = cohere(stream))) return rc1;
+    if ((rc = cohere(stream))) return rc;
     k_t2_csr<<<(uint32_t)nch2, kPartBlock, 0, stream>>>(off, adj, n, R, base2, cbase, cfirst, tmp2,
                                                        run2, nch2, s->st, sym ? 1u : 0u);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t3_regions<<<nwg, 256, 0, stream>>>(run2, nch2, R, cbase, wgcnt);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t3_offsets<<<(uint32_t)((R + 255) / 256), 256, 0, stream>>>(wgcnt, R, base2, wgoff);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t3_filter<<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, nch2, R, base2, cbase, s->zbits,
-                                                (n + 31) / 32, sw, sh, wgoff, wgcnt, s->st);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t4_scan<<<1, kPackBlock, 0, stream>>>(wgcnt, nwg, ipref);
-    if ((rc1 = cohere(stream))) return rc1;
-    k_t4_hook<<<kHook4Grid, kHook4Block, 0, stream>>>(sw, sh, wgoff, wgcnt, ipref, nwg, (int)nbg,
-                                                      P, s->st);
-    CCM_HIP(hipGetLastError());
-    return CC_OK;
+    if ((rc = cohere(stream))) return rc;
+    return filter_runs(R, nch2, tmp2, run2, base2, cbase, sw, sh, wgoff, wgcnt, ipref, P, s->zbits,
+                       (n + 31) / 32, s->st, Gate{}, stream);
 }
 
 }  // namespace ccm

@@ -92,3 +92,77 @@ def test_whole_bitmap_symmetric_range_and_zroot(ctx):
             L = torch.empty(n, dtype=torch.int32, device="cuda")
             ctx.solve_async(to_dev(b), n, L, flags=fl)
             assert ctx.sync() == cc.CC_ERANGE
+
+
+SLICE = 1 << 19
+
+
+@pytest.mark.parametrize("kind", ["er", "rmat", "paths", "rows"])
+@pytest.mark.parametrize("n,m", [(LDS_MAX_N + 33, 1 << 20), (LDS_MAX_N + 33, (1 << 20) - 1),
+                                 (3 * SLICE, 6_000_001), (3 * SLICE + 1, 3 * SLICE + 1),
+                                 (3 * SLICE + 1, 3 * SLICE), (8 * SLICE + 40, 12_000_000),
+                                 (22 * SLICE, 12_000_003), (22 * SLICE + 5, (1 << 24) + 77),
+                                 (22 * SLICE + 5, (1 << 24) - 1)])
+def test_tiles(ctx, kind, n, m):
+    """One partition pass up to 22 slices of 2^19 vertices, two beyond; a last slice
+    of few vertices; graphs with and without a giant component."""
+    e = graph(kind, n, m, n + m)
+    want = oracle.cc_labels(n, e)
+    ed = to_dev(e)
+    log(f"{kind} n={n} m={m}")
+    for name, fl in [("plain", 0), ("zroot", cc.F_ZROOT)]:
+        assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"{kind} n={n} m={m} [{name}]")
+    assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"{kind} n={n} m={m} [steps]")
+
+
+def test_tiles_symmetric_range_and_few_tiles(ctx):
+    n, m = 5 * SLICE + 11, 8_000_000
+    e = graphgen.er(n, m // 2, 3)
+    sym = np.concatenate([e, e[:, ::-1]])
+    want = oracle.cc_labels(n, e)
+    for fl in (cc.F_SYMMETRIC, cc.F_SYMMETRIC | cc.F_ZROOT):
+        assert_same_labels(to_host_u32(ctx.solve(to_dev(sym), n, flags=fl)), want, f"symmetric {fl}")
+    # every first endpoint in the last slice (11 vertices) or in one slice: few tiles hold entries
+    for lo, hi in ((5 * SLICE, n), (2 * SLICE, 3 * SLICE)):
+        f = e.copy()
+        f[:, 0] = lo + f[:, 0] % (hi - lo)
+        want = oracle.cc_labels(n, f)
+        for fl in (0, cc.F_ZROOT):
+            assert_same_labels(to_host_u32(ctx.solve(to_dev(f), n, flags=fl)), want, f"first in {lo} {fl}")
+    for bad in ([n, 0], [0, 0xFFFFFFFF]):
+        b = np.concatenate([e, np.array([bad], np.uint32)])
+        for fl in (0, cc.F_ZROOT):
+            L = torch.empty(n, dtype=torch.int32, device="cuda")
+            ctx.solve_async(to_dev(b), n, L, flags=fl)
+            assert ctx.sync() == cc.CC_ERANGE
+
+
+def test_scratch_that_cannot_grow(ctx):
+    """Under capture the filter's scratch cannot grow, nor can a server's block past
+    its budget: those solves take the direct hook."""
+    n, m = 3 * SLICE, 2 * SLICE * 3
+    e = graphgen.er(n, m, 12)
+    want = oracle.cc_labels(n, e)
+    c = cc.Context(zroot_samples=4096)
+    ed, L = to_dev(e), torch.empty(n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        c.solve_async(ed, n, L)
+    for _ in range(3):
+        L.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert_same_labels(to_host_u32(L), want, "captured")
+    del g
+    c.close()
+    # room for the entries and the labels, not for the filter's tiles
+    need = 8 * m + 4 * n
+    s = cc.Server(ctx, streams=1, hbm_budget=(need + (4 << 20)) * 4 // 3)
+    try:
+        out = np.empty(n, np.uint32)
+        t = s.submit(e, n, out)
+        assert s.wait(t)[0] == cc.CC_OK
+        assert_same_labels(out, want, "served")
+    finally:
+        s.close()
