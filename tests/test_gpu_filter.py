@@ -166,3 +166,31 @@ def test_scratch_that_cannot_grow(ctx):
         assert_same_labels(out, want, "served")
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("kind,n,m", [("rmat", 65537, 1 << 18), ("er", 65537, (1 << 18) - 1),
+                                      ("er", LDS_MAX_N, 3_000_000), ("paths", 3 * SLICE + 1, 3_000_000),
+                                      ("rmat", 8 * SLICE + 40, 12_000_000),
+                                      ("er", 22 * SLICE + 5, (1 << 24) + 77)])
+def test_wide_ids(ctx, kind, n, m):
+    """64-bit IDs through the filters: labels, IDs beyond 32 bits reported, and the
+    zero root of a solve by steps untouched by one in between."""
+    e = graph(kind, n, m, n + m)
+    want = oracle.cc_labels(n, e)
+    w = torch.from_numpy(e.astype(np.int64)).cuda()
+    log(f"wide {kind} n={n} m={m}")
+    assert_same_labels(ctx.solve_u64(w, n).cpu().numpy().astype(np.uint32), want, f"wide {kind} n={n}")
+    bad = w.clone()
+    bad[m // 2, 1] += 1 << 32
+    L = torch.empty(n, dtype=torch.int64, device="cuda")
+    ctx.solve_u64_async(bad, n, L)
+    assert ctx.sync() == cc.CC_ERANGE
+    ed = to_dev(e)
+    P = torch.empty(n, dtype=torch.int32, device="cuda")
+    ctx.init(n, P)
+    ctx.zroot(ed, n, flags=cc.F_ZROOT | cc.F_ZROOT_HINT, zroot_hint=n - 1)
+    ctx.solve_u64_async(w, n, L)
+    ctx.hook(ed, n, P, flags=cc.F_ZROOT)
+    ctx.compress(n, P, flags=cc.F_ZROOT)
+    ctx.canon(n, P)
+    assert_same_labels(to_host_u32(P), want, f"steps around a wide solve {kind} n={n}")
