@@ -87,7 +87,7 @@ int cc_version(void);
    regrouped hooks would apply (none does with CC_F_NO_SPLIT).
    - The filter sorts the entries by the ranges of 2^19 vertices of both
      endpoints, so that both membership tests read LDS. Whole solves and the
-     CC_F_ZROOT hook take it from n = 1,179,649 to 2^27 with at least one entry
+     CC_F_ZROOT hook take it from n = 1,179,649 to 2^28 with at least one entry
      per vertex and 2^20 entries (2^24 beyond 22 ranges), below 2^32; on the
      plain path the bitmap is that of the giant component a sample of the
      entries shows. If the sample shows none, the device takes the direct hook.

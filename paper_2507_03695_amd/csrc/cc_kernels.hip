@@ -854,7 +854,8 @@ int run_push(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
 //
 // A skewed graph's giant component shows in a small sample; a uniform one's needs
 // about n / 2 entries, so where the device finds none in the small sample, one of
-// up to n entries is tried (lists of two entries per vertex and more). If that
+// a quarter of the entries, n at most, is tried (lists of three entries per vertex
+// and more: a quarter of less shows none in a uniform graph either). If that
 // shows none either, the whole-bitmap pass (passes 0) hooks what it must in P,
 // which costs it little; the tiles are not built and the direct hook takes the
 // list. Whole solves, always filtering / direct / as decided here (us): R-MAT
@@ -906,7 +907,7 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
         return rc;
     }
     if ((rc = run_find_giant(n, m, E, P, bits, st, zr, true, stream))) return rc;
-    const bool dense = m >= 2 * n;
+    const bool dense = m >= 3 * n;
     if (dense || link_first) {
         if ((rc = run_warm(n, m, E, P, st, zr, sym, dense ? full : small, again, stream))) return rc;
         if ((rc = run_find_giant(n, m, E, P, bits, st, zr, false, stream))) return rc;
@@ -916,7 +917,7 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
     if ((rc = run_giant_bits(n, m, E, P, bits, st, zr ? kBitsZr : kBitsPlain, 0, write, stream))) return rc;
     if ((rc = run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, on, stream))) return rc;
     const Gate off{&st->giant, 0u};
-    const uint32_t g = grid_for(m, kBlock * kEPT, kGridCap);
+    const uint32_t g = grid_for(m, kBlock * kEPT, kZrGrid);
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
     auto direct = [&](auto* e) {
         if (!zr) k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);

@@ -41,7 +41,7 @@ constexpr int kSliceBits = 19;                       // 2^19 vertices per slice
 constexpr uint32_t kSliceWords = (1u << kSliceBits) / 32;   // 16384 words = 64 KB
 constexpr uint32_t kLoMask = (1u << kSliceBits) - 1;
 
-// Packed entries. With at most 256 slices every ID is below 2^27, and inside a
+// Packed entries. With at most 512 slices every ID is below 2^28, and inside a
 // bucket the slice bits of an endpoint are known, so the buffers between the
 // passes hold fewer than 8 bytes per entry:
 //  level 1 (bucket a known): w = u_lo | v << 19, h = v >> 13 (4 + 2 bytes)
@@ -60,7 +60,8 @@ struct L2Buf {
     uint8_t* h;
 };
 
-constexpr int kMaxSlices = 256;
+constexpr int kMaxSlices = 512;
+constexpr int kMaxSlicesOther = 256;                 // the plain bucketed hook, CSR input
 constexpr int kC1 = 8192;                            // level-1 chunk (entries)
 constexpr int kC2 = 8192;                            // level-2 chunk (entries)
 constexpr int kPartBlock = 1024;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t1_part(const T* __restrict__ ed
         if (live) rank[k] = (uint16_t)atomicAdd(&hist[e[k].x >> kSliceBits], 1u);
     }
     __syncthreads();
-    wave_scan<4>(hist, start, R);
+    wave_scan<8>(hist, start, R);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k)
@@ -233,19 +234,19 @@ __global__ __launch_bounds__(kScanBlock) void k_t1_scan(const uint32_t* __restri
 // ---- 3. bucket bases and level-2 chunk counts ---------------------------------------------
 // base2[a]: first entry of bucket a in the second buffer; cbase[a]: first level-2
 // chunk of bucket a; cbase[R] is the total.
-__global__ __launch_bounds__(256) void k_t1_bases(const uint32_t* __restrict__ pre1, uint64_t nch1,
+__global__ __launch_bounds__(kMaxSlices) void k_t1_bases(const uint32_t* __restrict__ pre1, uint64_t nch1,
                                                   int R, uint64_t* __restrict__ base2,
                                                   uint32_t* __restrict__ cbase, Gate gate) {
     if (gated_off(gate)) return;
-    // one thread per slice (R <= 256): sizes, then block-wide exclusive prefixes
-    __shared__ uint64_t s_b[256];
-    __shared__ uint32_t s_c[256];
+    // one thread per slice (R <= kMaxSlices): sizes, then block-wide exclusive prefixes
+    __shared__ uint64_t s_b[kMaxSlices];
+    __shared__ uint32_t s_c[kMaxSlices];
     const int a = threadIdx.x;
     const uint32_t size = a < R ? pre1[(uint64_t)a * (nch1 + 1) + nch1] : 0u;
     s_b[a] = size;
     s_c[a] = (size + kC2 - 1) / kC2;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {          // inclusive Hillis-Steele scan
+    for (int off = 1; off < kMaxSlices; off <<= 1) {          // inclusive Hillis-Steele scan
         const uint64_t xb = a >= off ? s_b[a - off] : 0ull;
         const uint32_t xc = a >= off ? s_c[a - off] : 0u;
         __syncthreads();
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(256) void k_t1_bases(const uint32_t* __restrict__ p
 // Level-2 chunk t of bucket a covers virtual positions [t*kC2, min((t+1)*kC2, size_a)).
 // Its descriptor (8 words at desc[8 g], g = cbase[a] + t) holds what k_t2_part
 // needs in one read: the first (c0) and last (c1) level-1 chunk it gathers
-// from, a | count << 8, t, and the 64-bit output offset base2[a] + t*kC2. One
+// from, a | count << 9, t, and the 64-bit output offset base2[a] + t*kC2. One
 // thread per (a, c): it writes the fields of the chunks that start or end in
 // its segment [pre[c], pre[c+1]).
 __global__ __launch_bounds__(256) void k_t2_bounds(const uint32_t* __restrict__ pre1, uint64_t nch1,
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(256) void k_t2_bounds(const uint32_t* __restrict__ 
         if (first >= p0 && first < p1) {
             const uint64_t o = base2[a] + first;
             d[0] = (uint32_t)c;
-            d[2] = (uint32_t)a | ((last + 1 - first) << 8);
+            d[2] = (uint32_t)a | ((last + 1 - first) << 9);
             d[3] = t;
             d[4] = (uint32_t)o;
             d[5] = (uint32_t)(o >> 32);
@@ -316,7 +317,7 @@ __device__ __forceinline__ void t2_sort_write(const u32x2 (&e)[kPartEPT], uint32
         if (i < cnt) rank[k] = (uint16_t)atomicAdd(&hist[e[k].y >> kSliceBits], 1u);
     }
     __syncthreads();
-    wave_scan<4>(hist, start, R);
+    wave_scan<8>(hist, start, R);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k)
@@ -345,8 +346,8 @@ __device__ __forceinline__ uint32_t t2_gather(uint32_t g, const uint32_t* __rest
     const uint4 d0 = reinterpret_cast<const uint4*>(desc)[2 * (uint64_t)g];
     const uint4 d1 = reinterpret_cast<const uint4*>(desc)[2 * (uint64_t)g + 1];
     const uint64_t c0 = d0.x, c1 = d0.y;
-    const int a = (int)(d0.z & 0xFFu);
-    const uint32_t cnt = d0.z >> 8;
+    const int a = (int)(d0.z & 0x1FFu);
+    const uint32_t cnt = d0.z >> 9;
     const uint32_t t = d0.w;
     obase = (uint64_t)d1.x | ((uint64_t)d1.y << 32);
     a_out = a;
@@ -705,10 +706,15 @@ __device__ __forceinline__ void block_scan_2048(uint32_t* x, uint32_t n, uint32_
     __syncthreads();
 }
 
-constexpr int kBPerBlock = 2;    // second-endpoint slices handled by one workgroup
+// Second-endpoint slices handled by one workgroup of the two-pass filter: two up to
+// 256 slices (four and eight measured 0.3 ms worse on R-MAT-26); beyond, where a
+// (slice, slice) tile is mostly small against the 64 KB of bitmap it needs, eight
+// share one copy of the first slice.
+constexpr int kFewSlices = 256;
+__host__ __device__ inline int b_per_block(int R) { return R <= kFewSlices ? 2 : 8; }
 
 // Survivor regions: workgroup (a, bg) of the filter reads exactly the entries of
-// tiles (a, b), b in [2 bg, 2 bg + 2); its kept entries go to a region of that
+// tiles (a, b), b in group bg; its kept entries go to a region of that
 // size inside [base2[a], base2[a+1]) of the survivor buffer; regions are
 // consecutive, so wgoff[w + 1] ends region w (wgoff has R * nbg + 1 entries).
 // One block per a.
@@ -719,9 +725,9 @@ __global__ __launch_bounds__(256) void k_t3_regions(const uint16_t* __restrict__
     if (gated_off(gate)) return;
     // one block per (a, bg): the group's entries summed over bucket a's chunks
     __shared__ uint32_t ws[4];
-    const int nbg = (R + kBPerBlock - 1) / kBPerBlock;
+    const int kb = b_per_block(R), nbg = (R + kb - 1) / kb;
     const int a = blockIdx.x / nbg, bg = blockIdx.x % nbg;
-    const int blo = bg * kBPerBlock, bhi = min(R, blo + kBPerBlock);
+    const int blo = bg * kb, bhi = min(R, blo + kb);
     const uint32_t g0 = cbase[a], g1 = cbase[a + 1];
     uint32_t t = 0;
     for (uint32_t g = g0 + threadIdx.x; g < g1; g += 256)
@@ -733,20 +739,28 @@ __global__ __launch_bounds__(256) void k_t3_regions(const uint16_t* __restrict__
 }
 
 // Per slice a, the regions' offsets: base2[a] plus the sizes of the groups
-// before bg. One thread per a.
-__global__ __launch_bounds__(256) void k_t3_offsets(const uint32_t* __restrict__ wgsize, int R,
-                                                    const uint64_t* __restrict__ base2,
-                                                    uint64_t* __restrict__ wgoff, Gate gate) {
+// before bg (at most 128 groups). One wave per a.
+__global__ __launch_bounds__(64) void k_t3_offsets(const uint32_t* __restrict__ wgsize, int R,
+                                                   const uint64_t* __restrict__ base2,
+                                                   uint64_t* __restrict__ wgoff, Gate gate) {
     if (gated_off(gate)) return;
-    const int a = blockIdx.x * 256 + threadIdx.x;
-    if (a >= R) return;
-    const int nbg = (R + kBPerBlock - 1) / kBPerBlock;
-    uint64_t run = base2[a];
-    for (int bg = 0; bg < nbg; ++bg) {
-        wgoff[(uint64_t)a * nbg + bg] = run;
-        run += wgsize[(uint64_t)a * nbg + bg];
+    static_assert(kFewSlices / 2 <= 128 && kMaxSlices / 8 <= 128, "two groups per lane");
+    const int a = blockIdx.x, lane = threadIdx.x;
+    const int kb = b_per_block(R), nbg = (R + kb - 1) / kb;
+    const uint32_t* size = wgsize + (uint64_t)a * nbg;
+    const uint32_t x0 = 2 * lane < nbg ? size[2 * lane] : 0u;
+    const uint32_t x1 = 2 * lane + 1 < nbg ? size[2 * lane + 1] : 0u;
+    uint32_t incl = x0 + x1;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
     }
-    if (a == R - 1) wgoff[(uint64_t)R * nbg] = run;   // end of the last region
+    const uint64_t run = base2[a] + (incl - x0 - x1);
+    uint64_t* out = wgoff + (uint64_t)a * nbg;
+    if (2 * lane < nbg) out[2 * lane] = run;
+    if (2 * lane + 1 < nbg) out[2 * lane + 1] = run + x0;
+    if (a == R - 1 && lane == 63) out[nbg] = run + x0 + x1;   // end of the last region
 }
 
 // Run holding index j0 of the window (last t < nw with s_pre[t] <= j0), found
@@ -820,7 +834,10 @@ __device__ __forceinline__ void t3_flush(const uint32_t* w, uint32_t* zbits, uin
 //  kFullRuns   the two-pass tiles: kept for the survivor hook (a tile is short,
 //              2^16 entries on R-MAT-26, and hooking its rest at its end
 //              would leave the CU waiting: filter 4.2 ms against 2.9 + 0.4)
-enum FilterMode { kMarkTiles, kFullTiles, kFullRuns };
+//  kManyRuns   the same beyond kFewSlices slices, where a tile is small: marks go
+//              to the global bitmap one by one (t3_flush's pass over a slice costs
+//              as much as some ten thousand of them)
+enum FilterMode { kMarkTiles, kFullTiles, kFullRuns, kManyRuns };
 constexpr uint32_t kMarkPart = 8;
 constexpr uint32_t kTileCost = 8192;  // entries' worth of a tile's fixed time (8 us)
 
@@ -838,7 +855,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                                                            uint32_t* __restrict__ wgcnt,
                                                            DevState* st, Gate gate) {
     if (gated_off(gate)) return;
-    constexpr bool TILES = MODE != kFullRuns;
+    constexpr bool RUNS = MODE == kFullRuns || MODE == kManyRuns, TILES = !RUNS;
     __shared__ uint32_t sa[kSliceWords];
     __shared__ uint32_t sb[kSliceWords];
     __shared__ uint32_t s_off[kWin3];
@@ -851,7 +868,8 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
     // the b groups), so the workgroups running at the same time hold few
     // copies of any one slice and see each other's marks through the global
     // bitmap sooner. (a, bg) = (i mod R, (i div R + a) mod nbg) is a bijection.
-    constexpr int kB = TILES ? 1 : kBPerBlock;
+    const int kB = TILES ? 1 : b_per_block(R);
+    constexpr bool one_by_one = MODE == kManyRuns;
     const uint32_t nbg = ((uint32_t)R + kB - 1) / kB;
     int a = (int)(blockIdx.x % (uint32_t)R);
     const int bg = (int)((blockIdx.x / (uint32_t)R + (uint32_t)a) % nbg);
@@ -894,7 +912,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
     }
     const uint32_t wi = (uint32_t)a * nbg + (uint32_t)bg;   // region index (kFullRuns)
     __shared__ uint32_t s_used;
-    if (MODE == kFullRuns && threadIdx.x == 0) {
+    if (RUNS && threadIdx.x == 0) {
         s_used = 0;
         if (nch == 0) wgcnt[wi] = 0;
     }
@@ -902,7 +920,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
     uint32_t* ow = nullptr;
     uint16_t* oh = nullptr;
     uint32_t cap = 0;
-    if (MODE == kFullRuns) {
+    if (RUNS) {
         ow = sw + wgoff[wi];
         oh = sh + wgoff[wi];
         cap = (uint32_t)(wgoff[wi + 1] - wgoff[wi]);
@@ -964,14 +982,20 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         // hooked in P (Algorithm 3, path splitting).
         auto settle = [&](u32x2 x) {
             const bool mu = (sa[x.x >> 5] >> (x.x & 31)) & 1u, mv = (lb[x.y >> 5] >> (x.y & 31)) & 1u;
-            if (mu && !mv) atomicOr(&lb[x.y >> 5], 1u << (x.y & 31));
-            if (mv && !mu) atomicOr(&sa[x.x >> 5], 1u << (x.x & 31));
+            if (mu != mv) {
+                const uint32_t lo = mu ? x.y : x.x, bit = 1u << (lo & 31);
+                const uint32_t old = atomicOr(mu ? &lb[lo >> 5] : &sa[lo >> 5], bit);
+                if (one_by_one && !(old & bit)) {
+                    const uint32_t y = (mu ? bbase : abase) + lo;
+                    atomicOr(&zbits[y >> 5], bit);
+                }
+            }
             return !mu && !mv;
         };
         auto hook = [&](u32x2 x) {
             const uint32_t u = abase + x.x, v = bbase + x.y;
             if (MODE == kMarkTiles) return;
-            if (MODE == kFullRuns) {
+            if (RUNS) {
                 // one lane reserves room for all that are here
                 const uint64_t here = __ballot(true);
                 const int first = __ffsll((unsigned long long)here) - 1;
@@ -1093,20 +1117,21 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         // this slice's pending entries are settled before the next slice's
         // bitmap replaces it
         if (MODE != kMarkTiles) queue_finish(q, lane, settle, hook);
-        if (b != a) {
+        if (b != a && !one_by_one) {
             __syncthreads();
             t3_flush(sb, zbits, (uint64_t)b * kSliceWords, words);
         }
     }
     __syncthreads();
-    t3_flush(sa, zbits, (uint64_t)a * kSliceWords, words);
-    if (MODE == kFullRuns && threadIdx.x == 0) wgcnt[wi] = min(s_used, cap);
+    if (!one_by_one) t3_flush(sa, zbits, (uint64_t)a * kSliceWords, words);
+    if (RUNS && threadIdx.x == 0) wgcnt[wi] = min(s_used, cap);
 }
 
 // ---- 6. the survivor hook -------------------------------------------------------------------
 // Work items of kItem consecutive entries of one region: an exclusive prefix of
 // the regions' item counts, then a grid-stride loop over items, each mapped to
-// its region by a binary search of that prefix.
+// its region by a binary search of that prefix (regions are of very different
+// sizes: R-MAT-26's 320,000 path entries survive in two).
 constexpr int kPackBlock = 1024;
 constexpr uint32_t kItem = 1024;     // entries per work item (4 per thread)
 
@@ -1306,7 +1331,7 @@ static int slices(uint64_t n) { return (int)((n + (1ull << kSliceBits) - 1) >> k
 // (ER n = 2^21, 16 entries per vertex: 1.04 ms regrouped against 1.79 ms direct).
 bool tiled_eligible(uint64_t n, uint64_t m, bool zr) {
     const uint64_t R = (n + (1ull << kSliceBits) - 1) >> kSliceBits;
-    return R >= (zr ? 8u : 4u) && R <= (uint64_t)kMaxSlices && m >= (1ull << 24) &&
+    return R >= (zr ? 8u : 4u) && R <= (uint64_t)kMaxSlicesOther && m >= (1ull << 24) &&
            m < (1ull << 32);
 }
 
@@ -1315,7 +1340,9 @@ bool tiled_eligible(uint64_t n, uint64_t m, bool zr) {
 // hook is faster (zero root, grid n = 33 M, 30 M entries: 2.2 ms against 3.0;
 // ER n = 30 M, 18 M entries: 2.6 against 2.5). Two passes start at the size their
 // fixed costs (16 launches) are worth; one pass was faster from 2^20 entries on
-// (R-MAT n = 3 M, 12 M entries: 918 us direct, 314 here).
+// (R-MAT n = 3 M, 12 M entries: 918 us direct, 314 here). Up to 512 slices: a
+// sixteenth of R-MAT-28 (n = 2^28, 2^28 entries), 10.0 ms direct, 7.1 here (plain
+// 13.5 and 6.6); beyond, a tile holds fewer entries than its bitmaps words.
 int filter_passes(uint64_t n, uint64_t m) {
     const uint64_t R = (n + (1ull << kSliceBits) - 1) >> kSliceBits;
     if (n <= lds_bits_max_n() || R > (uint64_t)kMaxSlices || m >= (1ull << 32)) return 0;
@@ -1369,7 +1396,7 @@ static TiledLayout tiled_layout(uint64_t n, uint64_t m, int passes, bool bits, b
     }
     if (passes == 1) l.wcnt = take(4 * R * R * ((l.nch1 + kWin3 - 1) / kWin3));
     if (passes == 2) {
-        const uint64_t nwg = R * ((R + kBPerBlock - 1) / kBPerBlock);
+        const uint64_t kb = (uint64_t)b_per_block(l.R), nwg = R * ((R + kb - 1) / kb);
         l.wgoff = take(8 * (nwg + 1));
         l.wgcnt = take(4 * nwg);
         l.ipref = take(4 * (nwg + 1));
@@ -1456,7 +1483,7 @@ static int level1(const TiledLayout& l, char* q, uint64_t n, uint64_t m, EdgeLis
     if ((rc = cohere(stream))) return rc;
     k_t1_scan<<<R * ntile, kScanBlock, 0, stream>>>(cnt1, l.nch1, ntile, tsum, pre1, gate);
     if ((rc = cohere(stream))) return rc;
-    k_t1_bases<<<1, 256, 0, stream>>>(pre1, l.nch1, l.R, base2, cbase, gate);
+    k_t1_bases<<<1, kMaxSlices, 0, stream>>>(pre1, l.nch1, l.R, base2, cbase, gate);
     if ((rc = cohere(stream))) return rc;
     const uint64_t pairs = (uint64_t)R * l.nch1;
     k_t2_bounds<<<(uint32_t)((pairs + 255) / 256), 256, 0, stream>>>(pre1, l.nch1, l.R, cbase, base2,
@@ -1485,16 +1512,16 @@ static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_
                        uint32_t* cbase, uint32_t* sw, uint16_t* sh, uint64_t* wgoff,
                        uint32_t* wgcnt, uint32_t* ipref, uint32_t* P, uint32_t* zbits,
                        uint64_t words, DevState* st, Gate gate, hipStream_t stream) {
-    const uint32_t nbg = (uint32_t)((R + kBPerBlock - 1) / kBPerBlock);
+    const uint32_t nbg = (uint32_t)((R + b_per_block(R) - 1) / b_per_block(R));
     const uint32_t nwg = (uint32_t)R * nbg;
     int rc;
     k_t3_regions<<<nwg, 256, 0, stream>>>(run2, nch2, R, cbase, wgcnt, gate);
     if ((rc = cohere(stream))) return rc;
-    k_t3_offsets<<<(uint32_t)((R + 255) / 256), 256, 0, stream>>>(wgcnt, R, base2, wgoff, gate);
+    k_t3_offsets<<<(uint32_t)R, 64, 0, stream>>>(wgcnt, R, base2, wgoff, gate);
     if ((rc = cohere(stream))) return rc;
-    k_t3_filter<kFullRuns><<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, nch2, R, nullptr, base2, cbase,
-                                                            zbits, words, P, sw, sh, wgoff, wgcnt, st,
-                                                            gate);
+    auto filter = R <= kFewSlices ? &k_t3_filter<kFullRuns> : &k_t3_filter<kManyRuns>;
+    filter<<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, nch2, R, nullptr, base2, cbase, zbits, words, P,
+                                            sw, sh, wgoff, wgcnt, st, gate);
     if ((rc = cohere(stream))) return rc;
     k_t4_scan<<<1, kPackBlock, 0, stream>>>(wgcnt, nwg, ipref, gate);
     if ((rc = cohere(stream))) return rc;
@@ -1565,7 +1592,7 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
     const uint64_t b_base2 = al(8 * (R + 1)), b_cbase = al(4 * (R + 1));
     const uint64_t b_cfirst = al(4 * nch2), b_run2 = al(2 * nch2 * (R + 1));
     const uint64_t b_sw = al(4 * m), b_sh = al(2 * m);
-    const uint64_t nwg = (uint64_t)R * ((R + kBPerBlock - 1) / kBPerBlock);
+    const uint64_t kb = (uint64_t)b_per_block(R), nwg = (uint64_t)R * ((R + kb - 1) / kb);
     const uint64_t b_wgoff = al(8 * (nwg + 1)), b_wgcnt = al(4 * nwg), b_ipref = al(4 * (nwg + 1));
     int rc = grow(s, b_sw + b_sh + b_tmp2 + b_base2 + b_cbase + b_cfirst + b_run2 + b_wgoff + b_wgcnt +
                          b_ipref, stream);

@@ -194,3 +194,14 @@ def test_wide_ids(ctx, kind, n, m):
     ctx.compress(n, P, flags=cc.F_ZROOT)
     ctx.canon(n, P)
     assert_same_labels(to_host_u32(P), want, f"steps around a wide solve {kind} n={n}")
+
+
+def test_tiles_beyond_256_slices(ctx):
+    """512 second-endpoint slices: a share of R-MAT scale 28 (n = 2^28 global)."""
+    ed, n = graphgen.rmat_share_dev(28, 18, graphgen.config_seed(5), 16, 0)
+    assert ed.shape[0] >= n
+    log(f"share28 generated: m={ed.shape[0]}")
+    want = oracle.cc_labels(n, ed.cpu().numpy().view(np.uint32))
+    log("share28 oracle done")
+    for fl in (0, cc.F_ZROOT):
+        assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"share28 flags={fl}")
