@@ -123,10 +123,11 @@ __device__ __forceinline__ void llink(PT* P, uint32_t u, uint32_t pu, uint32_t v
 // One graph with its parent array in LDS (entries of type PT), by a group of T
 // threads (T = 64: one wavefront; T = kBatchBlock: the workgroup); idx is the
 // thread's index in the group. Returns whether this thread saw an endpoint out
-// of range.
+// of range. sym: only entries with u < v are hooked.
 template <int T, typename PT>
 __device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t* E, int64_t m,
-                                                glabel_t* out, int idx, uint2* q) {
+                                                glabel_t* out, int idx, uint2* q,
+                                                bool sym = false) {
     auto sync = [] {
         if (T == 64) wave_sync();
         else __syncthreads();
@@ -179,7 +180,7 @@ __device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t
             const bool in = (int64_t)k * T < rem;
             const bool ok = u < n && v < n;
             bad |= in && !ok;
-            live[k] = in && ok && u != v;
+            live[k] = in && ok && (sym ? u < v : u != v);
             pu[k] = live[k] ? (uint32_t)P[u] : 0u;
             pv[k] = live[k] ? (uint32_t)P[v] : 0u;
         }
@@ -400,6 +401,95 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch(const GraphDesc* __restri
         if (lane == 0) *(CCM_GLOBAL int32_t*)d.status = any_bad ? CC_ERANGE : CC_OK;
         wave_sync();   // the next graph's init must not overtake this one's reads
     }
+}
+
+// ---- one small graph ---------------------------------------------------------------------
+// A whole solve by one workgroup in one launch, parent array in LDS (32-bit
+// entries): small graphs are bound by the launches between the steps, each a few
+// microseconds. With a zero root (zr) the endpoint counts of all entries follow in
+// LDS too: the zero root (most occurrences, ties to the lowest ID; or the hint),
+// the smallest member of its component and the bitmap of that component are left
+// in the slot as the separate steps would.
+__global__ __launch_bounds__(kBatchBlock) void k_solve_small(const int32_t* edges, int64_t m,
+                                                             uint32_t n, uint32_t* L,
+                                                             uint32_t* zbits, DevState* st,
+                                                             uint32_t sym, int zr, int use_hint,
+                                                             uint32_t hint) {
+    extern __shared__ uint32_t sP[];                    // n parents, then n counts (zr)
+    __shared__ uint2 s_q[kWaves * kLinkQueue];
+    __shared__ unsigned long long s_sel;
+    gedge_t* E = (gedge_t*)edges;
+    const int tid = threadIdx.x;
+    const bool bad = solve_graph_lds<kBatchBlock, uint32_t>(sP, n, E, m, (glabel_t*)L, tid,
+                                                            s_q + (tid >> 6) * kLinkQueue, sym != 0);
+    if (bad) atomicOr(&st->status, kStatusRange);
+    if (!zr) {
+        if (tid == 0) st_agent(&st->mpub, kEmpty);
+        return;
+    }
+    uint32_t* cnt = sP + n;
+    for (uint32_t v = tid; v < n; v += kBatchBlock) cnt[v] = 0;
+    if (tid == 0) s_sel = 0;
+    __syncthreads();
+    uint32_t z = hint;
+    if (!use_hint) {
+        for (int64_t e = tid; e < m; e += kBatchBlock) {
+            const i32x2 x = E[e];
+            const uint32_t u = (uint32_t)x.x, v = (uint32_t)x.y;
+            if (u >= n || v >= n || u == v) continue;
+            atomicAdd(&cnt[u], 1u);
+            atomicAdd(&cnt[v], 1u);
+        }
+        __syncthreads();
+        unsigned long long best = 0;
+        for (uint32_t v = tid; v < n; v += kBatchBlock)
+            if (cnt[v]) best = max(best, ((unsigned long long)cnt[v] << 32) | (0xFFFFFFFFu - v));
+        if (best) atomicMax(&s_sel, best);
+        __syncthreads();
+        z = s_sel ? 0xFFFFFFFFu - (uint32_t)s_sel : 0u;
+    }
+    auto root = [&](uint32_t x) {
+        uint32_t p = sP[x];
+        while (p != x) { x = p; p = sP[x]; }
+        return x;                                       // the component's smallest ID
+    };
+    const uint32_t rz = root(z);
+    if (tid == 0) {
+        st_agent(&st->zroot, z);
+        st_agent(&st->zpub, z);
+        st_agent(&st->mpub, rz);
+    }
+    for (uint32_t v0 = tid & ~63u; v0 < n; v0 += kBatchBlock) {
+        const uint32_t v = v0 + (tid & 63);
+        const uint64_t in = __ballot(v < n && root(v < n ? v : 0u) == rz);
+        if ((tid & 63) == 0) st_agent(&zbits[v0 >> 5], (uint32_t)in);
+        if ((tid & 63) == 32 && v0 + 32 < n) st_agent(&zbits[(v0 >> 5) + 1], (uint32_t)(in >> 32));
+    }
+}
+
+// Sizes at which one workgroup (1.3 G entries/s) beats the separate launches. Whole
+// solves, launches against this (us): R-MAT n = 1,500, 12,000 entries plain 45
+// against 26 on its own, 56 against 36 through cc_solve with its waits; with the
+// zero root 75 against 25; R-MAT n = 16,000, 60,000 entries 56 against 48; ER n =
+// 300, 300 entries 19 against 9. The counts of the zero root take as much LDS again
+// as the parents.
+constexpr uint64_t kSmallMaxN = 32768, kSmallMaxM = 65536;
+
+bool small_eligible(uint64_t n, uint64_t m, uint32_t flags, uint32_t samples) {
+    const bool zr = flags & CC_F_ZROOT;
+    return n <= (zr ? kSmallMaxN / 2 : kSmallMaxN) && m <= kSmallMaxM && (!zr || m <= samples);
+}
+
+int run_solve_small(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* L,
+                    uint32_t flags, uint32_t hint, hipStream_t stream) {
+    const bool zr = flags & CC_F_ZROOT;
+    CCM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_solve_small),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 4 * (int)kSmallMaxN));
+    k_solve_small<<<1, kBatchBlock, (zr ? 8 : 4) * n, stream>>>(
+        reinterpret_cast<const int32_t*>(edges), (int64_t)m, (uint32_t)n, L, s->zbits, s->st,
+        (flags & CC_F_SYMMETRIC) ? 1u : 0u, zr, (flags & CC_F_ZROOT_HINT) ? 1 : 0, hint);
+    CCM_HIP(hipGetLastError());
+    return CC_OK;
 }
 
 // ---- multi role: whole-device launches over chunk tables -------------------------------

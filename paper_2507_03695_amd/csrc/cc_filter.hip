@@ -23,7 +23,7 @@ namespace ccm {
 // all entries meet on the words just below the few large roots (R-MAT n = 2^22,
 // 2^21 entries sampled: 389 us with splitting, 125 without). One entry per
 // thread: the pass is a chain of dependent reads and CASes per entry.
-constexpr int kWBlock = 256;
+constexpr int kWBlock = kSampleRun;
 constexpr uint32_t kWGrid = 8192;
 
 template <bool ZR, typename T>
@@ -119,7 +119,7 @@ template <bool PICK, typename T>
 __global__ __launch_bounds__(kGBlock) void k_find_giant(const T* __restrict__ edges, uint64_t m,
                                                         uint32_t* P, uint64_t n,
                                                         const uint32_t* zbits, DevState* st,
-                                                        int first, Gate gate) {
+                                                        int stage, Gate gate) {
     if (gated_off(gate)) return;
     uint32_t in, tot;
     const uint32_t z = PICK ? 0u : ld_agent(&st->zroot);
@@ -132,9 +132,9 @@ __global__ __launch_bounds__(kGBlock) void k_find_giant(const T* __restrict__ ed
     if (threadIdx.x == 0) {
         const uint32_t giant = giant_enough(in, tot);
         if (PICK) st_agent(&st->zroot, g);
-        if (first) st_agent(&st->giant1, giant);
+        if (stage < 2) st_agent(&st->giant1, giant);
         st_agent(&st->giant, giant);
-        st_agent(&st->rebuild, first ? 0u : giant);
+        st_agent(&st->rebuild, stage ? giant : 0u);
     }
 }
 
@@ -311,9 +311,14 @@ __global__ __launch_bounds__(kLBlock) void k_hook_lds(const T* __restrict__ edge
 
 uint64_t lds_bits_max_n() { return (uint64_t)kLdsBitsWords * 32; }
 
+uint64_t warm_stride(uint64_t m, uint64_t want) {
+    want = std::max<uint64_t>(want, 1);
+    return std::max<uint64_t>((m + want / 2) / want, 1);
+}
+
 int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool zr, bool sym,
              uint64_t want, Gate gate, hipStream_t stream) {
-    const uint64_t ts = std::max<uint64_t>(m / std::max<uint64_t>(want, 1), 1);
+    const uint64_t ts = warm_stride(m, want);
     const uint64_t tiles = ((m + kWBlock - 1) / kWBlock + ts - 1) / ts;
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
     const uint32_t g = (uint32_t)std::min<uint64_t>(tiles, kWGrid);
@@ -328,11 +333,11 @@ int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool
 }
 
 int run_find_giant(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, const uint32_t* zbits, DevState* st,
-                   bool zr, bool first, hipStream_t stream) {
-    const Gate gate = first ? Gate{} : Gate{&st->giant1, 0u};
+                   bool zr, int stage, hipStream_t stream) {
+    const Gate gate = stage ? Gate{&st->giant1, 0u} : Gate{};
     auto launch = [&](auto* e) {
-        if (zr) k_find_giant<false><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
-        else k_find_giant<true><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+        if (zr) k_find_giant<false><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, stage, gate);
+        else k_find_giant<true><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, stage, gate);
     };
     if (E.wide) launch((const uint64_t*)E.p);
     else launch((const uint32_t*)E.p);

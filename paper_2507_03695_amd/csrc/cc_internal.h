@@ -26,9 +26,9 @@ struct DevState {
     uint32_t mpub;      // smallest member of zpub's component (zero-root compress; cc_canon)
     uint64_t zsel;      // packed argmax (count << 32) | (0xFFFFFFFF - id); 0 = none
     uint64_t log_count; // messages of a drained update log (cc_hook_log_drain)
-    uint32_t giant1;    // after the first sample: its entries show a giant component
+    uint32_t giant1;    // a small sample shows a giant component
     uint32_t giant;     // the filter's kernels run (else the direct hook's)
-    uint32_t rebuild;   // the bitmap is to be written after the second sample
+    uint32_t rebuild;   // the bitmap is to be written after a sample without it
     uint32_t pad1;
     uint64_t pad2[2];
 };
@@ -270,16 +270,25 @@ enum BitsMode { kBitsPick, kBitsPlain, kBitsZr };
 int run_giant_bits(uint64_t n, uint64_t m, EdgeList E, const uint32_t* P, uint32_t* zbits,
                    DevState* st, int mode, int first, Gate gate, hipStream_t stream);
 // Whether the forest shows a giant component (the zero root's, by P and zbits,
-// with zr): st->giant, after the first sample st->giant1 too, after the second
-// (which runs where giant1 is 0) st->rebuild. A plain solve's root: st->zroot.
+// with zr): st->giant. Stages 1 and 2 run where st->giant1 is 0; 0 and 1 set it too,
+// 1 and 2 set st->rebuild. A plain solve's root: st->zroot.
 int run_find_giant(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, const uint32_t* zbits, DevState* st,
-                   bool zr, bool first, hipStream_t stream);
+                   bool zr, int stage, hipStream_t stream);
+// run_warm hooks every warm_stride-th run of kSampleRun entries.
+constexpr int kSampleRun = 256;
+uint64_t warm_stride(uint64_t m, uint64_t want);
 // About `want` entries hooked in P (no bitmap), spread evenly over the list.
 int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool zr, bool sym,
              uint64_t want, Gate gate, hipStream_t stream);
 // Every entry tested against the whole bitmap in LDS, the rest hooked in P.
 int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, DevState* st,
                  bool split, bool sym, int device, hipStream_t stream);
+
+// A whole solve of a small graph in one launch (cc_batch.hip). With CC_F_ZROOT the
+// slot's bitmap holds n bits and its sample covers every entry.
+bool small_eligible(uint64_t n, uint64_t m, uint32_t flags, uint32_t samples);
+int run_solve_small(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* L,
+                    uint32_t flags, uint32_t hint, hipStream_t stream);
 
 // Batched path (cc_batch.hip).
 // The schedule taken when nothing else is known about a batch.

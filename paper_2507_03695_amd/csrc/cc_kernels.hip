@@ -351,11 +351,14 @@ __global__ __launch_bounds__(kBlock) void k_hook(const uint32_t* __restrict__ ed
 }
 
 // The direct hook of a solve whose sample showed no giant component: k_hook's
-// tiles on a resident grid, which leaves at once where the filter runs instead.
+// tiles, left at once where the filter runs instead. The entries of the second
+// sample (every skip-th run of kSampleRun) are hooked already.
+static_assert(kBlock == kSampleRun, "a block's k-th entries are one run of the sample");
 template <bool ZR, int SPLIT, bool LINKZ, typename T>
 __global__ __launch_bounds__(kBlock) void k_hook_gated(const T* __restrict__ edges, uint64_t m,
                                                        uint32_t n, uint32_t* P, uint32_t* zbits,
-                                                       DevState* st, uint32_t sym, Gate gate) {
+                                                       DevState* st, uint32_t sym, uint32_t skip,
+                                                       Gate gate) {
     if (gated_off(gate)) return;
     const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
     for (uint64_t tile = (uint64_t)blockIdx.x * (kBlock * kEPT); tile < m;
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(kBlock) void k_hook_gated(const T* __restrict__ edg
         for (int k = 0; k < kEPT; ++k) {
             const uint64_t e = tile + (uint64_t)k * kBlock + threadIdx.x;
             u32x2 uv = {0u, 0u};
-            if (e < m) uv = load_entry(edges, e);
+            if (e < m && (tile / kBlock + k) % skip) uv = load_entry(edges, e);
             u[k] = uv.x;
             v[k] = uv.y;
         }
@@ -772,7 +775,7 @@ static uint64_t sample_count(uint64_t m, uint64_t K) { return m <= K ? m : K; }
 
 // Size the membership bitmap for n vertices and clear it (only z set). Marks the
 // slot ready for a zero-root hook when n is the current solve's.
-int zbits_reset(Slot* s, uint64_t n, hipStream_t stream) {
+static int zbits_grow(Slot* s, uint64_t n, hipStream_t stream) {
     const uint64_t words = (n + 31) / 32;
     if (s->zbits_cap < words) {
         if (s->no_grow) return fail(CC_ENOMEM, "zero-root bitmap exceeds the fixed scratch");
@@ -787,6 +790,13 @@ int zbits_reset(Slot* s, uint64_t n, hipStream_t stream) {
         }
         s->zbits_cap = words;
     }
+    return CC_OK;
+}
+
+int zbits_reset(Slot* s, uint64_t n, hipStream_t stream) {
+    const uint64_t words = (n + 31) / 32;
+    int rc = zbits_grow(s, n, stream);
+    if (rc) return rc;
     k_zbits_clear<<<grid_for(words, kBlock, kGridCap), kBlock, 0, stream>>>(s->zbits, words, s->st);
     CCM_HIP(hipGetLastError());
     s->zr_ready = (n == s->cur_n);
@@ -854,13 +864,11 @@ int run_push(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
 //
 // A skewed graph's giant component shows in a small sample; a uniform one's needs
 // about n / 2 entries, so where the device finds none in the small sample, one of
-// a quarter of the entries, n at most, is tried (lists of three entries per vertex
-// and more: a quarter of less shows none in a uniform graph either). If that
-// shows none either, the whole-bitmap pass (passes 0) hooks what it must in P,
+// up to n entries, half the list at most, is tried. If that shows none either, the whole-bitmap pass (passes 0) hooks what it must in P,
 // which costs it little; the tiles are not built and the direct hook takes the
 // list. Whole solves, always filtering / direct / as decided here (us): R-MAT
 // n = 3 M, 12 M entries 301 / 1412 / 285; ER n = 16 M, 60 M entries 4872 / 3970 /
-// 2353; grid n = 4 M, 8 M entries 9024 / 1050 / 1144.
+// 2353; grid n = 4 M, 8 M entries 9024 / 1050 / 1080.
 //
 // The regrouped zero-root hook of two partition passes takes its small sample by
 // the linking form instead, the first 1/1024 of the entries, which sets the bits
@@ -875,8 +883,10 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
     const bool sym = flags & CC_F_SYMMETRIC;
     DevState* st = s->st;
     const Gate always{}, again{&st->giant1, 0u}, on{passes ? &st->giant : nullptr, 1u};
-    const uint64_t full = std::min<uint64_t>(m / 4, n);
-    const uint64_t small = std::min({full, n / 16, kSampleSmall});
+    // sizes in entries that are hooked: one of two on a symmetric list
+    const uint64_t live = sym ? m / 2 : m, per = sym ? 2 : 1;
+    const uint64_t full = (passes ? std::min(live / 2, n - n / 16) : std::min(live / 4, n)) * per;
+    const uint64_t small = std::min(full, std::min<uint64_t>(n / 16, kSampleSmall) * per);
     int rc;
     auto compress = [&](Gate g) -> int {
         if (zr)
@@ -906,24 +916,30 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
     } else if ((rc = run_warm(n, m, E, P, st, zr, sym, small, always, stream))) {
         return rc;
     }
-    if ((rc = run_find_giant(n, m, E, P, bits, st, zr, true, stream))) return rc;
-    const bool dense = m >= 3 * n;
-    if (dense || link_first) {
-        if ((rc = run_warm(n, m, E, P, st, zr, sym, dense ? full : small, again, stream))) return rc;
-        if ((rc = run_find_giant(n, m, E, P, bits, st, zr, false, stream))) return rc;
+    if ((rc = run_find_giant(n, m, E, P, bits, st, zr, 0, stream))) return rc;
+    if (link_first) {
+        if ((rc = run_warm(n, m, E, P, st, zr, sym, small, again, stream))) return rc;
+        if ((rc = run_find_giant(n, m, E, P, bits, st, zr, 1, stream))) return rc;
     }
+    if ((rc = run_warm(n, m, E, P, st, zr, sym, full, again, stream))) return rc;
+    if ((rc = run_find_giant(n, m, E, P, bits, st, zr, 2, stream))) return rc;
     const Gate write = link_first ? Gate{&st->rebuild, 1u} : on;
     if ((rc = compress(write))) return rc;
     if ((rc = run_giant_bits(n, m, E, P, bits, st, zr ? kBitsZr : kBitsPlain, 0, write, stream))) return rc;
     if ((rc = run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, on, stream))) return rc;
     const Gate off{&st->giant, 0u};
-    const uint32_t g = grid_for(m, kBlock * kEPT, kZrGrid);
+    // Longer lists on a resident grid (ER n = 200 M, 400 M entries: 31.6 ms, one
+    // workgroup per tile 32.1; grid n = 33 M: 5.7 and 6.0), shorter ones without the
+    // loop (ER n = 2 M, 4.2 M entries: 1.79 ms resident, 1.49 so).
+    const uint64_t dt = (m + kBlock * kEPT - 1) / (kBlock * kEPT);
+    const uint32_t g = (uint32_t)std::min<uint64_t>(dt, dt <= 16384 ? dt : kZrGrid);
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
+    const uint32_t skip = (uint32_t)std::min<uint64_t>(warm_stride(m, full), 0xFFFFFFFFull);
     auto direct = [&](auto* e) {
-        if (!zr) k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);
+        if (!zr) k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
         else if (hook_links_z(flags, n))
-            k_hook_gated<true, 1, true><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);
-        else k_hook_gated<true, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, off);
+            k_hook_gated<true, 1, true><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
+        else k_hook_gated<true, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
     };
     if (E.wide) direct((const uint64_t*)E.p);
     else direct((const uint32_t*)E.p);
@@ -1254,6 +1270,13 @@ int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* 
               uint32_t flags, uint32_t hint, hipStream_t stream) {
     if (n == 0) return CC_OK;
     int rc;
+    if (!(flags & CC_F_NO_SPLIT) && small_eligible(n, m, flags, s->samples)) {
+        s->cur_n = n;
+        s->zr_ready = flags & CC_F_ZROOT;
+        if (s->zr_ready && (rc = zbits_grow(s, n, stream))) return rc;
+        if ((rc = run_solve_small(s, n, m, edges, L, flags, hint, stream))) return rc;
+        return cohere(stream);
+    }
     if ((rc = run_init(s, n, L, stream))) return rc;
     if (flags & CC_F_ZROOT) {
         if ((rc = run_zroot(s, n, m, edges, flags, hint, stream))) return rc;

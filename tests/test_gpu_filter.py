@@ -205,3 +205,33 @@ def test_tiles_beyond_256_slices(ctx):
     log("share28 oracle done")
     for fl in (0, cc.F_ZROOT):
         assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"share28 flags={fl}")
+
+
+@pytest.mark.parametrize("n,m", [(1, 0), (1, 5), (2, 1), (65, 64), (1023, 4096), (16384, 65536), (16385, 65536),
+                                 (32768, 65536), (32769, 65536), (32768, 65537), (16384, 65535)])
+def test_small_in_one_launch(n, m):
+    """Small whole solves by one workgroup: labels, the zero root and what later steps
+    read of it, symmetric lists, endpoints out of range."""
+    c = cc.Context()
+    e = graph("rmat", n, m, 5 * n + m) if n > 100 else graphgen.er(n, m, 5 * n + m)
+    want = oracle.cc_labels(n, e)
+    ed = to_dev(e)
+    for fl in (0, cc.F_ZROOT, cc.F_ZROOT | cc.F_ZROOT_EXACT):
+        assert_same_labels(to_host_u32(c.solve(ed, n, flags=fl)), want, f"n={n} m={m} flags={fl}")
+    if m <= 65536:
+        assert c.get_zroot() == oracle.zroot(n, e, 65536)
+    L = c.solve(ed, n, flags=cc.F_ZROOT | cc.F_ZROOT_HINT, zroot_hint=n - 1)
+    assert_same_labels(to_host_u32(L), want, f"n={n} m={m} hint")
+    assert c.get_zroot() == n - 1
+    sym = np.concatenate([e[:m // 2], e[:m // 2, ::-1]])
+    for fl in (cc.F_SYMMETRIC, cc.F_SYMMETRIC | cc.F_ZROOT):
+        assert_same_labels(to_host_u32(c.solve(to_dev(sym), n, flags=fl)), oracle.cc_labels(n, sym), f"sym {fl}")
+    one_way = sym[sym[:, 0] > sym[:, 1]]           # on such a list no entry is hooked
+    assert_same_labels(to_host_u32(c.solve(to_dev(one_way), n, flags=cc.F_SYMMETRIC)), np.arange(n), "one way")
+    if m:
+        b = e.copy()
+        b[-1] = [0, n]
+        for fl in (0, cc.F_ZROOT):
+            c.solve_async(to_dev(b), n, L, flags=fl)
+            assert c.sync() == cc.CC_ERANGE
+    c.close()
