@@ -27,7 +27,7 @@ constexpr int kWBlock = kSampleRun;
 constexpr uint32_t kWGrid = 8192;
 
 template <bool ZR, typename T>
-__global__ __launch_bounds__(kWBlock) void k_warm(const T* __restrict__ edges, uint64_t m, uint32_t n,
+__global__ __launch_bounds__(kWBlock) void k_warm(const T edges, uint64_t m, uint32_t n,
                                                   uint64_t tstride, uint64_t tiles, uint32_t* P,
                                                   DevState* st, uint32_t sym, Gate gate) {
     if (gated_off(gate)) return;
@@ -62,7 +62,7 @@ static_assert(kGTable == 1u << 11, "the sample's hash yields 11 bits");
 // many have the root g).
 // root_of(x) gives a vertex's root.
 template <typename T, class Root>
-__device__ __forceinline__ uint32_t sample_root(const T* edges, uint64_t m, uint64_t n, bool pick,
+__device__ __forceinline__ uint32_t sample_root(const T& edges, uint64_t m, uint64_t n, bool pick,
                                                 uint32_t g, uint32_t* count, uint32_t* total,
                                                 const Root& root_of) {
     __shared__ uint32_t s_key[kGTable], s_cnt[kGTable];
@@ -116,7 +116,7 @@ __device__ __forceinline__ uint32_t giant_enough(uint32_t in, uint32_t total) {
 }
 
 template <bool PICK, typename T>
-__global__ __launch_bounds__(kGBlock) void k_find_giant(const T* __restrict__ edges, uint64_t m,
+__global__ __launch_bounds__(kGBlock) void k_find_giant(const T edges, uint64_t m,
                                                         uint32_t* P, uint64_t n,
                                                         const uint32_t* zbits, DevState* st,
                                                         int stage, Gate gate) {
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kGBlock) void k_find_giant(const T* __restrict__ ed
 // component's (st->giant1). Each wave
 // writes the two words of 64 consecutive vertices from a ballot.
 template <int MODE, typename T>
-__global__ __launch_bounds__(kGBlock) void k_giant_bits(const T* __restrict__ edges, uint64_t m,
+__global__ __launch_bounds__(kGBlock) void k_giant_bits(const T edges, uint64_t m,
                                                         const uint32_t* P, uint64_t n,
                                                         uint32_t* zbits, DevState* st, int first,
                                                         Gate gate) {
@@ -214,7 +214,7 @@ constexpr uint32_t kMarkGrid = 128;            // workgroups of the marking pass
 constexpr uint32_t kLdsBitsWords = 36864;      // 144 KB; the queues take the rest of the 160
 
 template <int SPLIT, int kLEPT, bool MARK, typename T>
-__global__ __launch_bounds__(kLBlock) void k_hook_lds(const T* __restrict__ edges, uint64_t m,
+__global__ __launch_bounds__(kLBlock) void k_hook_lds(const T edges, uint64_t m,
                                                       uint32_t n, uint32_t* P, uint32_t* zbits,
                                                       DevState* st, uint32_t sym, uint32_t tstride) {
     extern __shared__ uint32_t bits[];
@@ -322,12 +322,14 @@ int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool
     const uint64_t tiles = ((m + kWBlock - 1) / kWBlock + ts - 1) / ts;
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
     const uint32_t g = (uint32_t)std::min<uint64_t>(tiles, kWGrid);
-    auto launch = [&](auto* e) {
-        if (zr) k_warm<true><<<g, kWBlock, 0, stream>>>(e, m, n32, ts, tiles, P, st, sy, gate);
-        else k_warm<false><<<g, kWBlock, 0, stream>>>(e, m, n32, ts, tiles, P, st, sy, gate);
-    };
-    if (E.wide) launch((const uint64_t*)E.p);
-    else launch((const uint32_t*)E.p);
+    if (zr)
+        with_entries(E, [&](auto e) {
+            k_warm<true><<<g, kWBlock, 0, stream>>>(e, m, n32, ts, tiles, P, st, sy, gate);
+        });
+    else
+        with_coo(E, [&](auto e) {
+            k_warm<false><<<g, kWBlock, 0, stream>>>(e, m, n32, ts, tiles, P, st, sy, gate);
+        });
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -335,12 +337,14 @@ int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool
 int run_find_giant(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, const uint32_t* zbits, DevState* st,
                    bool zr, int stage, hipStream_t stream) {
     const Gate gate = stage ? Gate{&st->giant1, 0u} : Gate{};
-    auto launch = [&](auto* e) {
-        if (zr) k_find_giant<false><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, stage, gate);
-        else k_find_giant<true><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, stage, gate);
-    };
-    if (E.wide) launch((const uint64_t*)E.p);
-    else launch((const uint32_t*)E.p);
+    if (zr)
+        with_entries(E, [&](auto e) {
+            k_find_giant<false><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, stage, gate);
+        });
+    else
+        with_coo(E, [&](auto e) {
+            k_find_giant<true><<<1, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, stage, gate);
+        });
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -349,13 +353,21 @@ int run_giant_bits(uint64_t n, uint64_t m, EdgeList E, const uint32_t* P, uint32
                    DevState* st, int mode, int first, Gate gate, hipStream_t stream) {
     const uint64_t blocks = (n + 4 * kGBlock - 1) / (4 * kGBlock);
     const uint32_t g = (uint32_t)std::min<uint64_t>(blocks, 2048);
-    const uint32_t* e32 = (const uint32_t*)E.p;
-    if (mode == kBitsZr) k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(e32, m, P, n, zbits, st, first, gate);
-    else if (mode == kBitsPlain)
-        k_giant_bits<kBitsPlain><<<g, kGBlock, 0, stream>>>(e32, m, P, n, zbits, st, first, gate);
-    else if (E.wide)
-        k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>((const uint64_t*)E.p, m, P, n, zbits, st, first, gate);
-    else k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>(e32, m, P, n, zbits, st, first, gate);
+    const uint32_t* none = nullptr;
+    auto launch = [&](auto e) {
+        k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+    };
+    if (mode == kBitsZr && first) {
+        with_entries(E, [&](auto e) {
+            k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+        });
+    } else if (mode == kBitsZr) {
+        k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(none, m, P, n, zbits, st, first, gate);
+    } else if (mode == kBitsPlain) {
+        k_giant_bits<kBitsPlain><<<g, kGBlock, 0, stream>>>(none, m, P, n, zbits, st, first, gate);
+    } else {
+        with_coo(E, launch);
+    }
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -371,7 +383,7 @@ int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbit
     const uint64_t tile = (uint64_t)kLBlock * (wide ? 8 : 2);
     const uint32_t g = (uint32_t)std::min<uint64_t>((m + tile - 1) / tile, wgs);
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
-    auto launch = [&](auto kernel, auto* e, uint32_t ts, uint32_t blocks) -> int {
+    auto launch = [&](auto kernel, auto e, uint32_t ts, uint32_t blocks) -> int {
         // the largest size, whatever this call needs: the attribute belongs to the
         // kernel, and another thread's call may need more than this one
         CCM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
@@ -381,8 +393,8 @@ int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbit
         CCM_HIP(hipGetLastError());
         return CC_OK;
     };
-    auto pick = [&](auto* e) -> int {
-        using T = std::remove_const_t<std::remove_pointer_t<decltype(e)>>;
+    auto pick = [&](auto e) -> int {
+        using T = decltype(e);
         // Every fourth round by few workgroups, marks only: what each learns about
         // its copy, all know in the full pass, instead of hooking in P what the
         // others have marked (R-MAT n = 1,000,003, 15 M entries, whole solve: 332 us
@@ -396,7 +408,7 @@ int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbit
             return launch(wide ? &k_hook_lds<1, 8, false, T> : &k_hook_lds<1, 2, false, T>, e, 1u, g);
         return launch(wide ? &k_hook_lds<0, 8, false, T> : &k_hook_lds<0, 2, false, T>, e, 1u, g);
     };
-    return E.wide ? pick((const uint64_t*)E.p) : pick((const uint32_t*)E.p);
+    return with_entries(E, pick);
 }
 
 }  // namespace ccm

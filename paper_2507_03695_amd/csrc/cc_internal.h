@@ -130,11 +130,33 @@ struct Slot {
 int slot_create(Slot* s, int device, uint32_t samples);
 void slot_destroy(Slot* s);
 
-// A COO list: 2m IDs of 32 bits, or 64 (wide).
+// A graph's rows as entries (u, adj[i]), off[u] <= i < off[u + 1]; tstart[t] is the
+// row of position t * kCsrTile.
+constexpr int kCsrTile = 1024;
+struct CsrList {
+    const uint64_t* off;
+    const uint32_t* adj;
+    const uint32_t* tstart;
+    uint64_t ntiles;
+    uint32_t n;
+};
+// The entries of a solve: a COO list of 2m IDs of 32 bits, or of 64 (wide), or a CSR
+// graph (csr not NULL).
 struct EdgeList {
     const void* p;
     bool wide;
+    const CsrList* csr = nullptr;
 };
+// f(entries) with the type that load_entry takes. Only the zero-root filters come
+// with CSR graphs (with_entries), the others with COO lists.
+template <class F>
+auto with_coo(const EdgeList& E, const F& f) {
+    return E.wide ? f((const uint64_t*)E.p) : f((const uint32_t*)E.p);
+}
+template <class F>
+auto with_entries(const EdgeList& E, const F& f) {
+    return E.csr ? f(*E.csr) : with_coo(E, f);
+}
 
 // Which launches of a solve run is in part decided on the device: a kernel given
 // a gate leaves at once unless *word == want (word NULL: always runs).

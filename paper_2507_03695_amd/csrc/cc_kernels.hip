@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kBlock) void k_hook(const uint32_t* __restrict__ ed
 // sample (every skip-th run of kSampleRun) are hooked already.
 static_assert(kBlock == kSampleRun, "a block's k-th entries are one run of the sample");
 template <bool ZR, int SPLIT, bool LINKZ, typename T>
-__global__ __launch_bounds__(kBlock) void k_hook_gated(const T* __restrict__ edges, uint64_t m,
+__global__ __launch_bounds__(kBlock) void k_hook_gated(const T edges, uint64_t m,
                                                        uint32_t n, uint32_t* P, uint32_t* zbits,
                                                        DevState* st, uint32_t sym, uint32_t skip,
                                                        Gate gate) {
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(kBlock) void k_hook_gated(const T* __restrict__ edg
 // max-scan in LDS. A tile that spans more than kSweepMax rows (long runs of
 // empty rows) searches each position's row instead, so no workgroup's work
 // grows with the length of such runs beyond a logarithm.
-constexpr int kCsrTile = kBlock * kEPT;
+static_assert(kCsrTile == kBlock * kEPT, "a workgroup's tile");
 constexpr uint32_t kSweepMax = 4 * kCsrTile;
 
 // Checks the offsets (non-decreasing, off[0] = 0, off[n] = m) and writes the
@@ -935,14 +935,18 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
     const uint32_t g = (uint32_t)std::min<uint64_t>(dt, dt <= 16384 ? dt : kZrGrid);
     const uint32_t n32 = (uint32_t)n, sy = sym ? 1u : 0u;
     const uint32_t skip = (uint32_t)std::min<uint64_t>(warm_stride(m, full), 0xFFFFFFFFull);
-    auto direct = [&](auto* e) {
-        if (!zr) k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
-        else if (hook_links_z(flags, n))
+    if (!zr)
+        with_coo(E, [&](auto e) {
+            k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
+        });
+    else if (hook_links_z(flags, n))
+        with_entries(E, [&](auto e) {
             k_hook_gated<true, 1, true><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
-        else k_hook_gated<true, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
-    };
-    if (E.wide) direct((const uint64_t*)E.p);
-    else direct((const uint32_t*)E.p);
+        });
+    else
+        with_coo(E, [&](auto e) {
+            k_hook_gated<true, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
+        });
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -1162,6 +1166,26 @@ int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const ui
         CCM_HIP(hipGetLastError());
     }
     if ((rc = cohere(stream))) return rc;
+    if (zr && !(flags & CC_F_NO_SPLIT)) {
+        // The whole-bitmap and one-pass tile filters read the rows as entries (ms:
+        // extras n = 1.7 M, 10.4 M entries 0.58 direct, 0.40 so; ER n = 400,000, 1.5 M
+        // entries 0.40 and 0.24; grid n = 3 M, 4 M entries 0.51 and 0.56, hence three
+        // entries per two vertices at least). The regrouped hook of two passes has
+        // its own CSR form below. The plain direct hook, whose lanes share their first
+        // endpoint's reads, is hard to beat here: ER n = 12 M, 60 M entries 1.98 ms
+        // direct, 2.54 filtered.
+        const CsrList rows{off, adj, s->csr_tiles, ntiles, (uint32_t)n};
+        const EdgeList E{nullptr, false, &rows};
+        const bool lds = lds_eligible(n, m);
+        const int passes = (flags & CC_F_NO_TILE) || s->no_tiled || 2 * m < 3 * n ? 0 : filter_passes(n, m);
+        FilterScratch fs{};
+        if (lds || (passes == 1 && !filter_scratch(s, n, m, passes, false, false, stream, &fs))) {
+            if ((rc = hook_by_bits(s, n, m, E, L, s->zbits, passes, true, false, false, flags, stream)))
+                return rc;
+            if ((rc = run_compress(s, n, L, flags, stream, true))) return rc;
+            return cohere(stream);
+        }
+    }
     if (zr && !(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE)) && tiled_eligible(n, m, true)) {
         // as on COO input: a warm-up over the first 1/1024 of the tiles seeds the
         // bitmap, then the regrouped hook covers every position (the warm-up's

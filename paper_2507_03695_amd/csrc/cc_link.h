@@ -19,6 +19,24 @@ __device__ __forceinline__ u32x2 load_entry(const uint64_t* edges, uint64_t i) {
     return u32x2{x.x < kEmpty ? (uint32_t)x.x : kEmpty, x.y < kEmpty ? (uint32_t)x.y : kEmpty};
 }
 
+// Position i of a CSR graph as an entry: its row by a search between the first row
+// of i's tile and the next tile's (consecutive lanes search the same few rows, so
+// the steps are L1 hits). Clamped like the CSR hook's rows, so that offsets that are
+// no row index keep every access in its array.
+__device__ __forceinline__ u32x2 load_entry(const CsrList& g, uint64_t i) {
+    const uint64_t t = i / kCsrTile;
+    const uint32_t v = __builtin_nontemporal_load(g.adj + i);
+    uint32_t lo = g.tstart[t], hi = t + 1 < g.ntiles ? g.tstart[t + 1] : g.n - 1;
+    if (lo >= g.n) lo = g.n - 1;
+    if (hi >= g.n || hi < lo) hi = lo;
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo + 1) / 2;
+        if (g.off[mid] <= i) lo = mid;
+        else hi = mid - 1;
+    }
+    return u32x2{lo, v};
+}
+
 __device__ __forceinline__ bool gated_off(Gate g) { return g.word && ld_agent(g.word) != g.want; }
 
 // ---- keys: Formula 1's R used as an order while P stores vertex IDs ----------

@@ -99,7 +99,7 @@ __device__ __forceinline__ void wave_scan(const uint32_t* cnt, uint32_t* start, 
 
 // ---- 1. level-1 partition by the first endpoint's slice -----------------------------
 template <typename T>
-__global__ __launch_bounds__(kPartBlock) void k_t1_part(const T* __restrict__ edges,
+__global__ __launch_bounds__(kPartBlock) void k_t1_part(const T edges,
                                                         uint64_t m, uint32_t n, int R,
                                                         uint64_t nch1, uint32_t* __restrict__ t1w,
                                                         uint16_t* __restrict__ t1h,
@@ -1256,7 +1256,7 @@ constexpr int kMaxOnePass = 22;
 constexpr int kMaxTiles = kMaxOnePass * kMaxOnePass;
 
 template <typename T>
-__global__ __launch_bounds__(kPartBlock) void k_tile_part(const T* __restrict__ edges, uint64_t m,
+__global__ __launch_bounds__(kPartBlock) void k_tile_part(const T edges, uint64_t m,
                                                           uint32_t n, int R, uint64_t nch,
                                                           L2Buf out, uint16_t* __restrict__ run2T,
                                                           DevState* st, uint32_t sym, Gate gate) {
@@ -1472,12 +1472,10 @@ static int level1(const TiledLayout& l, char* q, uint64_t n, uint64_t m, EdgeLis
     int rc;
     // every kernel below reads tables the previous one wrote: coherence points between
     if ((rc = cohere(stream))) return rc;
-    if (E.wide)
-        k_t1_part<<<g1, kPartBlock, 0, stream>>>((const uint64_t*)E.p, m, (uint32_t)n, l.R, l.nch1,
-                                                 t1w, t1h, seg, cnt1, st, sym ? 1u : 0u, gate);
-    else
-        k_t1_part<<<g1, kPartBlock, 0, stream>>>((const uint32_t*)E.p, m, (uint32_t)n, l.R, l.nch1,
-                                                 t1w, t1h, seg, cnt1, st, sym ? 1u : 0u, gate);
+    with_coo(E, [&](auto e) {
+        k_t1_part<<<g1, kPartBlock, 0, stream>>>(e, m, (uint32_t)n, l.R, l.nch1, t1w, t1h, seg, cnt1, st,
+                                                 sym ? 1u : 0u, gate);
+    });
     if ((rc = cohere(stream))) return rc;
     k_t1_tsum<<<R * ntile, kScanBlock, 0, stream>>>(cnt1, l.nch1, ntile, tsum, gate);
     if ((rc = cohere(stream))) return rc;
@@ -1542,12 +1540,10 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
     int rc;
     if (passes == 1) {
         const uint32_t g = (uint32_t)l.nch1;
-        if (E.wide)
-            k_tile_part<<<g, kPartBlock, 0, stream>>>((const uint64_t*)E.p, m, (uint32_t)n, l.R,
-                                                      l.nch1, tmp2, run2, s->st, sym ? 1u : 0u, gate);
-        else
-            k_tile_part<<<g, kPartBlock, 0, stream>>>((const uint32_t*)E.p, m, (uint32_t)n, l.R,
-                                                      l.nch1, tmp2, run2, s->st, sym ? 1u : 0u, gate);
+        with_entries(E, [&](auto e) {
+            k_tile_part<<<g, kPartBlock, 0, stream>>>(e, m, (uint32_t)n, l.R, l.nch1, tmp2, run2, s->st,
+                                                      sym ? 1u : 0u, gate);
+        });
         if ((rc = cohere(stream))) return rc;
         const uint32_t nwin = (uint32_t)((l.nch1 + kWin3 - 1) / kWin3);
         auto* wcnt = reinterpret_cast<uint32_t*>(q + l.wcnt);

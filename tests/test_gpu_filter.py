@@ -235,3 +235,35 @@ def test_small_in_one_launch(n, m):
             c.solve_async(to_dev(b), n, L, flags=fl)
             assert c.sync() == cc.CC_ERANGE
     c.close()
+
+
+@pytest.mark.parametrize("kind,n,m", [("rmat", 65537, 1 << 18), ("er", LDS_MAX_N, 3_000_000),
+                                      ("paths", 300_001, 1_000_003), ("paths", 3 * SLICE + 1, 3_000_000),
+                                      ("rmat", 8 * SLICE + 40, 12_000_000), ("er", 8 * SLICE + 40, 12_000_000)])
+def test_rows(ctx, kind, n, m):
+    """CSR graphs read as entries by the zero-root filters: empty rows, symmetric rows,
+    offsets that are no row index."""
+    e = graph(kind, n, m, n + m).astype(np.int64)
+    e[:, 0] -= e[:, 0] % 3                         # two rows in three are empty
+    e = e[np.argsort(e[:, 0], kind="stable")]
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(e[:, 0], minlength=n), out=off[1:])
+    adj = to_dev(np.stack([e[:, 1], e[:, 1]], 1).astype(np.uint32))[:, 0].contiguous()
+    offd = torch.from_numpy(off).cuda()
+    want = oracle.cc_labels(n, e.astype(np.uint32))
+    log(f"rows {kind} n={n} m={m}")
+    for fl in (0, cc.F_ZROOT):
+        assert_same_labels(to_host_u32(ctx.solve_csr(offd, adj, n, flags=fl)), want, f"rows {kind} n={n} {fl}")
+    assert ctx.get_zroot() == oracle.zroot_csr(off.astype(np.uint64))
+    both = np.concatenate([e, e[:, ::-1]])         # a list in both orders, as the flag says
+    both = both[np.argsort(both[:, 0], kind="stable")]
+    off2 = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(both[:, 0], minlength=n), out=off2[1:])
+    adj2 = to_dev(np.stack([both[:, 1], both[:, 1]], 1).astype(np.uint32))[:, 0].contiguous()
+    got = ctx.solve_csr(torch.from_numpy(off2).cuda(), adj2, n, flags=cc.F_ZROOT | cc.F_SYMMETRIC)
+    assert_same_labels(to_host_u32(got), want, f"rows {kind} n={n} symmetric")
+    L = torch.empty(n, dtype=torch.int32, device="cuda")
+    bad = offd.clone()
+    bad[n // 2] = m + 5
+    ctx.solve_csr_async(bad, adj, n, L, flags=cc.F_ZROOT)
+    assert ctx.sync() == cc.CC_EINVAL
