@@ -46,6 +46,7 @@ constexpr int kWaveTicket = 16;    // the wave list's, on its own 64-byte line
 constexpr int kBatchEPT = 8;     // entries per thread and round on the HBM paths
 constexpr int kLdsEPT = 4;       // the same with the parent array in LDS
 constexpr int kLinkQueue = 127;  // per-wave LDS slots of entries that need a walk
+constexpr int64_t kNarrowM = 1 << 28;   // entries whose byte offsets, two rounds on, fit 32 bits
 
 // Agent-scope store to a global word (see the store rule in cc_kernels.hip).
 __device__ __forceinline__ void gstore(glabel_t* p, uint32_t v) {
@@ -124,8 +125,11 @@ __device__ __forceinline__ void llink(PT* P, uint32_t u, uint32_t pu, uint32_t v
 // threads (T = 64: one wavefront; T = kBatchBlock: the workgroup); idx is the
 // thread's index in the group. Returns whether this thread saw an endpoint out
 // of range. sym: only entries with u < v are hooked.
-template <int T, typename PT>
-__device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t* E, int64_t m,
+// I: the index type of the entries, 32 bits where byte offsets fit them (then an
+// entry's address is one offset to a scalar base: two VALU instructions per load
+// instead of eight).
+template <int T, typename PT, typename I>
+__device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t* E, I m,
                                                 glabel_t* out, int idx, uint2* q,
                                                 bool sym = false) {
     auto sync = [] {
@@ -155,30 +159,34 @@ __device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t
     // are queued the wave links them together, one per lane (4,096-graph
     // batch: 1.55 -> 1.28 ms). The parents read may have changed meanwhile;
     // they are still ancestors, which is all a walk needs.
-    constexpr int64_t kRound = (int64_t)T * kLdsEPT;
+    constexpr I kRound = (I)T * kLdsEPT;
     const int lane = idx & 63;
+    auto load = [&](I e) {
+        e = e < m ? e : m - 1;
+        if (sizeof(I) == 8) return __builtin_nontemporal_load(E + e);
+        return __builtin_nontemporal_load((gedge_t*)((const CCM_GLOBAL char*)E + (uint32_t)(8u * (uint32_t)e)));
+    };
     uint32_t qn = 0;                 // queued entries: the same in every lane
     i32x2 A[kLdsEPT], B[kLdsEPT];
 #pragma unroll
     for (int k = 0; k < kLdsEPT; ++k) {
-        const int64_t e = idx + (int64_t)k * T, f = e + kRound;
+        const I e = (I)idx + (I)k * T;
         A[k] = i32x2{0, 0};
         B[k] = i32x2{0, 0};
         if (m > 0) {
-            A[k] = __builtin_nontemporal_load(E + (e < m ? e : 0));
-            B[k] = __builtin_nontemporal_load(E + (f < m ? f : 0));
+            A[k] = load(e);
+            B[k] = load(e + kRound);
         }
     }
-    auto round = [&](i32x2 (&x)[kLdsEPT], int64_t e0) {
+    auto round = [&](i32x2 (&x)[kLdsEPT], I e0) {
         // every entry's two parent reads first (LDS latency overlaps), then the tests
         uint32_t pu[kLdsEPT], pv[kLdsEPT];
         bool live[kLdsEPT];
-        const int64_t rem = m - e0;
 #pragma unroll
         for (int k = 0; k < kLdsEPT; ++k) {
             const uint32_t u = (uint32_t)x[k].x, v = (uint32_t)x[k].y;
-            const bool in = (int64_t)k * T < rem;
-            const bool ok = u < n && v < n;
+            const bool in = e0 + (I)k * T < m;
+            const bool ok = max(u, v) < n;
             bad |= in && !ok;
             live[k] = in && ok && (sym ? u < v : u != v);
             pu[k] = live[k] ? (uint32_t)P[u] : 0u;
@@ -189,10 +197,12 @@ __device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t
             const uint32_t u = (uint32_t)x[k].x, v = (uint32_t)x[k].y;
             const bool walk = live[k] && !(pu[k] == pv[k] || pu[k] == v || pv[k] == u);
             const uint64_t ball = __ballot(walk);
-            if (walk)
-                q[qn + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] =
-                    uint2{u | (v << 16), pu[k] | (pv[k] << 16)};
-            qn += (uint32_t)__popcll(ball);
+            if (ball) {
+                if (walk)
+                    q[qn + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] =
+                        uint2{u | (v << 16), pu[k] | (pv[k] << 16)};
+                qn += (uint32_t)__popcll(ball);
+            }
             if (qn >= 64) {
                 wave_sync();
                 const uint2 a = q[lane];
@@ -203,13 +213,12 @@ __device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t
                 qn -= 64;
                 wave_sync();
             }
-            const int64_t e = e0 + 2 * kRound + (int64_t)k * T;
-            x[k] = __builtin_nontemporal_load(E + (e < m ? e : 0));
+            x[k] = load(e0 + 2 * kRound + (I)k * T);
         }
     };
     // loop control from the wave's first index, so that every lane of the wave
     // runs every round (the queue's ballots and count need the whole wave)
-    for (int64_t b0 = idx - lane; b0 < m; b0 += 2 * kRound) {
+    for (I b0 = idx - lane; b0 < m; b0 += 2 * kRound) {
         round(A, b0 + lane);
         if (b0 + kRound >= m) break;
         round(B, b0 + lane + kRound);
@@ -229,6 +238,13 @@ __device__ __forceinline__ bool solve_graph_lds(uint32_t* S, uint32_t n, gedge_t
         gstore(&out[v], r);
     }
     return bad;
+}
+
+template <int T, typename PT>
+__device__ __forceinline__ bool solve_graph_lds_any(uint32_t* S, uint32_t n, gedge_t* E, int64_t m,
+                                                    glabel_t* out, int idx, uint2* q) {
+    if (m < kNarrowM) return solve_graph_lds<T, PT, int32_t>(S, n, E, (int32_t)m, out, idx, q);
+    return solve_graph_lds<T, PT, int64_t>(S, n, E, m, out, idx, q);
 }
 
 // ---- 32-bit parent array in the label slice (HBM) --------------------------------------
@@ -368,13 +384,13 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch(const GraphDesc* __restri
         __syncthreads();
         const uint32_t t = s_next;
         if (t >= Gt) break;
-        const GraphDesc d = descs[order[t]];
+        const GraphDesc d = descs[__builtin_amdgcn_readfirstlane(order[__builtin_amdgcn_readfirstlane(t)])];
         gedge_t* E = (gedge_t*)d.edges;
         if (d.n <= lds16_cap / 2) {
-            if (solve_graph_lds<kBatchBlock, uint32_t>(sP, d.n, E, d.m, (glabel_t*)d.L, threadIdx.x, myq))
+            if (solve_graph_lds_any<kBatchBlock, uint32_t>(sP, d.n, E, d.m, (glabel_t*)d.L, threadIdx.x, myq))
                 s_bad = 1;
         } else if (d.n <= lds16_cap) {
-            if (solve_graph_lds<kBatchBlock, uint16_t>(sP, d.n, E, d.m, (glabel_t*)d.L, threadIdx.x, myq))
+            if (solve_graph_lds_any<kBatchBlock, uint16_t>(sP, d.n, E, d.m, (glabel_t*)d.L, threadIdx.x, myq))
                 s_bad = 1;
         } else {
             solve_graph_hbm((glabel_t*)d.L, d.n, E, d.m, &s_bad);
@@ -392,11 +408,11 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch(const GraphDesc* __restri
         if (lane == 0) t = atomicAdd(&tickets[kWaveTicket], 1u);
         t = __shfl(t, 0);
         if (t >= Gw) break;
-        const GraphDesc d = descs[order[Gt + t]];
+        const GraphDesc d = descs[__builtin_amdgcn_readfirstlane(order[Gt + __builtin_amdgcn_readfirstlane(t)])];
         gedge_t* E = (gedge_t*)d.edges;
         const bool bad = d.n <= wave_words
-                             ? solve_graph_lds<64, uint32_t>(wP, d.n, E, d.m, (glabel_t*)d.L, lane, myq)
-                             : solve_graph_lds<64, uint16_t>(wP, d.n, E, d.m, (glabel_t*)d.L, lane, myq);
+                             ? solve_graph_lds_any<64, uint32_t>(wP, d.n, E, d.m, (glabel_t*)d.L, lane, myq)
+                             : solve_graph_lds_any<64, uint16_t>(wP, d.n, E, d.m, (glabel_t*)d.L, lane, myq);
         const bool any_bad = __ballot(bad) != 0;
         if (lane == 0) *(CCM_GLOBAL int32_t*)d.status = any_bad ? CC_ERANGE : CC_OK;
         wave_sync();   // the next graph's init must not overtake this one's reads
@@ -420,7 +436,7 @@ __global__ __launch_bounds__(kBatchBlock) void k_solve_small(const int32_t* edge
     __shared__ unsigned long long s_sel;
     gedge_t* E = (gedge_t*)edges;
     const int tid = threadIdx.x;
-    const bool bad = solve_graph_lds<kBatchBlock, uint32_t>(sP, n, E, m, (glabel_t*)L, tid,
+    const bool bad = solve_graph_lds<kBatchBlock, uint32_t, int32_t>(sP, n, E, (int32_t)m, (glabel_t*)L, tid,
                                                             s_q + (tid >> 6) * kLinkQueue, sym != 0);
     if (bad) atomicOr(&st->status, kStatusRange);
     if (!zr) {
@@ -696,11 +712,26 @@ static int batch_prepare(BatchScratch* bs, uint32_t G, const GraphDesc* descs,
         const int role = batch_role(descs[g], sc, lds.wave_cap);
         (role == kRoleMulti ? multi : role == kRoleWave ? wave : tile).push_back(g);
     }
-    auto larger = [&](uint32_t a, uint32_t b) {
-        return descs[a].m + (int64_t)descs[a].n > descs[b].m + (int64_t)descs[b].n;
+    // Largest first to within 1/16 of the size, by counting: the order only evens out
+    // the workgroups' finish, and a comparison sort of 4,096 graphs took longer than
+    // a tenth of the launch.
+    auto bucket = [&](uint32_t g) -> uint32_t {
+        const uint64_t size = (uint64_t)descs[g].m + descs[g].n;
+        if (size < 32) return (uint32_t)size;
+        const int top = 63 - __builtin_clzll(size);          // >= 5
+        return (uint32_t)(16 * (top - 3) + ((size >> (top - 4)) & 15));
     };
-    std::stable_sort(tile.begin(), tile.end(), larger);
-    std::stable_sort(wave.begin(), wave.end(), larger);
+    auto largest_first = [&](std::vector<uint32_t>& v) {
+        uint32_t at[16 * 64 + 1] = {};
+        for (uint32_t g : v) ++at[bucket(g)];
+        uint32_t run = 0;
+        for (int b = 16 * 64; b >= 0; --b) { const uint32_t c = at[b]; at[b] = run; run += c; }
+        std::vector<uint32_t> out(v.size());
+        for (uint32_t g : v) out[at[bucket(g)]++] = g;
+        v.swap(out);
+    };
+    largest_first(tile);
+    largest_first(wave);
     const BatchLayout l = batch_layout(G);
     char* h = bs->host;
     std::memset(h, 0, kTicketBytes);
