@@ -114,12 +114,22 @@ __global__ __launch_bounds__(kBlock) void k_zargmax(const uint32_t* keys, const 
                                                     uint64_t T, DevState* st) {
     __shared__ uint64_t s_best[kBlock / 64];
     uint64_t best = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < T;
-         i += (uint64_t)gridDim.x * kBlock) {
-        uint32_t id = keys ? ld_agent(&keys[i]) : (uint32_t)i;
-        uint32_t c = ld_agent(&counts[i]);
-        if (id != kEmpty || !keys) {
-            uint64_t s = pack_sel(c, id);
+    // kR slots in flight per thread and few blocks: each block ends in an atomic on
+    // the one word (1,024 blocks of one slot per thread: 14 us, 128 of eight: 5)
+    constexpr int kR = 8;
+    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i0 < T; i0 += kR * stride) {
+        uint32_t id[kR], c[kR];
+#pragma unroll
+        for (int r = 0; r < kR; ++r) {
+            const uint64_t i = i0 + r * stride;
+            id[r] = !keys ? (uint32_t)i : i < T ? ld_agent(&keys[i]) : kEmpty;
+            c[r] = i < T ? ld_agent(&counts[i]) : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < kR; ++r) {
+            if (id[r] == kEmpty && keys) continue;
+            const uint64_t s = pack_sel(c[r], id[r]);
             best = s > best ? s : best;
         }
     }
@@ -826,7 +836,7 @@ int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t f
         }
         k_degfill<<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(s->deg, n, s->st);
         if (m) k_degcount<<<grid_for(m, kBlock, kGridCap), kBlock, 0, stream>>>(edges, m, n, s->deg, s->st);
-        k_zargmax<<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(nullptr, s->deg, n, s->st);
+        k_zargmax<<<grid_for(n, 8 * kBlock, kZrGrid), kBlock, 0, stream>>>(nullptr, s->deg, n, s->st);
     } else {
         const uint64_t K = s->samples;
         const uint64_t cnt = sample_count(m, K);
@@ -835,8 +845,8 @@ int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t f
         if (cnt)
             k_zcount<<<grid_for(cnt, kBlock, 1024), kBlock, 0, stream>>>(
                 edges, m, K, cnt, n, s->hkeys, s->hcounts, s->table - 1, s->st);
-        k_zargmax<<<grid_for(s->table, kBlock, 1024), kBlock, 0, stream>>>(s->hkeys, s->hcounts,
-                                                                            s->table, s->st);
+        k_zargmax<<<grid_for(s->table, 8 * kBlock, 1024), kBlock, 0, stream>>>(s->hkeys, s->hcounts,
+                                                                                s->table, s->st);
     }
     k_zfinish<<<1, 64, 0, stream>>>(s->st, 0, 0);
     CCM_HIP(hipGetLastError());
