@@ -41,9 +41,9 @@ TRAFFIC = {
 }
 
 HOOK_KERNELS = {
-    "zroot": "cc_hook step: k_hook<ZR> on 1/1024 of the entries, k_t1_part, k_t1_tsum, k_t1_scan, "
-             "k_t1_bases, k_t2_bounds, k_t2_part, k_t3_regions, k_t3_offsets, k_t3_filter, k_t4_scan, "
-             "k_t4_hook",
+    "zroot": "cc_hook step: k_hook<ZR> on 1/1024 of the entries, k_find_giant, k_t1_part, k_t1_tsum, "
+             "k_t1_scan, k_t1_bases, k_t2_bounds, k_t2_part, k_t3_regions, k_t3_offsets, k_t3_filter, "
+             "k_t4_scan, k_t4_hook, and the gated launches that leave at once",
     "plain": "cc_hook step: k_t1_part, k_t1_tsum, k_t1_scan, k_t1_bases, k_t2_bounds, "
              "k_t2_hookplain",
 }
@@ -52,7 +52,7 @@ HOOK_KERNELS = {
 # The sources of the kernels of the timed hook step (every kernel of it, and
 # the header they share); the HBM traffic figure is reported only while these
 # hash to the value it was measured on.
-HOOK_SOURCES = ("cc_internal.h", "cc_kernels.hip", "cc_tiled.hip")
+HOOK_SOURCES = ("cc_internal.h", "cc_link.h", "cc_kernels.hip", "cc_tiled.hip", "cc_filter.hip")
 
 
 def kernel_sources_sha256():

@@ -573,3 +573,73 @@ def test_regrouped_planted_mistakes_are_caught(bug, n, z, edges):
         sh, got = regrouped_run(n, z, edges, random.Random(s), nwarm=1, nfilt=1, nsurv=1, bug=bug)
         caught |= not np.array_equal(got, want)
     assert caught, f"{bug}: not caught"
+
+
+# ---- hooks by the bitmap of a sampled component -------------------------------------
+#
+# A sample of the entries is hooked without the bitmap, the forest flattened, and
+# the bitmap set to one root's component: the zero root's, or on a plain solve that
+# of a root of the sampled forest, whose key then becomes the smallest. A marking
+# pass over a part of the entries and the full pass follow, by workgroups that each
+# know their copy of the bitmap and their own marks; the full pass hooks an entry
+# with neither endpoint marked in P where it is found. Where the device sees no giant
+# component, the direct hook takes the list instead, without the sampled entries.
+
+def mark_then_hook_thread(sh, entries, split, hook):
+    yield
+    seen = list(sh.bit)
+    for u, v in entries:
+        if u == v or (seen[u] and seen[v]):
+            continue
+        if seen[u] != seen[v]:
+            w = v if seen[u] else u
+            seen[w] = True
+            yield
+            sh.bit[w] = True
+        elif hook:
+            yield from survivor_thread(sh, [(u, v)], split)
+
+
+def by_bits_run(n, z, edges, rng, split, direct):
+    sh = Shared(n, z)
+    if z is not None:
+        initial_push(sh, edges)
+    stride = rng.randint(2, 4)
+    sample = edges[::stride]
+    run_threads([survivor_thread(sh, sample[i::2], False) for i in range(2)], rng)
+    if direct:
+        rest = [e for i, e in enumerate(edges) if i % stride]
+        run_threads([thread(sh, rest[i::2], split) for i in range(2)], rng)
+        if z is None:
+            return np.array([root(sh.P, v) for v in range(n)], np.uint32)
+    else:
+        sh.P = [root(sh.P, v) for v in range(n)]
+        if z is None:
+            sh.z = rng.choice(sh.P)             # any root of the forest will do
+        sh.bit = [sh.bit[v] or sh.bit[sh.P[v]] or sh.P[v] == sh.z for v in range(n)]
+        part = edges[:len(edges) // 2]
+        run_threads([mark_then_hook_thread(sh, part[i::2], split, False) for i in range(2)], rng)
+        run_threads([mark_then_hook_thread(sh, edges[i::3], split, True) for i in range(3)], rng)
+        for x in range(n):
+            if sh.P[x] != x:
+                assert key(sh.P[x], sh.z) < key(x, sh.z), "parent with a greater key"
+    order = list(range(n))
+    rng.shuffle(order)
+    return compress_resolve(sh, order)
+
+
+@pytest.mark.parametrize("seed", range(16))
+def test_sampled_component_bitmap(seed):
+    """Random multigraphs, plain and with a zero root, every phase under random
+    schedules, filtered and direct: the labels are the oracle's."""
+    rng = random.Random(4000 + seed)
+    for _ in range(40):
+        n = rng.randint(2, 10)
+        m = rng.randint(1, 18)
+        edges = [(rng.randrange(n), rng.randrange(n)) for _ in range(m)]
+        want = oracle.cc_labels(n, np.asarray(edges, np.uint32).reshape(-1, 2))
+        for z in (None, rng.randrange(n)):
+            for split in (True, False):
+                for direct in (False, True):
+                    got = by_bits_run(n, z, edges, rng, split, direct)
+                    assert np.array_equal(got, want), (n, z, split, direct, edges, got.tolist())
