@@ -98,7 +98,7 @@ __device__ __forceinline__ void wave_scan(const uint32_t* cnt, uint32_t* start, 
 }
 
 // ---- 1. level-1 partition by the first endpoint's slice -----------------------------
-template <typename T>
+template <int MAXS, typename T>
 __global__ __launch_bounds__(kPartBlock) void k_t1_part(const T edges,
                                                         uint64_t m, uint32_t n, int R,
                                                         uint64_t nch1, uint32_t* __restrict__ t1w,
@@ -108,10 +108,10 @@ __global__ __launch_bounds__(kPartBlock) void k_t1_part(const T edges,
                                                         DevState* st, uint32_t sym, Gate gate) {
     if (gated_off(gate)) return;
     __shared__ u32x2 stage[kC1];
-    __shared__ uint32_t hist[kMaxSlices + 1];
-    __shared__ uint32_t start[kMaxSlices + 1];
+    __shared__ uint32_t hist[MAXS + 1];
+    __shared__ uint32_t start[MAXS + 1];
     const uint64_t c = blockIdx.x;
-    for (int i = threadIdx.x; i <= kMaxSlices; i += kPartBlock) hist[i] = 0;
+    for (int i = threadIdx.x; i <= MAXS; i += kPartBlock) hist[i] = 0;
     __syncthreads();
     u32x2 e[kPartEPT];
     uint16_t rank[kPartEPT];
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t1_part(const T edges,
         if (live) rank[k] = (uint16_t)atomicAdd(&hist[e[k].x >> kSliceBits], 1u);
     }
     __syncthreads();
-    wave_scan<8>(hist, start, R);
+    wave_scan<MAXS / 64>(hist, start, R);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k)
@@ -305,6 +305,7 @@ constexpr int kWin2 = 256;   // level-1 chunks per gather window (owner index fi
 // hist zeroed beforehand) sorted by the second endpoint's slice through LDS and
 // written contiguously to out in the level-2 form, with the start of every
 // slice's run in run2T.
+template <int MAXS>
 __device__ __forceinline__ void t2_sort_write(const u32x2 (&e)[kPartEPT], uint32_t cnt, int R,
                                               uint32_t* hist, uint32_t* start, u32x2* stage,
                                               L2Buf out, uint16_t* __restrict__ run2T,
@@ -317,7 +318,7 @@ __device__ __forceinline__ void t2_sort_write(const u32x2 (&e)[kPartEPT], uint32
         if (i < cnt) rank[k] = (uint16_t)atomicAdd(&hist[e[k].y >> kSliceBits], 1u);
     }
     __syncthreads();
-    wave_scan<8>(hist, start, R);
+    wave_scan<MAXS / 64>(hist, start, R);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kPartEPT; ++k)
@@ -391,6 +392,9 @@ __device__ __forceinline__ uint32_t t2_gather(uint32_t g, const uint32_t* __rest
     return cnt;
 }
 
+// MAXS: the slices its tables hold, 256 or 512 (R-MAT-26, 130 slices: 3.68 ms with
+// tables for 512, 3.63 with 256).
+template <int MAXS>
 __global__ __launch_bounds__(kPartBlock) void k_t2_part(const uint32_t* __restrict__ t1w,
                                                         const uint16_t* __restrict__ t1h,
                                                         const uint16_t* __restrict__ segT,
@@ -405,17 +409,17 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_part(const uint32_t* __restri
     __shared__ uint8_t owner[kC2];
     __shared__ uint32_t s_pre[kWin2 + 1];
     __shared__ uint32_t s_seg[kWin2];
-    __shared__ uint32_t hist[kMaxSlices + 1];
-    __shared__ uint32_t start[kMaxSlices + 1];
+    __shared__ uint32_t hist[MAXS + 1];
+    __shared__ uint32_t start[MAXS + 1];
     const uint32_t g = blockIdx.x;
     if (g >= cbase[R]) return;                  // the grid is an upper bound
-    for (int i = threadIdx.x; i <= kMaxSlices; i += kPartBlock) hist[i] = 0;
+    for (int i = threadIdx.x; i <= MAXS; i += kPartBlock) hist[i] = 0;
     u32x2 e[kPartEPT];
     int a;
     uint64_t obase;
     const uint32_t cnt = t2_gather(g, t1w, t1h, segT, pre1, nch1, desc, owner, s_pre, s_seg, e, a,
                                    obase);
-    t2_sort_write(e, cnt, R, hist, start, stage, L2Buf{tmp2.w + obase, tmp2.h + obase}, run2T,
+    t2_sort_write<MAXS>(e, cnt, R, hist, start, stage, L2Buf{tmp2.w + obase, tmp2.h + obase}, run2T,
                   nch2, g);
 }
 
@@ -552,8 +556,8 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_csr(const uint64_t* __restric
     // area: they are read into registers before t2_sort_write first writes it
     // (after two barriers), so both fit with two workgroups per CU
     uint32_t* head = reinterpret_cast<uint32_t*>(stage);
-    __shared__ uint32_t hist[kMaxSlices + 1];
-    __shared__ uint32_t start[kMaxSlices + 1];
+    __shared__ uint32_t hist[kMaxSlicesOther + 1];
+    __shared__ uint32_t start[kMaxSlicesOther + 1];
     __shared__ uint32_t s_w[kPartBlock / 64];
     __shared__ int s_a;
     const uint32_t g = blockIdx.x;
@@ -567,7 +571,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_csr(const uint64_t* __restric
         }
         s_a = lo;
     }
-    for (int i = threadIdx.x; i <= kMaxSlices; i += kPartBlock) hist[i] = 0;
+    for (int i = threadIdx.x; i <= kMaxSlicesOther; i += kPartBlock) hist[i] = 0;
     for (int i = threadIdx.x; i < kC2; i += kPartBlock) head[i] = 0;
     __syncthreads();
     const int a = s_a;
@@ -658,7 +662,7 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_csr(const uint64_t* __restric
         e[k].y = vv;
     }
     if (bad) atomicOr(&st->status, kStatusRange);
-    t2_sort_write(e, cnt, R, hist, start, stage, L2Buf{tmp2.w + pos0, tmp2.h + pos0}, run2T, nch2,
+    t2_sort_write<kMaxSlicesOther>(e, cnt, R, hist, start, stage, L2Buf{tmp2.w + pos0, tmp2.h + pos0}, run2T, nch2,
                   g);
 }
 
@@ -1473,8 +1477,9 @@ static int level1(const TiledLayout& l, char* q, uint64_t n, uint64_t m, EdgeLis
     // every kernel below reads tables the previous one wrote: coherence points between
     if ((rc = cohere(stream))) return rc;
     with_coo(E, [&](auto e) {
-        k_t1_part<<<g1, kPartBlock, 0, stream>>>(e, m, (uint32_t)n, l.R, l.nch1, t1w, t1h, seg, cnt1, st,
-                                                 sym ? 1u : 0u, gate);
+        auto part = l.R <= kFewSlices ? &k_t1_part<kFewSlices, decltype(e)> : &k_t1_part<kMaxSlices, decltype(e)>;
+        part<<<g1, kPartBlock, 0, stream>>>(e, m, (uint32_t)n, l.R, l.nch1, t1w, t1h, seg, cnt1, st,
+                                            sym ? 1u : 0u, gate);
     });
     if ((rc = cohere(stream))) return rc;
     k_t1_tsum<<<R * ntile, kScanBlock, 0, stream>>>(cnt1, l.nch1, ntile, tsum, gate);
@@ -1565,7 +1570,8 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
     if ((rc = level1(l, q, n, m, E, s->st, sym, gate, stream))) return rc;
     auto* cbase = reinterpret_cast<uint32_t*>(q + l.cbase);
     auto* base2 = reinterpret_cast<uint64_t*>(q + l.base2);
-    k_t2_part<<<(uint32_t)l.nch2, kPartBlock, 0, stream>>>(
+    auto part2 = l.R <= kFewSlices ? &k_t2_part<kFewSlices> : &k_t2_part<kMaxSlices>;
+    part2<<<(uint32_t)l.nch2, kPartBlock, 0, stream>>>(
         reinterpret_cast<uint32_t*>(q + l.t1w), reinterpret_cast<uint16_t*>(q + l.t1h),
         reinterpret_cast<uint16_t*>(q + l.seg), reinterpret_cast<uint32_t*>(q + l.pre1), l.nch1, l.R,
         cbase, reinterpret_cast<uint32_t*>(q + l.desc), tmp2, run2, l.nch2, gate);
