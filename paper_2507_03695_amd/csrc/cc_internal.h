@@ -240,7 +240,7 @@ int slot_sync(Slot* s, hipStream_t stream);
 bool tiled_eligible(uint64_t n, uint64_t m, bool zr);
 // The filter over (first slice, second slice) tiles, both membership tests in
 // LDS: 0 = not for these sizes, else its partition passes (1 or 2).
-int filter_passes(uint64_t n, uint64_t m);
+int filter_passes(uint64_t n, uint64_t m, bool zr);
 uint64_t filter_scratch_bytes(uint64_t n, uint64_t m, int passes, bool bits, bool p32);
 uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m);
 // Size the slot's scratch for the filter (passes 0: only the arrays asked for):

@@ -1175,7 +1175,9 @@ __global__ __launch_bounds__(kPackBlock) void k_t4_scan(const uint32_t* __restri
 // Algorithm 3's hooking loop (keys of Formula 1 as an order, path splitting)
 // over the kept entries. Their bits are tested once more first: every
 // workgroup's marks are in the bitmap by now, and most entries were kept only
-// because their own workgroup had not seen them.
+// because their own workgroup had not seen them. Where no giant component was seen
+// the test drops little and is left out (zero root, ER n = 67 M, 60 M entries:
+// 6.1 ms with it, 5.5 without).
 constexpr int kHook4Block = 256;
 constexpr int kHook4EPT = (int)kItem / kHook4Block;
 constexpr int kHook4Grid = 2048;     // 8 workgroups per CU
@@ -1186,11 +1188,13 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
                                                          const uint32_t* __restrict__ cnt,
                                                          const uint32_t* __restrict__ ipref,
                                                          uint32_t nw, int nbg, uint32_t* P,
-                                                         uint32_t* zbits, DevState* st, Gate gate) {
+                                                         uint32_t* zbits, DevState* st, Gate again,
+                                                         Gate gate) {
     if (gated_off(gate)) return;
     __shared__ uint32_t s_w;
     const uint32_t z = ld_agent(&st->zroot);
     const uint32_t items = ld_agent(&ipref[nw]);
+    const bool test = !gated_off(again);
     for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
         __syncthreads();                       // s_w of the previous item consumed
         if (threadIdx.x == 0) {
@@ -1221,8 +1225,8 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
         uint32_t bu[kHook4EPT], bv[kHook4EPT];
 #pragma unroll
         for (int k = 0; k < kHook4EPT; ++k) {
-            bu[k] = ld_agent(&zbits[u[k] >> 5]);
-            bv[k] = ld_agent(&zbits[v[k] >> 5]);
+            bu[k] = test ? ld_agent(&zbits[u[k] >> 5]) : 0u;
+            bv[k] = test ? ld_agent(&zbits[v[k] >> 5]) : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kHook4EPT; ++k) {
@@ -1340,19 +1344,23 @@ bool tiled_eligible(uint64_t n, uint64_t m, bool zr) {
 }
 
 // The filter over tiles: 0 = not taken, 1 = one partition pass, 2 = two. Below one
-// entry per vertex most vertices are outside any giant component, and the direct
-// hook is faster (zero root, grid n = 33 M, 30 M entries: 2.2 ms against 3.0;
-// ER n = 30 M, 18 M entries: 2.6 against 2.5). Two passes start at the size their
-// fixed costs (16 launches) are worth; one pass was faster from 2^20 entries on
+// entry per vertex a plain solve's component is seldom worth it; with a zero root
+// two passes take such lists too, since a share of a skewed graph is one (a
+// twentieth of R-MAT-26, n = 71 M, 52 M entries: 1.4 ms against 2.7 direct; ER
+// n = 67 M, 60 M entries 7.6 and 8.6, pieces of a path 6.0 and 3.4). A plain solve
+// takes two passes from 5/2 entries per vertex where it has the buckets too (ER
+// n = 67 M, 134 M entries 10.1 ms against 9.3 by buckets, 200 M 10.5 and 11.9).
+// Two passes start at the size their fixed costs (16 launches) are worth; one pass was faster from 2^20 entries on
 // (R-MAT n = 3 M, 12 M entries: 918 us direct, 314 here). Up to 512 slices: a
 // sixteenth of R-MAT-28 (n = 2^28, 2^28 entries), 10.0 ms direct, 7.1 here (plain
 // 13.5 and 6.6); beyond, a tile holds fewer entries than its bitmaps words.
-int filter_passes(uint64_t n, uint64_t m) {
+int filter_passes(uint64_t n, uint64_t m, bool zr) {
     const uint64_t R = (n + (1ull << kSliceBits) - 1) >> kSliceBits;
     if (n <= lds_bits_max_n() || R > (uint64_t)kMaxSlices || m >= (1ull << 32)) return 0;
-    if (m < n) return 0;
+    if (m < n && (!zr || R <= (uint64_t)kMaxOnePass || R > (uint64_t)kMaxSlicesOther)) return 0;
     // (below 2^31: a tile's width in the filter's index space exceeds its entries)
     if (R <= (uint64_t)kMaxOnePass && m < (1ull << 31)) return m >= (1ull << 20) ? 1 : 0;
+    if (!zr && R <= (uint64_t)kMaxSlicesOther && 2 * m < 5 * n) return 0;
     return m >= (1ull << 24) ? 2 : 0;
 }
 
@@ -1514,7 +1522,7 @@ int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uin
 static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_t* base2,
                        uint32_t* cbase, uint32_t* sw, uint16_t* sh, uint64_t* wgoff,
                        uint32_t* wgcnt, uint32_t* ipref, uint32_t* P, uint32_t* zbits,
-                       uint64_t words, DevState* st, Gate gate, hipStream_t stream) {
+                       uint64_t words, DevState* st, Gate again, Gate gate, hipStream_t stream) {
     const uint32_t nbg = (uint32_t)((R + b_per_block(R) - 1) / b_per_block(R));
     const uint32_t nwg = (uint32_t)R * nbg;
     int rc;
@@ -1529,7 +1537,7 @@ static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_
     k_t4_scan<<<1, kPackBlock, 0, stream>>>(wgcnt, nwg, ipref, gate);
     if ((rc = cohere(stream))) return rc;
     k_t4_hook<<<kHook4Grid, kHook4Block, 0, stream>>>(sw, sh, wgoff, wgcnt, ipref, nwg, (int)nbg, P,
-                                                      zbits, st, gate);
+                                                      zbits, st, again, gate);
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -1581,7 +1589,7 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
     return filter_runs(l.R, l.nch2, tmp2, run2, base2, cbase, reinterpret_cast<uint32_t*>(q + l.t1w),
                        reinterpret_cast<uint16_t*>(q + l.t1h), reinterpret_cast<uint64_t*>(q + l.wgoff),
                        reinterpret_cast<uint32_t*>(q + l.wgcnt), reinterpret_cast<uint32_t*>(q + l.ipref),
-                       P, zbits, words, s->st, gate, stream);
+                       P, zbits, words, s->st, Gate{&s->st->giant, 1u}, gate, stream);
 }
 
 // The regrouped zero-root hook on CSR input (steps 4-5 on adj's own buckets).
@@ -1621,7 +1629,7 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
                                                        run2, nch2, s->st, sym ? 1u : 0u);
     if ((rc = cohere(stream))) return rc;
     return filter_runs(R, nch2, tmp2, run2, base2, cbase, sw, sh, wgoff, wgcnt, ipref, P, s->zbits,
-                       (n + 31) / 32, s->st, Gate{}, stream);
+                       (n + 31) / 32, s->st, Gate{}, Gate{}, stream);
 }
 
 }  // namespace ccm

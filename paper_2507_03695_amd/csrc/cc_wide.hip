@@ -165,7 +165,7 @@ int run_solve_w(Slot* s, uint64_t n, uint64_t m, const uint64_t* edges, uint64_t
     int rc;
     if (n < kEmpty && !(flags & CC_F_NO_SPLIT)) {
         // R-MAT n = 2^23, 2^27 entries: 4.56 ms in 64 bits, 1.25 ms so
-        const int passes = filter_passes(n, m);
+        const int passes = m < n ? 0 : filter_passes(n, m, true);
         FilterScratch fs{};
         if ((passes || lds_eligible(n, m)) &&
             !filter_scratch(s, n, m, passes, passes != 0, true, stream, &fs)) {

@@ -267,3 +267,18 @@ def test_rows(ctx, kind, n, m):
     bad[n // 2] = m + 5
     ctx.solve_csr_async(bad, adj, n, L, flags=cc.F_ZROOT)
     assert ctx.sync() == cc.CC_EINVAL
+
+
+@pytest.mark.parametrize("kind", ["er", "rmat", "paths", "rows"])
+@pytest.mark.parametrize("n,m", [(36 * SLICE + 7, (1 << 24) + 77), (13_421_861, (1 << 24) + 77),
+                                 (13_421_834, (1 << 24) + 77), (22 * SLICE + 5, 28_835_853),
+                                 (22 * SLICE + 5, 28_835_852)])
+def test_two_passes_by_entries_per_vertex(ctx, kind, n, m):
+    """Fewer entries than vertices, each side of 5/4 (zero root) and of 5/2 (plain)."""
+    e = graph(kind, n, m, n + m)
+    want = oracle.cc_labels(n, e)
+    ed = to_dev(e)
+    log(f"{kind} n={n} m={m}")
+    for name, fl in [("plain", 0), ("zroot", cc.F_ZROOT)]:
+        assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"{kind} n={n} m={m} [{name}]")
+    assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"{kind} n={n} m={m} [steps]")
