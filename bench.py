@@ -36,8 +36,8 @@ PEAK_HBM_GBS = 8000.0
 # each counter scaled by what it reads for a 4 GiB device copy. Keyed by
 # (workload, variant); valid only for the kernel sources they were taken on.
 TRAFFIC = {
-    ("rmat26", "zroot"): {"bytes": 47080770588,
-                          "src_sha256": "dae9ed1e1f54392e6ab0aee0a8a33220fa254be2cd74d668aa6ef1de2642a650"},
+    ("rmat26", "zroot"): {"bytes": 47065756685,
+                          "src_sha256": "4ea6f64bbddbe1e0028426c37be55794a159dc522e21c1cf68ded0243d2ad065"},
 }
 
 HOOK_KERNELS = {
