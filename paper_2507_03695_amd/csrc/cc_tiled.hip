@@ -1061,6 +1061,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                         }
                         at = j + s_off[t0];
                     }
+                    at = h ? at : __builtin_amdgcn_readfirstlane(at);   // lane 0 has an entry
                     const uint32_t w = srcw[at], h8 = srch[at];
                     const u32x2 x = {w & kLoMask, (w >> kSliceBits) | (h8 << (32 - kSliceBits))};
                     const uint32_t both =
@@ -1076,17 +1077,22 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
             // The window's entries form one index space [0, total); each wave
             // takes ranges of kRange consecutive indices. Register k holds index
             // j0 + 64k + lane; right after it is tested it is reloaded with index
-            // jn + 64k + lane of the next range (index 0 past the end), so the
-            // next range's loads are in flight meanwhile.
+            // jn + 64k + lane of the next range, so the next range's loads are in
+            // flight meanwhile. Past the end a lane reads the wave's first entry: a
+            // slot that no entry was written to (a chunk's first one may be such, when
+            // all of its entries were dropped) can hold endpoints beyond a slice, whose
+            // bit test would read past the slice's words.
             uint32_t j0 = first + (uint32_t)wave * kRange;
             if (j0 >= total) continue;
             uint32_t ew[kRunsInFlight], eh[kRunsInFlight];
             uint32_t t = __builtin_amdgcn_readfirstlane(t3_find_run(s_pre, nw, j0, lane));
+            uint32_t safe = 0;                               // the entry j0 (j0 < total)
 #pragma unroll
             for (int k = 0; k < kRunsInFlight; ++k) {
                 const uint32_t jb = j0 + (uint32_t)k * 64, j = jb + (uint32_t)lane;
                 const uint32_t off = t3_offset(s_pre, s_off, nw, t, jb, j);
-                const uint32_t at = j < total ? j + off : 0u;
+                if (k == 0) safe = __builtin_amdgcn_readfirstlane(j + off);
+                const uint32_t at = j < total ? j + off : safe;
                 ew[k] = __builtin_nontemporal_load(srcw + at);
                 eh[k] = __builtin_nontemporal_load(srch + at);
             }
@@ -1100,7 +1106,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                     {
                         const uint32_t jb = jn + (uint32_t)k * 64, j = jb + (uint32_t)lane;
                         const uint32_t off = more ? t3_offset(s_pre, s_off, nw, tn, jb, j) : 0u;
-                        const uint32_t at = more && j < total ? j + off : 0u;
+                        const uint32_t at = more && j < total ? j + off : safe;
                         ew[k] = __builtin_nontemporal_load(srcw + at);
                         eh[k] = __builtin_nontemporal_load(srch + at);
                     }

@@ -282,3 +282,38 @@ def test_two_passes_by_entries_per_vertex(ctx, kind, n, m):
     for name, fl in [("plain", 0), ("zroot", cc.F_ZROOT)]:
         assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"{kind} n={n} m={m} [{name}]")
     assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"{kind} n={n} m={m} [steps]")
+
+
+def rows_of(e, n):
+    """(offsets, adj) on the device of the rows (u, v) of a list."""
+    e = e[np.argsort(e[:, 0], kind="stable")]
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(e[:, 0], minlength=n), out=off[1:])
+    return torch.from_numpy(off).cuda(), to_dev(np.stack([e[:, 1], e[:, 1]], 1))[:, 0].contiguous()
+
+
+@pytest.mark.parametrize("n,m", [(3 * SLICE + 5, 3_000_000), (8 * SLICE + 40, 12_000_000),
+                                 (23 * SLICE, (1 << 24) + 8192)])
+def test_chunks_without_an_entry(n, m):
+    """The first chunks of 8192 entries (and some later ones) hold none that is kept:
+    self-loops, or u > v on a symmetric list. Their slots in the tiles are whatever the
+    scratch held before, here another list's entries."""
+    c = cc.Context(zroot_samples=4096)
+    c.solve(to_dev(graphgen.er(n, m + 70_000, 31)), n)
+    e = graphgen.er(n, m, 32)
+    loops = e.copy()
+    loops[:20_000] = 0                             # row 0 of the rows begins with them too
+    for a in (0, 8192, 40 * 8192, m // 8192 * 8192):
+        loops[a:a + 8192, 1] = loops[a:a + 8192, 0]
+    half = np.sort(e[:m // 2], axis=1)
+    sym = np.ascontiguousarray(np.concatenate([half[:, ::-1], half]))   # every u > v first
+    for name, x, fl in (("loops", loops, 0), ("symmetric", sym, cc.F_SYMMETRIC)):
+        want = oracle.cc_labels(n, x)
+        ed = to_dev(x)
+        off, adj = rows_of(x, n)
+        for zr in (0, cc.F_ZROOT):
+            log(f"{name} n={n} m={m} zr={zr}")
+            assert_same_labels(to_host_u32(c.solve(ed, n, flags=fl | zr)), want, f"{name} n={n} {zr}")
+            assert_same_labels(to_host_u32(c.solve_csr(off, adj, n, flags=fl | zr)), want, f"{name} rows n={n} {zr}")
+        assert_same_labels(to_host_u32(by_steps(c, ed, n, flags=fl)), want, f"{name} n={n} steps")
+    c.close()
