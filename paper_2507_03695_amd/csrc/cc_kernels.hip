@@ -1319,15 +1319,20 @@ int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* 
         s->cur_n = n;
         s->zr_ready = flags & CC_F_ZROOT;
         if (s->zr_ready && (rc = zbits_grow(s, n, stream))) return rc;
+        if ((rc = cohere(stream))) return rc;        // before the entries are read
         if ((rc = run_solve_small(s, n, m, edges, L, flags, hint, stream))) return rc;
         return cohere(stream);
     }
     if ((rc = run_init(s, n, L, stream))) return rc;
+    // One coherence point before anything reads the entries (the zero root's sample
+    // and push read them too) or P. What those two steps write of P and the bitmap
+    // goes to memory, and a hook may read either as it was before them: an older
+    // parent is an ancestor, a clear bit only sends an entry to P.
+    if ((rc = cohere(stream))) return rc;
     if (flags & CC_F_ZROOT) {
         if ((rc = run_zroot(s, n, m, edges, flags, hint, stream))) return rc;
         if ((rc = run_push(s, n, m, edges, L, stream))) return rc;
     }
-    if ((rc = cohere(stream))) return rc;
     if (!(flags & (CC_F_ZROOT | CC_F_NO_SPLIT))) {
         const EdgeList E{edges, false};
         FilterScratch fs;

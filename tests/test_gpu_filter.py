@@ -317,3 +317,25 @@ def test_chunks_without_an_entry(n, m):
             assert_same_labels(to_host_u32(c.solve_csr(off, adj, n, flags=fl | zr)), want, f"{name} rows n={n} {zr}")
         assert_same_labels(to_host_u32(by_steps(c, ed, n, flags=fl)), want, f"{name} n={n} steps")
     c.close()
+
+
+@pytest.mark.parametrize("n,m", [(900, 4000), (16_384, 60_000), (40_000, 300_000), (400_000, 900_000)])
+def test_entries_rewritten_by_the_kernel_before(n, m):
+    """Solves queued one after another on one buffer that a kernel rewrites in between,
+    with no wait: each reads the entries written last (every path reads them only after
+    a coherence point, also the small one-launch solve and the zero root's sample)."""
+    c = cc.Context()
+    lists = [graphgen.er(n, m, 50 + k) for k in range(4)]
+    lists[2][:, 1] = lists[2][:, 0]                # nothing joined: any old entry would show
+    wants = [oracle.cc_labels(n, x) for x in lists]
+    devs = [to_dev(x) for x in lists]
+    buf = torch.empty_like(devs[0])
+    out = torch.empty((40, n), dtype=torch.int32, device="cuda")
+    for fl in (0, cc.F_ZROOT):
+        for i in range(len(out)):
+            buf.copy_(devs[i % 4])
+            c.solve_async(buf, n, out[i], flags=fl)
+        assert c.sync() == cc.CC_OK
+        for i in range(len(out)):
+            assert_same_labels(to_host_u32(out[i]), wants[i % 4], f"n={n} m={m} flags={fl} call {i}")
+    c.close()
