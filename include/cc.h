@@ -138,6 +138,11 @@ typedef struct cc_ctx_opts {
    pinned host staging, and grows on demand what larger solves need: the
    zero-root membership bitmap (n/8 bytes), the buffers of the regrouped hooks
    (5 to 11 bytes per entry, 6 per entry more with CSR input), the CSR tile tables and the batch work list.
+   A buffer that work captured into a graph has used is kept until cc_destroy, also
+   when a larger solve outgrows it, so such a graph may be replayed as long as the
+   context lives. Under capture nothing grows: a solve whose regrouped hook would
+   have to takes the direct one, and one whose zero-root bitmap or degree counts
+   would have to fails with CC_ENOMEM (solve once before capturing).
    opts may be NULL (defaults). */
 int cc_create(cc_ctx** out, const cc_ctx_opts* opts);
 /* Release a context and everything it owns. Waits for its work to finish. */

@@ -110,9 +110,24 @@ void slot_destroy(Slot* s) {
     if (s->zbits) (void)hipFree(s->zbits);
     if (s->csr_tiles) (void)hipFree(s->csr_tiles);
     tiled_free(&s->tiled);
+    for (void* p : s->kept) (void)hipFree(p);
     batch_scratch_free(&s->batch);
     if (s->host_status) (void)hipHostFree(s->host_status);
     *s = Slot{};
+}
+
+bool stream_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+int slot_outgrow(Slot* s, void* buf, bool* captured) {
+    if (buf && *captured) s->kept.push_back(buf);
+    else if (buf) CCM_HIP(hipFree(buf));
+    *captured = false;
+    return CC_OK;
 }
 
 __global__ void k_status_take(DevState* st, uint32_t* out) {

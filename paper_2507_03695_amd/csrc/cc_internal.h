@@ -85,10 +85,11 @@ struct BatchScratch {
 // on one wavefront, the rest on one workgroup each.
 typedef cc_batch_sched BatchSched;
 
-// Scratch of the tiled zero-root hook (one block, grown on demand).
+// Scratch of the regrouped hooks (one block, grown on demand).
 struct TiledScratch {
     char* buf = nullptr;
     uint64_t cap = 0;
+    bool captured = false;     // see Slot::kept
 };
 
 // Scratch owned by one slot.
@@ -103,11 +104,17 @@ struct Slot {
     uint32_t samples = 0;          // K
     uint32_t* deg = nullptr;       // device, exact-degree counts (grown on demand)
     uint64_t deg_cap = 0;
+    bool deg_captured = false;
     uint32_t* host_status = nullptr;  // pinned host block of 64 bytes (status word, read-backs)
     BatchScratch batch;
     // Zero-root membership bitmap: bit x set => x is in the zero root's tree.
     uint32_t* zbits = nullptr;     // device, ceil(n/32) words (grown on demand)
     uint64_t zbits_cap = 0;        // words
+    bool zbits_captured = false;
+    // Buffers that a larger solve outgrew after work captured into a graph had used
+    // them: a replay still reads and writes them, so they are freed with the slot.
+    // (A buffer that no capture has used is freed when it is outgrown.)
+    std::vector<void*> kept;
     // Bitmap of a plain whole solve's giant component (cc_filter.hip), for arrays
     // of at most lds_bits_max_n() vertices.
     uint32_t* gbits = nullptr;
@@ -129,6 +136,14 @@ struct Slot {
 
 int slot_create(Slot* s, int device, uint32_t samples);
 void slot_destroy(Slot* s);
+// Whether work queued on `stream` is being captured (also where that cannot be told).
+bool stream_capturing(hipStream_t stream);
+// A grown buffer is about to be used on `stream`.
+inline void note_capture(bool* captured, hipStream_t stream) {
+    if (!*captured) *captured = stream_capturing(stream);
+}
+// A buffer of the slot makes room for a larger one: freed, or kept (Slot::kept).
+int slot_outgrow(Slot* s, void* buf, bool* captured);
 
 // A graph's rows as entries (u, adj[i]), off[u] <= i < off[u + 1]; tstart[t] is the
 // row of position t * kCsrTile.
@@ -244,8 +259,9 @@ int filter_passes(uint64_t n, uint64_t m, bool zr);
 uint64_t filter_scratch_bytes(uint64_t n, uint64_t m, int passes, bool bits, bool p32);
 uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m);
 // Size the slot's scratch for the filter (passes 0: only the arrays asked for):
-// with a bitmap of its own (bits), with a 32-bit parent array (p32). CC_ENOMEM
-// where it cannot grow now (fixed scratch, capture, no memory).
+// with a bitmap of its own (bits), with a 32-bit parent array (p32). Not CC_OK
+// where it cannot grow now: kScratchCapture under capture, else CC_ENOMEM.
+constexpr int kScratchCapture = 1;
 struct FilterScratch {
     char* buf;
     uint32_t* bits;
@@ -257,7 +273,8 @@ int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool 
 // entry tested against zbits, the rest hooked in P (key order of DevState::zroot).
 int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, int passes,
                bool bits, bool p32, bool sym, Gate gate, hipStream_t stream);
-// The plain hook (key = ID) over first-endpoint buckets.
+// The plain hook (key = ID) over first-endpoint buckets. kScratchCapture (nothing
+// queued) where its scratch would have to grow under capture.
 int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, bool sym,
                      hipStream_t stream);
 // Device bytes a whole-path solve (run_solve) grows in its slot for these

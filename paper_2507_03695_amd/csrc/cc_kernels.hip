@@ -789,8 +789,10 @@ static int zbits_grow(Slot* s, uint64_t n, hipStream_t stream) {
     const uint64_t words = (n + 31) / 32;
     if (s->zbits_cap < words) {
         if (s->no_grow) return fail(CC_ENOMEM, "zero-root bitmap exceeds the fixed scratch");
+        if (stream_capturing(stream)) return fail(CC_ENOMEM, "zero-root bitmap cannot grow under capture");
         CCM_HIP(hipStreamSynchronize(stream));
-        if (s->zbits) CCM_HIP(hipFree(s->zbits));
+        int rc = slot_outgrow(s, s->zbits, &s->zbits_captured);
+        if (rc) return rc;
         s->zbits = nullptr;
         s->zbits_cap = 0;
         if (hipMalloc(&s->zbits, words * sizeof(uint32_t)) != hipSuccess) {
@@ -799,6 +801,8 @@ static int zbits_grow(Slot* s, uint64_t n, hipStream_t stream) {
             return fail(CC_ENOMEM, "zero-root bitmap allocation failed");
         }
         s->zbits_cap = words;
+    } else if (!s->no_grow) {
+        note_capture(&s->zbits_captured, stream);
     }
     return CC_OK;
 }
@@ -824,7 +828,10 @@ int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t f
         if (s->deg_cap < n && s->no_grow)
             return fail(CC_ENOMEM, "exact-degree counts need memory beyond the fixed scratch");
         if (s->deg_cap < n) {
-            if (s->deg) CCM_HIP(hipFree(s->deg));
+            if (stream_capturing(stream))
+                return fail(CC_ENOMEM, "exact-degree counts cannot grow under capture");
+            int rc = slot_outgrow(s, s->deg, &s->deg_captured);
+            if (rc) return rc;
             s->deg = nullptr;
             s->deg_cap = 0;
             if (hipMalloc(&s->deg, n * sizeof(uint32_t)) != hipSuccess) {
@@ -833,6 +840,8 @@ int run_zroot(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t f
                 return fail(CC_ENOMEM, "exact-degree scratch allocation failed");
             }
             s->deg_cap = n;
+        } else if (!s->no_grow) {
+            note_capture(&s->deg_captured, stream);
         }
         k_degfill<<<grid_for(n, kBlock, kGridCap), kBlock, 0, stream>>>(s->deg, n, s->st);
         if (m) k_degcount<<<grid_for(m, kBlock, kGridCap), kBlock, 0, stream>>>(edges, m, n, s->deg, s->st);
@@ -983,8 +992,10 @@ int run_hook(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
     if (zr && (!s->zr_ready || s->cur_n != n))
         return fail(CC_EINVAL, "a CC_F_ZROOT hook needs cc_init then cc_zroot on the same n");
     const bool regroup = !(flags & (CC_F_NO_SPLIT | CC_F_NO_TILE)) && !s->no_tiled;
-    if (!zr && regroup && tiled_eligible(n, m, false))
-        return run_hook_buckets(s, n, m, edges, P, sym != 0, stream);
+    if (!zr && regroup && tiled_eligible(n, m, false)) {
+        const int rc = run_hook_buckets(s, n, m, edges, P, sym != 0, stream);
+        if (rc != kScratchCapture) return rc;
+    }
     const bool split = split_walks(flags, n);
     const uint32_t n32 = (uint32_t)n;
     uint32_t* zb = s->zbits;
@@ -997,7 +1008,8 @@ int run_hook(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
         FilterScratch fs{};
         int rc = passes ? filter_scratch(s, n, m, passes, false, false, stream, &fs) : CC_OK;
         if (!rc) return hook_by_bits(s, n, m, E, P, zb, passes, true, false, false, flags, stream);
-        if (tiled_eligible(n, m, true)) return rc;
+        if (rc == CC_ENOMEM && tiled_eligible(n, m, true)) return rc;
+        if (rc < 0 && rc != CC_ENOMEM) return rc;
     }
     if (!zr && !(flags & CC_F_NO_SPLIT) && hook_in_two_parts(n, m, split)) {
         // in two parts (ER n = 2^16 with 2^20 entries, whole solve: 0.150 -> 0.115 ms)

@@ -1433,32 +1433,29 @@ uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m) {
 }
 
 static int grow(Slot* s, uint64_t bytes, hipStream_t stream) {
-    if (s->tiled.cap >= bytes) return CC_OK;
-    if (s->no_grow) return fail(CC_ENOMEM, "regrouped-hook scratch exceeds the fixed scratch");
-    CCM_HIP(hipStreamSynchronize(stream));
-    if (s->tiled.buf) CCM_HIP(hipFree(s->tiled.buf));
-    s->tiled.buf = nullptr;
-    s->tiled.cap = 0;
-    if (hipMalloc(&s->tiled.buf, bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    if (s->tiled.cap < bytes) {
+        if (s->no_grow) return fail(CC_ENOMEM, "regrouped-hook scratch exceeds the fixed scratch");
+        if (stream_capturing(stream)) return kScratchCapture;   // growing waits for the stream
+        CCM_HIP(hipStreamSynchronize(stream));
+        int rc = slot_outgrow(s, s->tiled.buf, &s->tiled.captured);
+        if (rc) return rc;
         s->tiled.buf = nullptr;
-        return fail(CC_ENOMEM, "tiled hook scratch allocation failed");
+        s->tiled.cap = 0;
+        if (hipMalloc(&s->tiled.buf, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            s->tiled.buf = nullptr;
+            return fail(CC_ENOMEM, "tiled hook scratch allocation failed");
+        }
+        s->tiled.cap = bytes;
+    } else if (!s->no_grow) {
+        note_capture(&s->tiled.captured, stream);
     }
-    s->tiled.cap = bytes;
     return CC_OK;
 }
 
 int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool p32,
                    hipStream_t stream, FilterScratch* out) {
     const TiledLayout l = tiled_layout(n, m, passes, bits, p32);
-    if (s->tiled.cap < l.total && !s->no_grow) {
-        // growing waits for the stream, which a capture does not allow
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return fail(CC_ENOMEM, "regrouped-hook scratch cannot grow under capture");
-        }
-    }
     int rc = grow(s, l.total, stream);
     if (rc) return rc;
     out->buf = s->tiled.buf;
@@ -1612,6 +1609,7 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
     const uint64_t b_wgoff = al(8 * (nwg + 1)), b_wgcnt = al(4 * nwg), b_ipref = al(4 * (nwg + 1));
     int rc = grow(s, b_sw + b_sh + b_tmp2 + b_base2 + b_cbase + b_cfirst + b_run2 + b_wgoff + b_wgcnt +
                          b_ipref, stream);
+    if (rc == kScratchCapture) return fail(CC_ENOMEM, "regrouped-hook scratch cannot grow under capture");
     if (rc) return rc;
     char* q = s->tiled.buf;
     uint32_t* sw = reinterpret_cast<uint32_t*>(q); q += b_sw;

@@ -339,3 +339,86 @@ def test_entries_rewritten_by_the_kernel_before(n, m):
         for i in range(len(out)):
             assert_same_labels(to_host_u32(out[i]), wants[i % 4], f"n={n} m={m} flags={fl} call {i}")
     c.close()
+
+
+def test_captured_solves_keep_their_scratch():
+    """A solve captured on a warm context holds pointers into its scratch: larger solves
+    that outgrow the scratch (and the bitmap) leave the old blocks to it until the
+    context is destroyed. Replayed between eager solves."""
+    n, m = 3 * SLICE, 24_000_000
+    e = graphgen.er(n, m, 61)
+    want = oracle.cc_labels(n, e)
+    big_n, big_m = 5 * SLICE, 40_000_000
+    big = to_dev(graphgen.er(big_n, big_m, 62))
+    ed = to_dev(e)
+    c = cc.Context(zroot_samples=4096)
+    for fl in (0, cc.F_ZROOT):
+        c.solve(ed, n, flags=fl)
+    L = torch.empty(n, dtype=torch.int32, device="cuda")
+    Lz = torch.empty(n, dtype=torch.int32, device="cuda")
+    Lb = torch.empty(big_n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        c.solve_async(ed, n, L)
+        c.solve_async(ed, n, Lz, flags=cc.F_ZROOT)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    c.solve_async(big, big_n, Lb)
+    c.solve_async(big, big_n, Lb, flags=cc.F_ZROOT)
+    assert c.sync() == cc.CC_OK
+    # the outgrown block is still there: all of the larger list's 5 bytes per entry are
+    # new, not only what they exceed the captured list's by (the runtime's own buffers
+    # come and go by a few MB, hence halfway between)
+    assert free - torch.cuda.mem_get_info()[0] >= 5 * big_m - 5 * m // 2, "the captured scratch was given back"
+    for rep in range(3):
+        L.fill_(-1)
+        Lz.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert_same_labels(to_host_u32(L), want, f"replay {rep}")
+        assert_same_labels(to_host_u32(Lz), want, f"replay {rep} [zroot]")
+        c.solve_async(big, big_n, Lb, flags=cc.F_ZROOT if rep else 0)
+    assert c.sync() == cc.CC_OK
+    del g
+    c.close()
+
+
+def test_capture_that_would_grow_the_scratch():
+    """At the sizes of the regrouped hooks a capture on a cold context takes the direct
+    hook, plain and with a zero root (whose bitmap is there), and the steps too."""
+    n, m = 8 * SLICE, (1 << 24) + 5
+    e = graphgen.er(n, m, 63)
+    want = oracle.cc_labels(n, e)
+    ed = to_dev(e)
+    L = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(3)]
+    c = cc.Context(zroot_samples=4096)
+    c.solve(ed[:1000], n, flags=cc.F_ZROOT)         # the bitmap, no tiles
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        c.solve_async(ed, n, L[0])
+        c.solve_async(ed, n, L[1], flags=cc.F_ZROOT)
+        c.init(n, L[2])
+        c.hook(ed, n, L[2])
+        c.compress(n, L[2])
+    for rep in range(3):
+        for x in L:
+            x.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        for k, x in enumerate(L):
+            assert_same_labels(to_host_u32(x), want, f"replay {rep} [{k}]")
+    del g
+    c.close()
+    cold = cc.Context()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        cold.solve_async(ed, n, L[0])
+        with pytest.raises(cc.CCError):              # no bitmap to capture with
+            cold.solve_async(ed, n, L[1], flags=cc.F_ZROOT)
+    g.replay()
+    torch.cuda.synchronize()
+    assert_same_labels(to_host_u32(L[0]), want, "after a refused call")
+    del g
+    cold.close()
