@@ -260,12 +260,15 @@ uint64_t filter_scratch_bytes(uint64_t n, uint64_t m, int passes, bool bits, boo
 uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m);
 // Size the slot's scratch for the filter (passes 0: only the arrays asked for):
 // with a bitmap of its own (bits), with a 32-bit parent array (p32). Not CC_OK
-// where it cannot grow now: kScratchCapture under capture, else CC_ENOMEM.
+// where it cannot grow now: kScratchCapture under capture, else CC_ENOMEM. Most
+// callers go on by another hook then, so the failure's text is left to the one that
+// does not: `why`.
 constexpr int kScratchCapture = 1;
 struct FilterScratch {
     char* buf;
     uint32_t* bits;
     uint32_t* p32;
+    const char* why;
 };
 int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool p32,
                    hipStream_t stream, FilterScratch* out);

@@ -1008,7 +1008,7 @@ int run_hook(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
         FilterScratch fs{};
         int rc = passes ? filter_scratch(s, n, m, passes, false, false, stream, &fs) : CC_OK;
         if (!rc) return hook_by_bits(s, n, m, E, P, zb, passes, true, false, false, flags, stream);
-        if (rc == CC_ENOMEM && tiled_eligible(n, m, true)) return rc;
+        if (rc == CC_ENOMEM && tiled_eligible(n, m, true)) return fail(rc, fs.why);
         if (rc < 0 && rc != CC_ENOMEM) return rc;
     }
     if (!zr && !(flags & CC_F_NO_SPLIT) && hook_in_two_parts(n, m, split)) {

@@ -1432,10 +1432,17 @@ uint64_t bucket_scratch_bytes(uint64_t n, uint64_t m) {
     return tiled_layout(n, m, 3, false, false).total;
 }
 
-static int grow(Slot* s, uint64_t bytes, hipStream_t stream) {
+static int grow(Slot* s, uint64_t bytes, hipStream_t stream, const char** why) {
     if (s->tiled.cap < bytes) {
-        if (s->no_grow) return fail(CC_ENOMEM, "regrouped-hook scratch exceeds the fixed scratch");
-        if (stream_capturing(stream)) return kScratchCapture;   // growing waits for the stream
+        if (s->no_grow) {
+            *why = "regrouped-hook scratch exceeds the fixed scratch";
+            return CC_ENOMEM;
+        }
+        if (stream_capturing(stream)) {          // growing waits for the stream
+            *why = "regrouped-hook scratch cannot grow under capture";
+            return kScratchCapture;
+        }
+        *why = "tiled hook scratch allocation failed";
         CCM_HIP(hipStreamSynchronize(stream));
         int rc = slot_outgrow(s, s->tiled.buf, &s->tiled.captured);
         if (rc) return rc;
@@ -1444,7 +1451,7 @@ static int grow(Slot* s, uint64_t bytes, hipStream_t stream) {
         if (hipMalloc(&s->tiled.buf, bytes) != hipSuccess) {
             (void)hipGetLastError();
             s->tiled.buf = nullptr;
-            return fail(CC_ENOMEM, "tiled hook scratch allocation failed");
+            return CC_ENOMEM;
         }
         s->tiled.cap = bytes;
     } else if (!s->no_grow) {
@@ -1456,7 +1463,7 @@ static int grow(Slot* s, uint64_t bytes, hipStream_t stream) {
 int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool p32,
                    hipStream_t stream, FilterScratch* out) {
     const TiledLayout l = tiled_layout(n, m, passes, bits, p32);
-    int rc = grow(s, l.total, stream);
+    int rc = grow(s, l.total, stream, &out->why);
     if (rc) return rc;
     out->buf = s->tiled.buf;
     out->bits = bits ? reinterpret_cast<uint32_t*>(s->tiled.buf + l.bits) : nullptr;
@@ -1508,7 +1515,9 @@ static int level1(const TiledLayout& l, char* q, uint64_t n, uint64_t m, EdgeLis
 int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, bool sym,
                      hipStream_t stream) {
     const TiledLayout l = tiled_layout(n, m, 3, false, false);
-    int rc = grow(s, l.total, stream);
+    const char* why = "";
+    int rc = grow(s, l.total, stream, &why);
+    if (rc == CC_ENOMEM) return fail(rc, why);
     if (rc) return rc;
     char* q = s->tiled.buf;
     if ((rc = level1(l, q, n, m, EdgeList{edges, false}, s->st, sym, Gate{}, stream))) return rc;
@@ -1607,9 +1616,10 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
     const uint64_t b_sw = al(4 * m), b_sh = al(2 * m);
     const uint64_t kb = (uint64_t)b_per_block(R), nwg = (uint64_t)R * ((R + kb - 1) / kb);
     const uint64_t b_wgoff = al(8 * (nwg + 1)), b_wgcnt = al(4 * nwg), b_ipref = al(4 * (nwg + 1));
+    const char* why = "";
     int rc = grow(s, b_sw + b_sh + b_tmp2 + b_base2 + b_cbase + b_cfirst + b_run2 + b_wgoff + b_wgcnt +
-                         b_ipref, stream);
-    if (rc == kScratchCapture) return fail(CC_ENOMEM, "regrouped-hook scratch cannot grow under capture");
+                         b_ipref, stream, &why);
+    if (rc == CC_ENOMEM || rc == kScratchCapture) return fail(CC_ENOMEM, why);
     if (rc) return rc;
     char* q = s->tiled.buf;
     uint32_t* sw = reinterpret_cast<uint32_t*>(q); q += b_sw;

@@ -422,3 +422,23 @@ def test_capture_that_would_grow_the_scratch():
     assert_same_labels(to_host_u32(L[0]), want, "after a refused call")
     del g
     cold.close()
+
+
+def test_a_call_that_succeeds_leaves_no_failure_text():
+    """A solve that goes on by another hook where its scratch cannot grow returns CC_OK
+    and leaves the thread's last failure as it was."""
+    n, m = 3 * SLICE, 6 * SLICE
+    ed = to_dev(graphgen.er(n, m, 64))
+    L = torch.empty(n, dtype=torch.int32, device="cuda")
+    c = cc.Context()
+    lib = cc.load()
+    assert lib.cc_solve(5, 0, None, None) == cc.CC_EINVAL
+    text = lib.cc_last_error_detail()
+    assert text
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        c.solve_async(ed, n, L)
+    assert lib.cc_last_error_detail() == text
+    del g
+    c.close()
