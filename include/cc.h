@@ -72,7 +72,8 @@ int cc_version(void);
 #define CC_F_ZROOT_HINT   0x4u
 /* Plain root walks without path splitting (Algorithm 1's finds as printed)
    everywhere, and no pointer jumping inside a hook. Without the flag the
-   regrouped hooks and the batch's workgroup role split paths, and the direct
+   regrouped hooks and the batch's workgroup role split paths (the one-pass filter
+   and the filters' samples from a walk's sixteenth step on), and the direct
    hooks split them where the parent array exceeds 4 MB (one XCD's L2; below
    that the walks are L2 hits and the splitting stores cost more than they
    save). Below that size the direct plain hook, given at least 2^18 entries

@@ -19,9 +19,9 @@ namespace ccm {
 // ---- the sample -------------------------------------------------------------------------
 // Algorithm 1 / 3 on every tstride-th run of kWBlock entries (so that a list in
 // any order, sorted rows for instance, is sampled evenly), without the bitmap
-// and without path splitting: the trees are young, and the splitting stores of
-// all entries meet on the words just below the few large roots (R-MAT n = 2^22,
-// 2^21 entries sampled: 389 us with splitting, 125 without). One entry per
+// and with path splitting only in long walks: the trees are young, and the splitting
+// stores of all entries would meet on the words just below the few large roots (R-MAT
+// n = 2^22, 2^21 entries sampled: 389 us with splitting, 125 without or late). One entry per
 // thread: the pass is a chain of dependent reads and CASes per entry.
 constexpr int kWBlock = kSampleRun;
 constexpr uint32_t kWGrid = 8192;
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kWBlock) void k_warm(const T edges, uint64_t m, uin
         if (sym ? e.x >= e.y : e.x == e.y) continue;
         const uint32_t pu = P[e.x], pv = P[e.y];
         if (pu == pv || pu == e.y || pv == e.x) continue;
-        (void)link<ZR, 0>(P, e.x, pu, e.y, pv, z);
+        (void)link<ZR, 2>(P, e.x, pu, e.y, pv, z);
     }
 }
 

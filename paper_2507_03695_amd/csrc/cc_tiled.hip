@@ -831,7 +831,12 @@ __device__ __forceinline__ void t3_flush(const uint32_t* w, uint32_t* zbits, uin
 //              those of its own entries; this launch's flush shows every workgroup
 //              the others' marks before any entry is hooked (R-MAT n = 2^22, 2^26
 //              entries: both passes 335 us, the full one alone 472).
-//  kFullTiles  the one-pass tiles: hooked in P from the wave's queue
+//  kFullTiles  the one-pass tiles: hooked in P from the wave's queue. Its walks are
+//              short where the giant component was sampled, so they split late: on
+//              R-MAT n = 2^22 late, full and no splitting take 513, 511 and 516 us
+//              whole, but a path of 2 M vertices beside 2 M vertices of a uniform
+//              graph (entries in order) 4.0 ms split late, 4.5 split fully; without
+//              any, each walk would be as long as the path hooked so far.
 //  The one-pass tiles are one index space, tile after tile, cut into equal parts,
 //  one per workgroup: lists whose first endpoints lie in few slices (a share of a
 //  larger graph, sorted rows) fill few tiles.
@@ -983,7 +988,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         // Second looks (endpoints relative to the slices' first IDs), with the bits as
         // they are then: both marked, dropped; one marked, the other is marked (in
         // LDS; t3_flush takes the slice's new marks to the global bitmap); neither,
-        // hooked in P (Algorithm 3, path splitting).
+        // hooked in P (Algorithm 3, walks split from their sixteenth step on).
         auto settle = [&](u32x2 x) {
             const bool mu = (sa[x.x >> 5] >> (x.x & 31)) & 1u, mv = (lb[x.y >> 5] >> (x.y & 31)) & 1u;
             if (mu != mv) {
@@ -1017,7 +1022,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
             }
             const uint32_t pu = P[u], pv = P[v];
             if (u == v || pu == pv || pu == v || pv == u) return;
-            (void)link<true, 0>(P, u, pu, v, pv, z);
+            (void)link<true, 2>(P, u, pu, v, pv, z);
         };
         for (uint32_t w0 = 0; w0 < nch; w0 += kWin3) {
             const uint32_t nw = min((uint32_t)kWin3, nch - w0);

@@ -442,3 +442,25 @@ def test_a_call_that_succeeds_leaves_no_failure_text():
     assert lib.cc_last_error_detail() == text
     del g
     c.close()
+
+
+@pytest.mark.parametrize("down", [False, True])
+@pytest.mark.parametrize("n,m,path", [(1_000_000, 3_000_000, 1 << 18), (4_000_000, 8_000_000, 1 << 21)])
+def test_a_long_path_beside_a_giant_component(ctx, n, m, path, down):
+    """A uniform graph's component and one path of many vertices listed in order, up and
+    down: the filter runs, and the path's entries all go to P, whose walks have to be
+    shortened as they go."""
+    h = n - path
+    p = np.arange(h, n - 1, dtype=np.uint32)
+    p = p[::-1] if down else p
+    e = np.ascontiguousarray(np.concatenate([graphgen.er(h, m, 71), np.stack([p, p + 1], 1)]))
+    want = oracle.cc_labels(n, e)
+    ed = to_dev(e)
+    off, adj = rows_of(e, n)
+    log(f"path n={n} down={down}")
+    for fl in (0, cc.F_ZROOT):
+        assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"n={n} down={down} {fl}")
+    assert_same_labels(to_host_u32(ctx.solve_csr(off, adj, n, flags=cc.F_ZROOT)), want, f"rows n={n} down={down}")
+    assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"steps n={n} down={down}")
+    w = ctx.solve_u64(torch.from_numpy(e.astype(np.int64)).cuda(), n)
+    assert_same_labels(w.cpu().numpy().astype(np.uint32), want, f"wide n={n} down={down}")
