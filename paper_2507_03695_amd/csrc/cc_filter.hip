@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kWBlock) void k_warm(const T edges, uint64_t m, uin
         if (sym ? e.x >= e.y : e.x == e.y) continue;
         const uint32_t pu = P[e.x], pv = P[e.y];
         if (pu == pv || pu == e.y || pv == e.x) continue;
-        (void)link<ZR, 2>(P, e.x, pu, e.y, pv, z);
+        (void)link<ZR, kLateSplit>(P, e.x, pu, e.y, pv, z);
     }
 }
 
@@ -135,6 +135,7 @@ __global__ __launch_bounds__(kGBlock) void k_find_giant(const T edges, uint64_t 
         if (stage < 2) st_agent(&st->giant1, giant);
         st_agent(&st->giant, giant);
         st_agent(&st->rebuild, stage ? giant : 0u);
+        st_agent(&st->flat, stage || !giant ? 1u : 0u);
     }
 }
 
@@ -142,25 +143,26 @@ __global__ __launch_bounds__(kGBlock) void k_find_giant(const T edges, uint64_t 
 // Runs on a flat forest (after compress). A vertex is a member when its root is
 // st->zroot, or (ZR) when it or its root is marked. With PICK the root is found
 // here, as k_find_giant would, by every block for itself from the same reads (one
-// launch less); block 0 records it, and with `first` whether it is a giant
-// component's (st->giant1). Each wave
+// launch less); block 0 records it, and with `sample` whether it is a giant
+// component's (st->giant; after the first sample, 1, st->giant1 too). Each wave
 // writes the two words of 64 consecutive vertices from a ballot.
 template <int MODE, typename T>
 __global__ __launch_bounds__(kGBlock) void k_giant_bits(const T edges, uint64_t m,
                                                         const uint32_t* P, uint64_t n,
-                                                        uint32_t* zbits, DevState* st, int first,
+                                                        uint32_t* zbits, DevState* st, int sample,
                                                         Gate gate) {
     if (gated_off(gate)) return;
     constexpr bool ZR = MODE == kBitsZr;
     uint32_t g;
-    if (MODE == kBitsPick || (first && blockIdx.x == 0)) {
+    if (MODE == kBitsPick || (sample && blockIdx.x == 0)) {
         uint32_t in, tot;
         const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
         g = sample_root(edges, m, n, MODE == kBitsPick, z, &in, &tot,
                         [&](uint32_t x) { return ld_agent(&P[x]); });
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             if (MODE == kBitsPick) st_agent(&st->zroot, g);
-            if (first) st_agent(&st->giant1, giant_enough(in, tot));
+            if (sample == 1) st_agent(&st->giant1, giant_enough(in, tot));
+            if (sample) st_agent(&st->giant, giant_enough(in, tot));
         }
     } else {
         g = ld_agent(&st->zroot);
@@ -207,7 +209,11 @@ __global__ __launch_bounds__(kGBlock) void k_giant_bits(const T edges, uint64_t 
 //    marked, the other is marked too (LDS, and the global word when this set the
 //    bit); neither, the entry is hooked in P as in the direct hook.
 // The bits set since by other workgroups are not seen; a clear bit only sends an
-// entry to P.
+// entry to P. Where the samples show no giant component the marking pass of a list of
+// few entries per vertex leaves at once (n = 1 M, 12 parts, 4 M entries: 321 us with it,
+// 306 without; 20 parts of 5,000 vertices, 16 per vertex: 132 and 143), and rows are
+// left to the caller, whose hook finds them without a search per entry; a list's entries
+// still come here: hooked 64 at a time, they cost what the direct hook takes.
 constexpr int kLBlock = 1024;
 constexpr int kLWaves = kLBlock / 64;
 constexpr uint32_t kMarkGrid = 128;            // workgroups of the marking pass
@@ -220,6 +226,7 @@ __global__ __launch_bounds__(kLBlock) void k_hook_lds(const T edges, uint64_t m,
     extern __shared__ uint32_t bits[];
     __shared__ u32x2 s_queue[kLWaves * 2 * kQueueCap];
     const uint32_t z = ld_agent(&st->zroot);
+    if (((MARK && m < 8ull * n) || std::is_same<T, CsrList>::value) && !ld_agent(&st->giant)) return;
     const uint32_t words = (n + 31) / 32;
     // Plain loads: the copies of an XCD's workgroups come out of its L2 (run_hook_lds
     // sees to it that no older line is there). Each workgroup starts elsewhere, so
@@ -350,21 +357,21 @@ int run_find_giant(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, const uint32
 }
 
 int run_giant_bits(uint64_t n, uint64_t m, EdgeList E, const uint32_t* P, uint32_t* zbits,
-                   DevState* st, int mode, int first, Gate gate, hipStream_t stream) {
+                   DevState* st, int mode, int sample, Gate gate, hipStream_t stream) {
     const uint64_t blocks = (n + 4 * kGBlock - 1) / (4 * kGBlock);
     const uint32_t g = (uint32_t)std::min<uint64_t>(blocks, 2048);
     const uint32_t* none = nullptr;
     auto launch = [&](auto e) {
-        k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+        k_giant_bits<kBitsPick><<<g, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, sample, gate);
     };
-    if (mode == kBitsZr && first) {
+    if (mode == kBitsZr && sample) {
         with_entries(E, [&](auto e) {
-            k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, first, gate);
+            k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(e, m, P, n, zbits, st, sample, gate);
         });
     } else if (mode == kBitsZr) {
-        k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(none, m, P, n, zbits, st, first, gate);
+        k_giant_bits<kBitsZr><<<g, kGBlock, 0, stream>>>(none, m, P, n, zbits, st, sample, gate);
     } else if (mode == kBitsPlain) {
-        k_giant_bits<kBitsPlain><<<g, kGBlock, 0, stream>>>(none, m, P, n, zbits, st, first, gate);
+        k_giant_bits<kBitsPlain><<<g, kGBlock, 0, stream>>>(none, m, P, n, zbits, st, sample, gate);
     } else {
         with_coo(E, launch);
     }

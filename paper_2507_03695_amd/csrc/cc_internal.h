@@ -29,7 +29,7 @@ struct DevState {
     uint32_t giant1;    // a small sample shows a giant component
     uint32_t giant;     // the filter's kernels run (else the direct hook's)
     uint32_t rebuild;   // the bitmap is to be written after a sample without it
-    uint32_t pad1;
+    uint32_t flat;      // the forest is to be flattened after the samples
     uint64_t pad2[2];
 };
 static_assert(sizeof(DevState) == 64, "DevState is one 64-byte block");
@@ -274,8 +274,11 @@ int filter_scratch(Slot* s, uint64_t n, uint64_t m, int passes, bool bits, bool 
                    hipStream_t stream, FilterScratch* out);
 // The filter on scratch sized by filter_scratch with the same arguments: every
 // entry tested against zbits, the rest hooked in P (key order of DevState::zroot).
+// other: what is to happen where the gate is shut, without a bitmap. kOther, kOtherZr:
+// the regrouped entries are hooked in P (key = ID, or with the zero root's keys).
+enum OtherHook { kNoOther, kOther, kOtherZr };
 int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, int passes,
-               bool bits, bool p32, bool sym, Gate gate, hipStream_t stream);
+               bool bits, bool p32, bool sym, Gate gate, int other, hipStream_t stream);
 // The plain hook (key = ID) over first-endpoint buckets. kScratchCapture (nothing
 // queued) where its scratch would have to grow under capture.
 int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, bool sym,
@@ -306,11 +309,11 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
 // Largest n whose whole bitmap fits a workgroup's LDS.
 uint64_t lds_bits_max_n();
 // The bitmap of st->zroot's component, from a flat forest; kBitsPick finds the
-// root first (the one most often seen above sampled endpoints). first: records
-// st->giant1.
+// root first (the one most often seen above sampled endpoints). sample: 1 records
+// st->giant1 and st->giant (after the first sample), 2 st->giant, 0 neither.
 enum BitsMode { kBitsPick, kBitsPlain, kBitsZr };
 int run_giant_bits(uint64_t n, uint64_t m, EdgeList E, const uint32_t* P, uint32_t* zbits,
-                   DevState* st, int mode, int first, Gate gate, hipStream_t stream);
+                   DevState* st, int mode, int sample, Gate gate, hipStream_t stream);
 // Whether the forest shows a giant component (the zero root's, by P and zbits,
 // with zr): st->giant. Stages 1 and 2 run where st->giant1 is 0; 0 and 1 set it too,
 // 1 and 2 set st->rebuild. A plain solve's root: st->zroot.
@@ -322,7 +325,8 @@ uint64_t warm_stride(uint64_t m, uint64_t want);
 // About `want` entries hooked in P (no bitmap), spread evenly over the list.
 int run_warm(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, DevState* st, bool zr, bool sym,
              uint64_t want, Gate gate, hipStream_t stream);
-// Every entry tested against the whole bitmap in LDS, the rest hooked in P.
+// Every entry tested against the whole bitmap in LDS, the rest hooked in P. Rows without
+// a giant component (st->giant) are left alone.
 int run_hook_lds(uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, DevState* st,
                  bool split, bool sym, int device, hipStream_t stream);
 

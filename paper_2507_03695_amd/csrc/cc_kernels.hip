@@ -484,9 +484,11 @@ __global__ __launch_bounds__(kBlock) void k_csr_hook(const uint64_t* __restrict_
                                                      const uint32_t* __restrict__ adj, uint32_t n,
                                                      uint64_t m, const uint32_t* __restrict__ tstart,
                                                      uint64_t ntiles, uint32_t* P, uint32_t* zbits,
-                                                     DevState* st, uint32_t sym) {
+                                                     DevState* st, uint32_t sym,
+                                                     Gate gate = Gate{nullptr, 0u}) {
     __shared__ uint32_t head[kCsrTile];
     __shared__ uint32_t s_wmax[kBlock / 64];
+    if (gated_off(gate)) return;
     const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
     if (blockIdx.x >= ntiles) return;
     {
@@ -883,11 +885,18 @@ int run_push(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P
 //
 // A skewed graph's giant component shows in a small sample; a uniform one's needs
 // about n / 2 entries, so where the device finds none in the small sample, one of
-// up to n entries, half the list at most, is tried. If that shows none either, the whole-bitmap pass (passes 0) hooks what it must in P,
-// which costs it little; the tiles are not built and the direct hook takes the
-// list. Whole solves, always filtering / direct / as decided here (us): R-MAT
-// n = 3 M, 12 M entries 301 / 1412 / 285; ER n = 16 M, 60 M entries 4872 / 3970 /
-// 2353; grid n = 4 M, 8 M entries 9024 / 1050 / 1080.
+// up to n entries, half the list at most, is tried. If that shows none either, the
+// whole-bitmap pass (passes 0) hooks what it must in P, which costs it little; the
+// sizes that were regrouped before there was a sample (tiled_eligible) hook their
+// regrouped entries over the flat forest that the sample leaves, by tiles or by
+// first-endpoint buckets; rows take the CSR hook, and the rest the direct hook, without
+// building the tiles. Whole solves, always filtering / direct / as decided here (us):
+// R-MAT n = 3 M, 12 M entries 301 / 1412 / 285; ER n = 16 M, 60 M entries 4872 / 3970 /
+// 2353; grid n = 4 M, 8 M entries 9024 / 1050 / 1080. Without a giant component, buckets
+// from the start / direct / regrouped after the sample: 12 parts dealt over n = 4 M, 64 M
+// entries 2003 / 2766 / 1577; 20 parts dealt over n = 11 M, 128 M entries 3926 / 5768 /
+// 3938; 20 parts side by side, n = 64 M, 512 M entries 20859 / 24051 / 19068; 12 parts
+// dealt over n = 24 M, 256 M entries 8032 / 10849 / 9567 (2,021 of it the sample).
 //
 // The regrouped zero-root hook of two partition passes takes its small sample by
 // the linking form instead, the first 1/1024 of the entries, which sets the bits
@@ -916,6 +925,18 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
         CCM_HIP(hipGetLastError());
         return CC_OK;
     };
+    // Rows without a giant component: the CSR hook over the flat forest. Its lanes share
+    // their first endpoint's reads, and it needs no search per entry (paths n = 1 M, 3 M
+    // entries: hook 345 us by positions in k_hook_lds, 218 so).
+    auto hook_rows = [&]() -> int {
+        const CsrList& r = *E.csr;
+        const Gate off{&st->giant, 0u};
+        auto hook = split ? &k_csr_hook<true, 1, true> : &k_csr_hook<true, kLateSplit, true>;
+        hook<<<(uint32_t)r.ntiles, kBlock, 0, stream>>>(r.off, r.adj, r.n, m, r.tstart, r.ntiles, P, bits, st,
+                                                        sym ? 1u : 0u, off);
+        CCM_HIP(hipGetLastError());
+        return CC_OK;
+    };
     if (!passes) {
         const int mode = zr ? kBitsZr : kBitsPick;
         if ((rc = run_warm(n, m, E, P, st, zr, sym, small, always, stream))) return rc;
@@ -923,8 +944,9 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
         if ((rc = run_giant_bits(n, m, E, P, bits, st, mode, 1, always, stream))) return rc;
         if ((rc = run_warm(n, m, E, P, st, zr, sym, full, again, stream))) return rc;
         if ((rc = compress(again))) return rc;
-        if ((rc = run_giant_bits(n, m, E, P, bits, st, mode, 0, again, stream))) return rc;
-        return run_hook_lds(n, m, E, P, bits, st, split, sym, s->device, stream);
+        if ((rc = run_giant_bits(n, m, E, P, bits, st, mode, 2, again, stream))) return rc;
+        if ((rc = run_hook_lds(n, m, E, P, bits, st, split, sym, s->device, stream))) return rc;
+        return E.csr ? hook_rows() : CC_OK;
     }
     const bool link_first = zr && passes == 2;
     if (link_first) {
@@ -941,7 +963,7 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
         // 7.07 ms sampled, 7.47 so).
         if (4 * live < 5 * n && tiled_eligible(n, m, true)) {
             if ((rc = run_find_giant(n, m, E, P, bits, st, zr, 0, stream))) return rc;
-            return run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, always, stream);
+            return run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, always, kNoOther, stream);
         }
     } else if ((rc = run_warm(n, m, E, P, st, zr, sym, small, always, stream))) {
         return rc;
@@ -953,10 +975,17 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
     }
     if ((rc = run_warm(n, m, E, P, st, zr, sym, full, again, stream))) return rc;
     if ((rc = run_find_giant(n, m, E, P, bits, st, zr, 2, stream))) return rc;
+    // Without a giant component, the sizes that were always regrouped hook their
+    // regrouped entries, over the flat forest that the samples leave.
+    const bool regroup = !E.csr && tiled_eligible(n, m, zr);
     const Gate write = link_first ? Gate{&st->rebuild, 1u} : on;
-    if ((rc = compress(write))) return rc;
+    if ((rc = compress(!regroup && !E.csr ? write : link_first ? Gate{&st->flat, 1u} : always))) return rc;
     if ((rc = run_giant_bits(n, m, E, P, bits, st, zr ? kBitsZr : kBitsPlain, 0, write, stream))) return rc;
-    if ((rc = run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, on, stream))) return rc;
+    if ((rc = run_filter(s, n, m, E, P, bits, passes, own_bits, p32, sym, on,
+                         !regroup ? kNoOther : zr ? kOtherZr : kOther, stream)))
+        return rc;
+    if (regroup) return CC_OK;
+    if (E.csr) return hook_rows();
     const Gate off{&st->giant, 0u};
     // Longer lists on a resident grid (ER n = 200 M, 400 M entries: 31.6 ms, one
     // workgroup per tile 32.1; grid n = 33 M: 5.7 and 6.0), shorter ones without the
@@ -970,7 +999,7 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
             k_hook_gated<false, 1, false><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
         });
     else if (hook_links_z(flags, n))
-        with_entries(E, [&](auto e) {
+        with_coo(E, [&](auto e) {
             k_hook_gated<true, 1, true><<<g, kBlock, 0, stream>>>(e, m, n32, P, bits, st, sy, skip, off);
         });
     else

@@ -48,11 +48,11 @@ __device__ __forceinline__ bool key_less(uint32_t a, uint32_t b, uint32_t z) {
 }
 
 // Root of x, given px = a value read from P[x]. SPLIT = 1: path splitting (each
-// visited vertex takes its grandparent); SPLIT = 0: plain walk; SPLIT = 2: splitting
-// from the kSplitAfter-th step on, for young trees: their few levels cost less to
-// walk than to split, but entries in an unlucky order can still form chains as long as
-// a component, which nothing else would shorten.
-constexpr int kSplitAfter = 16;
+// visited vertex takes its grandparent); SPLIT = 0: plain walk; SPLIT = k > 1:
+// splitting from the k-th step on, for young trees and small arrays: their few levels
+// cost less to walk than to split, but entries in an unlucky order can still form
+// chains as long as a component, which nothing else would shorten.
+constexpr int kLateSplit = 16;
 // The splitting writes are device-coherent stores. A plain store would leave a
 // dirty line in the writing XCD's L2 whose other words are that XCD's copies;
 // links are CASes performed at the memory side, which that copy does not see,
@@ -66,7 +66,7 @@ __device__ __forceinline__ uint32_t find_root(uint32_t* P, uint32_t x, uint32_t 
     int level = 0;
     while (gp != px) {
         const uint32_t ggp = P[gp];
-        if (SPLIT == 1 || (SPLIT == 2 && ++level >= kSplitAfter)) {
+        if (SPLIT == 1 || (SPLIT > 1 && ++level >= SPLIT)) {
             stress_delay(x);
             st_agent(&P[x], gp);
         }

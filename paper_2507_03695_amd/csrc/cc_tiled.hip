@@ -423,11 +423,17 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_part(const uint32_t* __restri
                   nch2, g);
 }
 
-// Plain path (key = ID) on the level-1 buckets: each workgroup gathers one
+// Direct hook on the level-1 buckets (no bitmap): each workgroup gathers one
 // level-2 chunk, whose first endpoints all lie in one slice of 2^19 vertices,
 // and hooks it. The workgroups running at one time mostly take consecutive
 // chunks of one slice, so their first endpoints' parent entries (2 MB) stay in
 // L2; only the second endpoints' reads are random over the whole array.
+// LOOP: for a launch over many chunks that may be shut by its gate (65,000 workgroups
+// that leave at once take 36 us, kShutGrid of them 9). The loop costs up to a tenth of
+// the pass (grid n = 33 M, 83 M entries 9.0 ms, 9.9 with it), so the others go without.
+constexpr uint32_t kShutGrid = 16384;
+
+template <bool ZR, bool LOOP>
 __global__ __launch_bounds__(kPartBlock) void k_t2_hookplain(const uint32_t* __restrict__ t1w,
                                                              const uint16_t* __restrict__ t1h,
                                                              const uint16_t* __restrict__ segT,
@@ -435,11 +441,14 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_hookplain(const uint32_t* __r
                                                              uint64_t nch1, int R,
                                                              const uint32_t* __restrict__ cbase,
                                                              const uint32_t* __restrict__ desc,
-                                                             uint32_t* P) {
+                                                             uint32_t* P, DevState* st, Gate gate) {
+    if (gated_off(gate)) return;
+    const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
     __shared__ uint8_t owner[kC2];
     __shared__ uint32_t s_pre[kWin2 + 1];
     __shared__ uint32_t s_seg[kWin2];
-    const uint32_t g = blockIdx.x;
+    uint32_t g = blockIdx.x;
+    do {
     if (g >= cbase[R]) return;                  // the grid is an upper bound
     u32x2 e[kPartEPT];
     int a;
@@ -463,8 +472,10 @@ __global__ __launch_bounds__(kPartBlock) void k_t2_hookplain(const uint32_t* __r
         const uint32_t u = e[k].x, v = e[k].y;
         if (!h[k] || u == v) continue;
         if (pu[k] == pv[k] || pu[k] == v || pv[k] == u) continue;   // same tree already
-        (void)link<false, 1>(P, u, pu[k], v, pv[k], 0);
+        (void)link<ZR, 1>(P, u, pu[k], v, pv[k], z);
     }
+    g += gridDim.x;
+    } while (LOOP);
 }
 
 // ---- CSR input: the rows are the level-1 buckets ---------------------------------
@@ -1022,7 +1033,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
             }
             const uint32_t pu = P[u], pv = P[v];
             if (u == v || pu == pv || pu == v || pv == u) return;
-            (void)link<true, 2>(P, u, pu, v, pv, z);
+            (void)link<true, kLateSplit>(P, u, pu, v, pv, z);
         };
         for (uint32_t w0 = 0; w0 < nch; w0 += kWin3) {
             const uint32_t nw = min((uint32_t)kWin3, nch - w0);
@@ -1342,6 +1353,107 @@ __global__ __launch_bounds__(256) void k_tile_count(const uint16_t* __restrict__
     if (threadIdx.x == 0) wcnt[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
 }
 
+// The tiles' entries hooked in P, without a bitmap, tile after tile: for lists whose
+// sample shows no giant component. Both endpoints' parent entries of a tile are 2 MB
+// each. The tiles are one index space (a tile kVisit wider than its entries, the time
+// its run table takes to read) cut into parts, one per workgroup: kHookPart, or wider
+// on long lists (kHookParts of them; 16,000 workgroups that leave at a shut gate take 9
+// us, these 4). Consecutive workgroups go
+// to the XCDs in turn, so part numbers are dealt so that an XCD's workgroups take
+// neighbouring parts and share the slices in its L2.
+constexpr uint32_t kHookPart = 8192, kHookParts = 4096;
+constexpr uint32_t kVisit = 1024;
+constexpr int kXcds = 8;
+constexpr int kTileEPT = 4;
+
+template <bool ZR>
+__global__ __launch_bounds__(kHook3Block) void k_tile_hook(L2Buf tmp2,
+                                                           const uint16_t* __restrict__ run2T,
+                                                           uint64_t nch, int R,
+                                                           const uint32_t* __restrict__ wcnt,
+                                                           uint32_t* P, DevState* st,
+                                                           uint32_t wide_part, Gate gate) {
+    if (gated_off(gate)) return;
+    __shared__ uint32_t s_off[kWin3];
+    __shared__ uint32_t s_pre[kWin3 + 1];
+    __shared__ uint32_t s_tile[kMaxTiles + 1];
+    __shared__ uint32_t wsum[kWaves3 + 1];
+    const uint32_t z = ZR ? ld_agent(&st->zroot) : 0u;
+    const uint32_t tiles = (uint32_t)(R * R);
+    const uint32_t nwin = ((uint32_t)nch + kWin3 - 1) / kWin3;
+    for (uint32_t i = threadIdx.x; i < tiles; i += kHook3Block) {
+        uint32_t t = 0;
+        for (uint32_t w = 0; w < nwin; ++w) t += wcnt[(uint64_t)i * nwin + w];
+        s_off[i] = t ? t + kVisit : 0u;
+    }
+    __syncthreads();
+    wave_scan<8>(s_off, s_tile, (int)tiles);
+    __syncthreads();
+    const uint32_t all = s_tile[tiles];
+    const uint32_t parts = (all + wide_part - 1) / wide_part, per = (parts + kXcds - 1) / kXcds;
+    const uint32_t part = blockIdx.x % kXcds * per + blockIdx.x / kXcds;
+    if (blockIdx.x / kXcds >= per || part >= parts) return;
+    const uint32_t lo = part * wide_part, hi = min(all, lo + wide_part);
+    uint32_t d = 0;
+    for (uint32_t top = tiles; top - d > 1;) {              // last d with s_tile[d] <= lo
+        const uint32_t mid = (d + top) / 2;
+        if (s_tile[mid] <= lo) d = mid;
+        else top = mid;
+    }
+    for (; d < tiles && s_tile[d] < hi; ++d) {
+        const uint32_t wide = s_tile[d + 1] - s_tile[d];
+        if (!wide) continue;
+        const uint32_t jlo = lo > s_tile[d] ? lo - s_tile[d] : 0u;
+        const uint32_t jhi = min(hi - s_tile[d], wide - kVisit);
+        if (jlo >= jhi) continue;                           // only the visit's end
+        const uint32_t abase = d / (uint32_t)R << kSliceBits, bbase = d % (uint32_t)R << kSliceBits;
+        uint32_t jw = 0;                                    // tile index of the window's first
+        for (uint32_t w0 = 0; w0 < (uint32_t)nch && jw < jhi; w0 += kWin3) {
+            const uint32_t wn = wcnt[(uint64_t)d * nwin + w0 / kWin3];
+            if (jw + wn <= jlo) { jw += wn; continue; }
+            const uint32_t nw = min((uint32_t)kWin3, (uint32_t)nch - w0);
+            __syncthreads();
+            for (uint32_t t = threadIdx.x; t < nw; t += kHook3Block) {
+                const uint64_t g = (uint64_t)w0 + t;
+                const uint32_t r0 = run2T[(uint64_t)d * nch + g];
+                s_off[t] = r0;
+                s_pre[t] = run2T[(uint64_t)(d + 1) * nch + g] - r0;
+            }
+            __syncthreads();
+            block_scan_2048(s_pre, nw, wsum);
+            for (uint32_t t = threadIdx.x; t < nw; t += kHook3Block)
+                s_off[t] = (w0 + t) * (uint32_t)kC2 + s_off[t] - s_pre[t];
+            __syncthreads();
+            const uint32_t total = min(wn, jhi - jw), first = jlo > jw ? jlo - jw : 0u;
+            jw += wn;
+            for (uint32_t jb = first + threadIdx.x; jb < total; jb += kTileEPT * kHook3Block) {
+                uint32_t u[kTileEPT], v[kTileEPT], pu[kTileEPT], pv[kTileEPT];
+#pragma unroll
+                for (int k = 0; k < kTileEPT; ++k) {
+                    const uint32_t j = min(jb + (uint32_t)k * kHook3Block, total - 1);
+                    uint32_t t0 = 0, t1 = nw;               // s_pre[t0] <= j < s_pre[t1]
+                    while (t1 - t0 > 1) {
+                        const uint32_t tm = (t0 + t1) / 2;
+                        if (s_pre[tm] <= j) t0 = tm;
+                        else t1 = tm;
+                    }
+                    const uint32_t at = j + s_off[t0], w = tmp2.w[at], h8 = tmp2.h[at];
+                    u[k] = abase | (w & kLoMask);
+                    v[k] = bbase | (w >> kSliceBits) | (h8 << (32 - kSliceBits));
+                }
+#pragma unroll
+                for (int k = 0; k < kTileEPT; ++k) { pu[k] = P[u[k]]; pv[k] = P[v[k]]; }
+#pragma unroll
+                for (int k = 0; k < kTileEPT; ++k) {
+                    if (jb + (uint32_t)k * kHook3Block >= total) continue;
+                    if (pu[k] == pv[k] || pu[k] == v[k] || pv[k] == u[k]) continue;
+                    (void)link<ZR, 1>(P, u[k], pu[k], v[k], pv[k], z);
+                }
+            }
+        }
+    }
+}
+
 // ---- host side --------------------------------------------------------------------
 
 static int slices(uint64_t n) { return (int)((n + (1ull << kSliceBits) - 1) >> kSliceBits); }
@@ -1517,6 +1629,17 @@ static int level1(const TiledLayout& l, char* q, uint64_t n, uint64_t m, EdgeLis
     return cohere(stream);
 }
 
+template <bool ZR>
+static void hook_level1(const TiledLayout& l, char* q, uint32_t* P, DevState* st, Gate gate,
+                        hipStream_t stream) {
+    const bool loop = gate.word && l.nch2 > 2 * kShutGrid;
+    auto hook = loop ? &k_t2_hookplain<ZR, true> : &k_t2_hookplain<ZR, false>;
+    hook<<<loop ? kShutGrid : (uint32_t)l.nch2, kPartBlock, 0, stream>>>(
+        reinterpret_cast<uint32_t*>(q + l.t1w), reinterpret_cast<uint16_t*>(q + l.t1h),
+        reinterpret_cast<uint16_t*>(q + l.seg), reinterpret_cast<uint32_t*>(q + l.pre1), l.nch1, l.R,
+        reinterpret_cast<uint32_t*>(q + l.cbase), reinterpret_cast<uint32_t*>(q + l.desc), P, st, gate);
+}
+
 int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* P, bool sym,
                      hipStream_t stream) {
     const TiledLayout l = tiled_layout(n, m, 3, false, false);
@@ -1527,10 +1650,7 @@ int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uin
     char* q = s->tiled.buf;
     if ((rc = level1(l, q, n, m, EdgeList{edges, false}, s->st, sym, Gate{}, stream))) return rc;
     // the plain path hooks the level-2 chunks as they are gathered
-    k_t2_hookplain<<<(uint32_t)l.nch2, kPartBlock, 0, stream>>>(
-        reinterpret_cast<uint32_t*>(q + l.t1w), reinterpret_cast<uint16_t*>(q + l.t1h),
-        reinterpret_cast<uint16_t*>(q + l.seg), reinterpret_cast<uint32_t*>(q + l.pre1), l.nch1, l.R,
-        reinterpret_cast<uint32_t*>(q + l.cbase), reinterpret_cast<uint32_t*>(q + l.desc), P);
+    hook_level1<false>(l, q, P, s->st, Gate{}, stream);
     CCM_HIP(hipGetLastError());
     return CC_OK;
 }
@@ -1560,8 +1680,9 @@ static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_
 }
 
 int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_t* zbits, int passes,
-               bool bits, bool p32, bool sym, Gate gate, hipStream_t stream) {
+               bool bits, bool p32, bool sym, Gate gate, int other, hipStream_t stream) {
     const TiledLayout l = tiled_layout(n, m, passes, bits, p32);
+    const Gate part = other != kNoOther ? Gate{} : gate, off{gate.word, !gate.want};
     if (s->tiled.cap < l.total) return fail(CC_EDEVICE, "regrouped-hook scratch too small (a bug)");
     char* q = s->tiled.buf;
     const L2Buf tmp2{reinterpret_cast<uint32_t*>(q + l.w), reinterpret_cast<uint8_t*>(q + l.h)};
@@ -1572,12 +1693,12 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
         const uint32_t g = (uint32_t)l.nch1;
         with_entries(E, [&](auto e) {
             k_tile_part<<<g, kPartBlock, 0, stream>>>(e, m, (uint32_t)n, l.R, l.nch1, tmp2, run2, s->st,
-                                                      sym ? 1u : 0u, gate);
+                                                      sym ? 1u : 0u, part);
         });
         if ((rc = cohere(stream))) return rc;
         const uint32_t nwin = (uint32_t)((l.nch1 + kWin3 - 1) / kWin3);
         auto* wcnt = reinterpret_cast<uint32_t*>(q + l.wcnt);
-        k_tile_count<<<(uint32_t)(l.R * l.R) * nwin, 256, 0, stream>>>(run2, l.nch1, nwin, wcnt, gate);
+        k_tile_count<<<(uint32_t)(l.R * l.R) * nwin, 256, 0, stream>>>(run2, l.nch1, nwin, wcnt, part);
         if ((rc = cohere(stream))) return rc;
         // one workgroup per CU is resident; no more than its copies are worth
         const uint32_t wgs = (uint32_t)std::max<uint64_t>(
@@ -1589,10 +1710,21 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
         k_t3_filter<kFullTiles><<<wgs, kHook3Block, 0, stream>>>(
             tmp2, run2, l.nch1, l.R, wcnt, nullptr, nullptr, zbits, words, P, nullptr, nullptr, nullptr,
             nullptr, s->st, gate);
+        if (other != kNoOther) {
+            const uint64_t all = m + (uint64_t)(l.R * l.R) * kVisit;
+            const uint64_t part = std::max<uint64_t>(kHookPart, all / kHookParts);
+            const uint32_t gh = (uint32_t)((all / part + kXcds) / kXcds * kXcds);
+            auto hook = other == kOtherZr ? &k_tile_hook<true> : &k_tile_hook<false>;
+            hook<<<gh, kHook3Block, 0, stream>>>(tmp2, run2, l.nch1, l.R, wcnt, P, s->st, (uint32_t)part, off);
+        }
         CCM_HIP(hipGetLastError());
         return CC_OK;
     }
-    if ((rc = level1(l, q, n, m, E, s->st, sym, gate, stream))) return rc;
+    if ((rc = level1(l, q, n, m, E, s->st, sym, part, stream))) return rc;
+    // the other hook reads the level-1 buckets, whose room the filter's survivors take
+    // (only one of the two runs)
+    if (other == kOtherZr) hook_level1<true>(l, q, P, s->st, off, stream);
+    else if (other == kOther) hook_level1<false>(l, q, P, s->st, off, stream);
     auto* cbase = reinterpret_cast<uint32_t*>(q + l.cbase);
     auto* base2 = reinterpret_cast<uint64_t*>(q + l.base2);
     auto part2 = l.R <= kFewSlices ? &k_t2_part<kFewSlices> : &k_t2_part<kMaxSlices>;

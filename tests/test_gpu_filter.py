@@ -464,3 +464,60 @@ def test_a_long_path_beside_a_giant_component(ctx, n, m, path, down):
     assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"steps n={n} down={down}")
     w = ctx.solve_u64(torch.from_numpy(e.astype(np.int64)).cuda(), n)
     assert_same_labels(w.cpu().numpy().astype(np.uint32), want, f"wide n={n} down={down}")
+
+
+def parts(n, m, k, side, seed):
+    """k equal uniform components: side by side in the IDs, or dealt over them."""
+    r = np.random.RandomState(seed)
+    size = n // k
+    c, a, b = r.randint(0, k, m), r.randint(0, size, m), r.randint(0, size, m)
+    e = np.stack([c * size + a, c * size + b] if side else [a * k + c, b * k + c], 1)
+    return np.ascontiguousarray(e.astype(np.uint32))
+
+
+@pytest.mark.parametrize("side", [False, True])
+@pytest.mark.parametrize("n,m,k", [(300_000, 1_200_000, 20), (100_000, 1_600_000, 20), (4 * SLICE, 1 << 24, 12),
+                                   (4 * SLICE, (1 << 24) - 1, 12), (3 * SLICE + 1, 1 << 24, 12),
+                                   (8 * SLICE + 40, (1 << 24) + 8191, 31), (22 * SLICE, (1 << 24) + 77, 12),
+                                   (23 * SLICE, 40_000_000, 20)])
+def test_components_of_equal_size(ctx, n, m, k, side):
+    """Dense lists without a giant component, each side of the sizes at which their
+    regrouped entries are hooked: lists, symmetric lists, steps, rows, 64-bit IDs, an
+    endpoint out of range."""
+    e = parts(n, m, k, side, n + m)
+    want = oracle.cc_labels(n, e)
+    ed = to_dev(e)
+    off, adj = rows_of(e, n)
+    log(f"parts n={n} m={m} side={side}")
+    for fl in (0, cc.F_ZROOT):
+        assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"n={n} m={m} {fl}")
+    assert_same_labels(to_host_u32(ctx.solve_csr(off, adj, n, flags=cc.F_ZROOT)), want, f"rows n={n} m={m}")
+    assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"n={n} m={m} steps")
+    w = ctx.solve_u64(ed.to(torch.int64), n)
+    assert_same_labels(w.cpu().numpy().astype(np.uint32), want, f"wide n={n} m={m}")
+    del w
+    both = torch.cat([ed, ed.flip(1)])
+    for fl in (cc.F_SYMMETRIC, cc.F_SYMMETRIC | cc.F_ZROOT):
+        assert_same_labels(to_host_u32(ctx.solve(both, n, flags=fl)), want, f"symmetric n={n} m={m} {fl}")
+    ed[m // 2, 1] = n
+    L = torch.empty(n, dtype=torch.int32, device="cuda")
+    for fl in (0, cc.F_ZROOT):
+        ctx.solve_async(ed, n, L, flags=fl)
+        assert ctx.sync() == cc.CC_ERANGE
+
+
+def test_few_tiles_without_a_giant_component(ctx):
+    """First endpoints in one slice or in a last slice of few vertices: nearly all tiles
+    are empty, and parts of the tile hook's index space hold several or none."""
+    n = 5 * SLICE + 11
+    i = np.arange(1 << 24, dtype=np.int64)
+    for lo, size in ((2 * SLICE, SLICE), (5 * SLICE, 11), (0, 3)):
+        u = lo + i * 7919 % size
+        v = (u % 11 + 11 * (i * 104729 % (n // 11))) % n    # a vertex's residue mod 11 is its part's
+        e = np.ascontiguousarray(np.stack([u, v], 1).astype(np.uint32))
+        want = oracle.cc_labels(n, e)
+        ed = to_dev(e)
+        log(f"few tiles at {lo}")
+        for fl in (0, cc.F_ZROOT):
+            assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"first in {lo} {fl}")
+        assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"first in {lo} steps")
