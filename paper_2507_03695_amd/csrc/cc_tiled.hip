@@ -857,7 +857,15 @@ __device__ __forceinline__ void t3_flush(const uint32_t* w, uint32_t* zbits, uin
 //  kManyRuns   the same beyond kFewSlices slices, where a tile is small: marks go
 //              to the global bitmap one by one (t3_flush's pass over a slice costs
 //              as much as some ten thousand of them)
-enum FilterMode { kMarkTiles, kFullTiles, kFullRuns, kManyRuns };
+//  kSparseRuns the same on other lists of fewer than kFlushEntries entries to a
+//              workgroup: the others see the marks at once, and the entries that are
+//              kept, which are most, are written when first settled (zero root, ER n =
+//              67 M, 60 M entries: 7.6 ms as kFullRuns, 7.1 so; a twentieth of R-MAT-26
+//              2.4 and 1.9). Where marks settle most entries, a second look when the
+//              second queue is full saves more (R-MAT-24 rows, 60 M entries, 121,000 to
+//              a workgroup: survivor hook 65 us with it, 118 without).
+enum FilterMode { kMarkTiles, kFullTiles, kFullRuns, kManyRuns, kSparseRuns };
+constexpr uint64_t kFlushEntries = 32768;
 constexpr uint32_t kMarkPart = 8;
 constexpr uint32_t kTileCost = 8192;  // entries' worth of a tile's fixed time (8 us)
 
@@ -875,7 +883,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                                                            uint32_t* __restrict__ wgcnt,
                                                            DevState* st, Gate gate) {
     if (gated_off(gate)) return;
-    constexpr bool RUNS = MODE == kFullRuns || MODE == kManyRuns, TILES = !RUNS;
+    constexpr bool RUNS = MODE >= kFullRuns, TILES = !RUNS;
     __shared__ uint32_t sa[kSliceWords];
     __shared__ uint32_t sb[kSliceWords];
     __shared__ uint32_t s_off[kWin3];
@@ -889,7 +897,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
     // copies of any one slice and see each other's marks through the global
     // bitmap sooner. (a, bg) = (i mod R, (i div R + a) mod nbg) is a bijection.
     const int kB = TILES ? 1 : b_per_block(R);
-    constexpr bool one_by_one = MODE == kManyRuns;
+    constexpr bool one_by_one = MODE == kManyRuns || MODE == kSparseRuns, direct = MODE == kSparseRuns;
     const uint32_t nbg = ((uint32_t)R + kB - 1) / kB;
     int a = (int)(blockIdx.x % (uint32_t)R);
     const int bg = (int)((blockIdx.x / (uint32_t)R + (uint32_t)a) % nbg);
@@ -1085,7 +1093,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                     if (MODE == kMarkTiles) {
                         if (h && !both) (void)settle(x);
                     } else {
-                        queue_push(q, lane, h && !both, x, settle, hook);
+                        queue_push<direct>(q, lane, h && !both, x, settle, hook);
                     }
                 }
                 continue;
@@ -1133,7 +1141,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                     if (MODE == kMarkTiles) {
                         if (pend) (void)settle(x);
                     } else {
-                        queue_push(q, lane, pend, x, settle, hook);
+                        queue_push<direct>(q, lane, pend, x, settle, hook);
                     }
                 }
                 if (!more) break;
@@ -1142,7 +1150,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         }
         // this slice's pending entries are settled before the next slice's
         // bitmap replaces it
-        if (MODE != kMarkTiles) queue_finish(q, lane, settle, hook);
+        if (MODE != kMarkTiles) queue_finish<direct>(q, lane, settle, hook);
         if (b != a && !one_by_one) {
             __syncthreads();
             t3_flush(sb, zbits, (uint64_t)b * kSliceWords, words);
@@ -1656,7 +1664,7 @@ int run_hook_buckets(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uin
 }
 
 // Steps 5-6 on the level-2 buffers: survivors to (sw, sh), then hooked.
-static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_t* base2,
+static int filter_runs(int R, uint64_t m, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_t* base2,
                        uint32_t* cbase, uint32_t* sw, uint16_t* sh, uint64_t* wgoff,
                        uint32_t* wgcnt, uint32_t* ipref, uint32_t* P, uint32_t* zbits,
                        uint64_t words, DevState* st, Gate again, Gate gate, hipStream_t stream) {
@@ -1667,7 +1675,9 @@ static int filter_runs(int R, uint64_t nch2, L2Buf tmp2, uint16_t* run2, uint64_
     if ((rc = cohere(stream))) return rc;
     k_t3_offsets<<<(uint32_t)R, 64, 0, stream>>>(wgcnt, R, base2, wgoff, gate);
     if ((rc = cohere(stream))) return rc;
-    auto filter = R <= kFewSlices ? &k_t3_filter<kFullRuns> : &k_t3_filter<kManyRuns>;
+    auto filter = R > kFewSlices            ? &k_t3_filter<kManyRuns>
+                  : m < kFlushEntries * nwg ? &k_t3_filter<kSparseRuns>
+                                            : &k_t3_filter<kFullRuns>;
     filter<<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, nch2, R, nullptr, base2, cbase, zbits, words, P,
                                             sw, sh, wgoff, wgcnt, st, gate);
     if ((rc = cohere(stream))) return rc;
@@ -1735,7 +1745,7 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
     if ((rc = cohere(stream))) return rc;
     // the survivor regions live in the level-1 buffers, free once the level-2
     // partition has read them (positions [base2[a], base2[a+1]) for slice a)
-    return filter_runs(l.R, l.nch2, tmp2, run2, base2, cbase, reinterpret_cast<uint32_t*>(q + l.t1w),
+    return filter_runs(l.R, m, l.nch2, tmp2, run2, base2, cbase, reinterpret_cast<uint32_t*>(q + l.t1w),
                        reinterpret_cast<uint16_t*>(q + l.t1h), reinterpret_cast<uint64_t*>(q + l.wgoff),
                        reinterpret_cast<uint32_t*>(q + l.wgcnt), reinterpret_cast<uint32_t*>(q + l.ipref),
                        P, zbits, words, s->st, Gate{&s->st->giant, 1u}, gate, stream);
@@ -1779,7 +1789,7 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
     k_t2_csr<<<(uint32_t)nch2, kPartBlock, 0, stream>>>(off, adj, n, R, base2, cbase, cfirst, tmp2,
                                                        run2, nch2, s->st, sym ? 1u : 0u);
     if ((rc = cohere(stream))) return rc;
-    return filter_runs(R, nch2, tmp2, run2, base2, cbase, sw, sh, wgoff, wgcnt, ipref, P, s->zbits,
+    return filter_runs(R, m, nch2, tmp2, run2, base2, cbase, sw, sh, wgoff, wgcnt, ipref, P, s->zbits,
                        (n + 31) / 32, s->st, Gate{}, Gate{}, stream);
 }
 

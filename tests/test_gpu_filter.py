@@ -521,3 +521,19 @@ def test_few_tiles_without_a_giant_component(ctx):
         for fl in (0, cc.F_ZROOT):
             assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=fl)), want, f"first in {lo} {fl}")
         assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"first in {lo} steps")
+
+
+@pytest.mark.parametrize("n,m", [(60 * SLICE, (1 << 24) + 1), (36 * SLICE + 7, 23_035_903), (36 * SLICE + 7, 23_035_904)])
+def test_few_entries_to_a_workgroup(ctx, n, m):
+    """Two passes with few entries to a workgroup of the filter, and each side of 32,768
+    (37 slices: 37 * 19 workgroups): nearly all entries are kept, or a skewed list's marks
+    settle most."""
+    for kind in ("er", "rmat", "paths"):
+        e = graph(kind, n, m, n + m)
+        want = oracle.cc_labels(n, e)
+        ed = to_dev(e)
+        off, adj = rows_of(e, n)
+        log(f"{kind} n={n} m={m}")
+        assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=cc.F_ZROOT)), want, f"{kind} n={n} m={m}")
+        assert_same_labels(to_host_u32(ctx.solve_csr(off, adj, n, flags=cc.F_ZROOT)), want, f"rows {kind} n={n}")
+        assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"{kind} n={n} m={m} steps")
