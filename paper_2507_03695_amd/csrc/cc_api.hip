@@ -406,16 +406,13 @@ extern "C" int cc_solve_csr(cc_ctx* ctx, uint64_t n, const uint64_t* offsets, co
     int rc = set_dev(ctx);
     if (rc) return rc;
     hipStream_t hs = (hipStream_t)stream;
-    // the entry count sizes the launches: read off[n] (a coherent copy)
-    if ((rc = cohere(hs))) return rc;
-    uint64_t* hm = reinterpret_cast<uint64_t*>(ctx->slot.host_status);
-    CCM_HIP(hipMemcpyAsync(hm, offsets + n, sizeof(uint64_t), hipMemcpyDeviceToHost, hs));
-    CCM_HIP(hipStreamSynchronize(hs));
-    const uint64_t m = *hm;
-    *hm = 0;
+    // the entry count sizes the launches
+    uint64_t m = 0;
+    uint32_t maxdeg = 0;
+    if ((rc = run_csr_head(&ctx->slot, n, offsets, flags, hs, &m, &maxdeg))) return rc;
     if (m && !adj) return fail(CC_EINVAL, "NULL adj with a nonzero entry count");
     if (m > (1ull << 40)) return fail(CC_EINVAL, "offsets[n] is implausibly large");
-    if ((rc = run_solve_csr(&ctx->slot, n, m, offsets, adj, L, flags, zroot_hint, hs))) return rc;
+    if ((rc = run_solve_csr(&ctx->slot, n, m, offsets, adj, L, flags, zroot_hint, maxdeg, hs))) return rc;
     return finish_status(ctx, hs, st);
 }
 

@@ -239,7 +239,11 @@ int run_solve(Slot* s, uint64_t n, uint64_t m, const uint32_t* edges, uint32_t* 
               uint32_t flags, uint32_t hint, hipStream_t stream);
 // Whole path on CSR input (m = off[n], read by the caller).
 int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
-                  uint32_t* L, uint32_t flags, uint32_t hint, hipStream_t stream);
+                  uint32_t* L, uint32_t flags, uint32_t hint, uint32_t maxdeg, hipStream_t stream);
+// What run_solve_csr needs of the offsets, waited for: m = off[n], and with CC_F_ZROOT
+// (no hint) the longest row, whose vertex is left in DevState::zsel; else maxdeg 0.
+int run_csr_head(Slot* s, uint64_t n, const uint64_t* off, uint32_t flags, hipStream_t stream, uint64_t* m,
+                 uint32_t* maxdeg);
 // Plain path with 64-bit IDs (cc_wide.hip).
 int run_solve_w(Slot* s, uint64_t n, uint64_t m, const uint64_t* edges, uint64_t* L,
                 uint32_t flags, hipStream_t stream);
@@ -301,9 +305,10 @@ void slot_lend_scratch(Slot* s, char* block, uint64_t bytes, uint64_t n, uint32_
                        LentScratch* saved);
 void slot_return_scratch(Slot* s, const LentScratch* saved);
 void tiled_free(TiledScratch* t);
-// The same on CSR input, where the rows already are the first-endpoint buckets.
+// The same on CSR input, where the rows already are the first-endpoint buckets. retest:
+// the survivors' bits are tested once more before they are hooked.
 int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
-                       uint32_t* P, hipStream_t stream, bool sym = false);
+                       uint32_t* P, bool retest, hipStream_t stream, bool sym = false);
 
 // Hooks that test a bitmap in LDS (cc_filter.hip).
 // Largest n whose whole bitmap fits a workgroup's LDS.

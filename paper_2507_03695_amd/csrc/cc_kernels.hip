@@ -457,6 +457,16 @@ __global__ void k_zsel_reset(DevState* st) {
     if (threadIdx.x == 0 && blockIdx.x == 0) st_agent64(&st->zsel, 0);
 }
 
+// What the host needs before it can launch: the entry count and (with the maximum
+// degree found) zsel, to pinned host memory.
+__global__ void k_csr_head(const uint64_t* end, const DevState* st, int zr, uint64_t* host) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        __hip_atomic_store(host, ld_agent64(end), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(host + 1, zr ? ld_agent64(&st->zsel) : 0ull, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // Initial Push over the zero root's whole row (Algorithm 4 initial-push loop).
 __global__ __launch_bounds__(kBlock) void k_csr_push(const uint64_t* __restrict__ off,
                                                      const uint32_t* __restrict__ adj, uint64_t n,
@@ -1187,8 +1197,25 @@ int run_canon(Slot* s, uint64_t n, uint32_t* L, hipStream_t stream) {
     return CC_OK;
 }
 
+int run_csr_head(Slot* s, uint64_t n, const uint64_t* off, uint32_t flags, hipStream_t stream, uint64_t* m,
+                 uint32_t* maxdeg) {
+    const bool zmax = (flags & CC_F_ZROOT) && !(flags & CC_F_ZROOT_HINT);
+    if (zmax) k_zsel_reset<<<1, 64, 0, stream>>>(s->st);
+    int rc = cohere(stream);
+    if (rc) return rc;
+    if (zmax) k_csr_zmax<<<grid_for(n, 4 * kBlock, 2048), kBlock, 0, stream>>>(off, n, s->st);
+    uint64_t* host = reinterpret_cast<uint64_t*>(s->host_status);
+    k_csr_head<<<1, 64, 0, stream>>>(off + n, s->st, zmax, host);
+    CCM_HIP(hipGetLastError());
+    CCM_HIP(hipStreamSynchronize(stream));
+    *m = __atomic_load_n(host, __ATOMIC_ACQUIRE);
+    *maxdeg = (uint32_t)(__atomic_load_n(host + 1, __ATOMIC_RELAXED) >> 32);
+    host[0] = host[1] = 0;
+    return CC_OK;
+}
+
 int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
-                  uint32_t* L, uint32_t flags, uint32_t hint, hipStream_t stream) {
+                  uint32_t* L, uint32_t flags, uint32_t hint, uint32_t maxdeg, hipStream_t stream) {
     if (n == 0) return CC_OK;
     int rc;
     const bool zr = flags & CC_F_ZROOT;
@@ -1213,33 +1240,31 @@ int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const ui
     k_csr_tiles<<<gn, kBlock, 0, stream>>>(off, n, m, s->csr_tiles, ntiles, s->st);
     CCM_HIP(hipGetLastError());
     if (zr) {
-        if (flags & CC_F_ZROOT_HINT) {
-            k_zfinish<<<1, 64, 0, stream>>>(s->st, 1, hint);
-        } else {
-            k_zsel_reset<<<1, 64, 0, stream>>>(s->st);
-            if ((rc = cohere(stream))) return rc;
-            k_csr_zmax<<<grid_for(n, 4 * kBlock, 2048), kBlock, 0, stream>>>(off, n, s->st);
-            if ((rc = cohere(stream))) return rc;
-            k_zfinish<<<1, 64, 0, stream>>>(s->st, 0, 0);
-        }
+        k_zfinish<<<1, 64, 0, stream>>>(s->st, flags & CC_F_ZROOT_HINT ? 1 : 0, hint);
         CCM_HIP(hipGetLastError());
         if ((rc = zbits_reset(s, n, stream))) return rc;
         k_csr_push<<<64, kBlock, 0, stream>>>(off, adj, n, m, L, s->zbits, s->st);
         CCM_HIP(hipGetLastError());
     }
     if ((rc = cohere(stream))) return rc;
+    const bool skewed = maxdeg >= 64 * (m / n + 1);      // the longest row against the mean
     if (zr && !(flags & CC_F_NO_SPLIT)) {
         // The whole-bitmap and one-pass tile filters read the rows as entries (ms:
         // extras n = 1.7 M, 10.4 M entries 0.58 direct, 0.40 so; ER n = 400,000, 1.5 M
         // entries 0.40 and 0.24; grid n = 3 M, 4 M entries 0.51 and 0.56, hence three
         // entries per two vertices at least). The regrouped hook of two passes has
-        // its own CSR form below. The plain direct hook, whose lanes share their first
+        // its own CSR form below, and keeps the skewed graphs of 12 ranges and more (one
+        // pass, two, us: R-MAT n = 2^23, 17 M entries 887 and 474, 69 M 1406 and 818; n =
+        // 2^22, 35 M 825 and 918; ER n = 10 M, 50 M 2166 and 2324; 16 parts n = 8 M,
+        // 60 M 2937 and 16004). The plain direct hook, whose lanes share their first
         // endpoint's reads, is hard to beat here: ER n = 12 M, 60 M entries 1.98 ms
         // direct, 2.54 filtered.
         const CsrList rows{off, adj, s->csr_tiles, ntiles, (uint32_t)n};
         const EdgeList E{nullptr, false, &rows};
         const bool lds = lds_eligible(n, m);
-        const int passes = (flags & CC_F_NO_TILE) || s->no_tiled || 2 * m < 3 * n ? 0 : filter_passes(n, m, true);
+        const bool two = skewed && n > (11ull << 19) && tiled_eligible(n, m, true);
+        const int passes =
+            (flags & CC_F_NO_TILE) || s->no_tiled || 2 * m < 3 * n || two ? 0 : filter_passes(n, m, true);
         FilterScratch fs{};
         if (lds || (passes == 1 && !filter_scratch(s, n, m, passes, false, false, stream, &fs))) {
             if ((rc = hook_by_bits(s, n, m, E, L, s->zbits, passes, true, false, false, flags, stream)))
@@ -1258,7 +1283,10 @@ int run_solve_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const ui
                 off, adj, (uint32_t)n, m, s->csr_tiles, ntiles, L, s->zbits, s->st, sym);
             CCM_HIP(hipGetLastError());
         }
-        if ((rc = run_hook_tiled_csr(s, n, m, off, adj, L, stream, sym != 0))) return rc;
+        // A skewed graph's giant component is in the bitmap by the time the survivors are
+        // hooked: their bits are worth a second look (ER n = 16 M, 60 M entries: 4.0 ms
+        // with it, 3.0 without; R-MAT-24, 2^28 entries: 2.2 without the look, 1.8 with it).
+        if ((rc = run_hook_tiled_csr(s, n, m, off, adj, L, skewed, stream, sym != 0))) return rc;
     } else if (ntiles) {
         const uint32_t g = (uint32_t)ntiles;
         const uint32_t n32 = (uint32_t)n;

@@ -1753,7 +1753,7 @@ int run_filter(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P, uint32_
 
 // The regrouped zero-root hook on CSR input (steps 4-5 on adj's own buckets).
 int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, const uint32_t* adj,
-                       uint32_t* P, hipStream_t stream, bool sym) {
+                       uint32_t* P, bool retest, hipStream_t stream, bool sym) {
     const int R = slices(n);
     const uint64_t nch2 = m / kC2 + (uint64_t)R + 1;
     auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
@@ -1790,7 +1790,7 @@ int run_hook_tiled_csr(Slot* s, uint64_t n, uint64_t m, const uint64_t* off, con
                                                        run2, nch2, s->st, sym ? 1u : 0u);
     if ((rc = cohere(stream))) return rc;
     return filter_runs(R, m, nch2, tmp2, run2, base2, cbase, sw, sh, wgoff, wgcnt, ipref, P, s->zbits,
-                       (n + 31) / 32, s->st, Gate{}, Gate{}, stream);
+                       (n + 31) / 32, s->st, retest ? Gate{} : Gate{&s->st->zroot, kEmpty}, Gate{}, stream);
 }
 
 }  // namespace ccm

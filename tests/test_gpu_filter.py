@@ -537,3 +537,27 @@ def test_few_entries_to_a_workgroup(ctx, n, m):
         assert_same_labels(to_host_u32(ctx.solve(ed, n, flags=cc.F_ZROOT)), want, f"{kind} n={n} m={m}")
         assert_same_labels(to_host_u32(ctx.solve_csr(off, adj, n, flags=cc.F_ZROOT)), want, f"rows {kind} n={n}")
         assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"{kind} n={n} m={m} steps")
+
+
+@pytest.mark.parametrize("kind", ["er", "rmat", "star"])
+@pytest.mark.parametrize("n", [11 * SLICE, 11 * SLICE + 1])
+def test_rows_by_their_longest(n, kind):
+    """Rows of skewed graphs take the two-pass hook from 12 slices on, others the one-pass
+    tiles; a hint leaves the longest row unknown. The zero root is the longest row's."""
+    m = (1 << 24) + 9
+    e = graph("er" if kind == "star" else kind, n, m, n)
+    if kind == "star":                             # one long row is enough to be skewed
+        e[: 1 << 12, 0] = n - 5
+    want = oracle.cc_labels(n, e)
+    off, adj = rows_of(e, n)
+    log(f"rows {kind} n={n}")
+    c = cc.Context()
+    for fl in (cc.F_ZROOT, 0):
+        assert_same_labels(to_host_u32(c.solve_csr(off, adj, n, flags=fl)), want, f"{kind} n={n} {fl}")
+        assert c.get_zroot() == oracle.zroot_csr(off.cpu().numpy().astype(np.uint64))
+    L = torch.empty(n, dtype=torch.int32, device="cuda")
+    c.solve_csr_async(off, adj, n, L, flags=cc.F_ZROOT | cc.F_ZROOT_HINT, zroot_hint=n - 1)
+    assert c.sync() == cc.CC_OK
+    assert_same_labels(to_host_u32(L), want, f"{kind} n={n} hint")
+    assert c.get_zroot() == n - 1
+    c.close()
