@@ -596,7 +596,10 @@ int cc_serve_open(cc_ctx* ctx, const cc_serve_opts* opts, cc_server** out);
  * until the request's device footprint fits the budget: 8m + 4n bytes (edges,
  * labels) plus the scratch its solve needs (the zero-root bitmap, the
  * regrouped hook's buffers), all taken from the server's arena, so serving
- * allocates nothing per request. Small requests (n <= small_n) go to batched
+ * allocates nothing per request. The one-pass filter's scratch (5 bytes per
+ * entry) and a plain solve's two-pass filter's (11, where the bucketed hook needs
+ * 6) are taken only while half of the arena stays free; without, such a request
+ * takes the direct or the bucketed hook. Small requests (n <= small_n) go to batched
  * launches through per-worker staging instead. flags: CC_F_ZROOT,
  * CC_F_ZROOT_EXACT, CC_F_NO_SPLIT, CC_F_NO_TILE, CC_F_SYMMETRIC (applied on the
  * single-graph path; batched requests take the plain path, same labels).

@@ -98,6 +98,7 @@ struct Req {
     uint32_t flags = 0;
     uint64_t foot = 0;      // device bytes of the large path: edges, labels, scratch
     uint64_t scratch = 0;   // of which the solve's own scratch (lent to the slot)
+    uint64_t full = 0;      // the scratch that the solve is fastest with (>= scratch)
     bool small = false;
     uint64_t off = 0;       // arena offset (large path)
     int status = CC_OK;
@@ -138,13 +139,27 @@ struct cc_server {
 
 namespace {
 
+// Room for a large request in the arena. The filter's scratch beyond what the solve
+// can do with is taken only while half of the arena stays free: it must not keep out a
+// request that would fit beside this one without it.
+bool place(cc_server* s, Req* r) {
+    const uint64_t base = r->foot - r->scratch;
+    if (r->full > r->scratch && s->arena.used() + base + r->full <= s->arena.size / 2 &&
+        s->arena.alloc(base + r->full, &r->off)) {
+        r->scratch = r->full;
+        r->foot = base + r->full;
+        return true;
+    }
+    return s->arena.alloc(r->foot, &r->off);
+}
+
 // Move queued requests that fit into the ready list (caller holds mu).
 void admit(cc_server* s) {
     Req* blocked = nullptr;
     for (auto it = s->queue.begin(); it != s->queue.end();) {
         if (s->inflight >= s->opts.max_inflight) break;
         Req* r = *it;
-        bool ok = r->small || s->arena.alloc(r->foot, &r->off);
+        bool ok = r->small || place(s, r);
         if (ok) {
             r->t_admit = now_ns();
             s->ready.push_back(r);
@@ -376,10 +391,9 @@ extern "C" int cc_serve_submit(cc_server* s, uint64_t n, uint64_t m, const uint3
         return fail(CC_EINVAL, "flag not accepted by the server (CC_F_ZROOT_HINT, unknown)");
     Req* r = new Req();
     r->n = n; r->m = m; r->eh = edges_host; r->Lh = L_host; r->flags = flags;
-    r->scratch = solve_scratch_bytes(n, m, flags, false);
-    const uint64_t base = align_up(8 * m) + align_up(4 * n);
-    if (base + r->scratch > s->arena.size) r->scratch = solve_scratch_bytes(n, m, flags, true);
-    r->foot = base + r->scratch;
+    r->scratch = solve_scratch_bytes(n, m, flags, true);
+    r->full = solve_scratch_bytes(n, m, flags, false);
+    r->foot = align_up(8 * m) + align_up(4 * n) + r->scratch;
     const uint64_t stage_need = align_up(8 * m) + align_up(4 * n) + 512;
     r->small = n <= s->opts.small_n && n < (1ull << 31) && stage_need <= s->stage_cap;
     if (!r->small && r->foot > s->arena.size) {

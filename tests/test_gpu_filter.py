@@ -561,3 +561,27 @@ def test_rows_by_their_longest(n, kind):
     assert_same_labels(to_host_u32(L), want, f"{kind} n={n} hint")
     assert c.get_zroot() == n - 1
     c.close()
+
+
+def test_served_requests_share_a_tight_arena():
+    """Two requests that fit the arena together without the filter's scratch are in
+    flight together; with room to spare a request has it."""
+    n, m = 3 * SLICE, 6_000_000
+    es = [graphgen.er(n, m, 81 + k) for k in range(2)]
+    wants = [oracle.cc_labels(n, e) for e in es]
+    ctx = cc.Context()
+    both = 2 * (8 * m + 4 * n) + (4 << 20)
+    for arena in (both, 8 * both):
+        s = cc.Server(ctx, streams=2, hbm_budget=arena * 4 // 3)
+        try:
+            outs = [np.empty(n, np.uint32) for _ in es]
+            ts = [s.submit(e, n, o) for e, o in zip(es, outs)]
+            stats = [s.wait(t) for t in ts]
+            assert [rc for rc, _ in stats] == [cc.CC_OK] * 2
+            for o, w in zip(outs, wants):
+                assert_same_labels(o, w, f"served, arena {arena}")
+            a, b = stats[0][1], stats[1][1]
+            assert b.t_admit_ns < a.t_done_ns, "the second request waited for the first one's room"
+        finally:
+            s.close()
+    ctx.close()
