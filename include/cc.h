@@ -88,10 +88,15 @@ int cc_version(void);
    regrouped hooks would apply (none does with CC_F_NO_SPLIT).
    - The filter sorts the entries by the ranges of 2^19 vertices of both
      endpoints, so that both membership tests read LDS. Whole solves and the
-     CC_F_ZROOT hook take it from n = 1,179,649 to 2^28 with at least one entry
-     per vertex and 2^20 entries (2^24 beyond 22 ranges), below 2^32; on the
-     plain path the bitmap is that of the giant component a sample of the
-     entries shows. If the sample shows none, the device takes the direct hook.
+     CC_F_ZROOT hook take it from n = 1,179,649 to 2^28, below 2^32 entries: up to
+     22 ranges in one pass, with 2^20 entries and one per vertex; beyond in two,
+     with 2^24 entries and one per vertex, but for 23 to 256 ranges with 5/2 per
+     vertex on the plain path, and with CC_F_ZROOT any number per vertex. On the
+     plain path the bitmap is that of the giant component a sample of the entries
+     shows. If the sample shows none, the device hooks the regrouped entries
+     without a bitmap from 2^24 entries on, up to 256 ranges and from 4 (8 with
+     CC_F_ZROOT), and takes the direct hook elsewhere; zero-root lists of 23 to 256
+     ranges below 5/4 entries per vertex are filtered in any case.
    - The plain cc_hook takes the entries grouped by their first endpoint's range
      (4 <= ceil(n / 2^19) <= 256, 2^24 <= m < 2^32), so that those parent reads
      stay in L2.
@@ -138,7 +143,9 @@ typedef struct cc_ctx_opts {
    root selection state, a sampled-degree hash table, per-block minima) and
    pinned host staging, and grows on demand what larger solves need: the
    zero-root membership bitmap (n/8 bytes), the buffers of the regrouped hooks
-   (5 to 11 bytes per entry, 6 per entry more with CSR input), the CSR tile tables and the batch work list.
+   (5 bytes per entry for one partition pass, 11 for two, on COO and CSR input; 6 for
+   the plain cc_hook; plain whole solves n/8 bytes more), the CSR tile tables and the
+   batch work list. cc_solve_u64 adds 4n bytes where it solves in 32 bits.
    A buffer that work captured into a graph has used is kept until cc_destroy, also
    when a larger solve outgrows it, so such a graph may be replayed as long as the
    context lives. Under capture nothing grows: a solve whose regrouped hook would
@@ -216,10 +223,12 @@ int cc_solve_async(cc_ctx* ctx, uint64_t n, uint64_t m, const uint32_t* edge_lis
    with the longest row, ties to the lowest ID (Algorithm 4 reads degrees from
    CSR; CC_F_ZROOT_HINT uses zroot_hint instead), and the Initial Push covers
    its whole row. Rows are hooked in order, so runs of entries share their
-   first endpoint's parent reads; within the limits of CC_F_NO_TILE's
-   regrouped hooks, the zero-root solve instead takes the regrouped hook with
-   the rows of each vertex range as its first-endpoint buckets (CC_F_NO_TILE
-   keeps the direct one).
+   first endpoint's parent reads. The zero-root solve instead reads the rows as
+   entries of the whole-bitmap filter (the sizes named at CC_F_NO_SPLIT) or of the
+   one-pass filter (CC_F_NO_TILE's sizes, with 3/2 entries per vertex), or takes the
+   two-pass filter with the rows of each vertex range as its first-endpoint buckets:
+   from 23 ranges on, and from 12 where the longest row is 64 times the mean.
+   CC_F_NO_TILE keeps the direct hook beyond the whole bitmap's sizes.
      n        vertices, < 2^32
      offsets  device, n+1 uint64, non-decreasing, offsets[0] = 0; m =
               offsets[n] is read back (the call waits for `stream` once, before
@@ -242,6 +251,10 @@ int cc_solve_csr(cc_ctx* ctx, uint64_t n, const uint64_t* offsets, const uint32_
             CC_ERANGE at cc_sync and are skipped)
      L      device, n uint64, written: L_v = smallest ID of v's component
      flags  CC_F_NO_SPLIT and CC_F_SYMMETRIC (anything else: CC_EINVAL)
+   Below 2^28 vertices, lists that the filters of CC_F_NO_TILE or the whole bitmap
+   take are solved in a 32-bit parent array of the context's scratch (4n bytes, and 5
+   or 11 per entry), whose growth waits for `stream`; without CC_F_NO_SPLIT, and where
+   the scratch can be had.
    Asynchronous on `stream`; status through `st` (cc_status_wait) when it is
    not NULL, else through cc_sync. */
 int cc_solve_u64(cc_ctx* ctx, uint64_t n, uint64_t m, const uint64_t* edges, uint64_t* L,
@@ -436,8 +449,9 @@ int cc_unpack_ids(cc_ctx* ctx, uint64_t count, const uint8_t* in, uint32_t id_by
  * library's device image; each device holds its own copy until the process
  * ends, located at the first call on that device. Every call on a device
  * shares that device's array, so calls that overlap on one device race: queue
- * them on one stream. The hooks are the direct ones (the regrouped hooks'
- * buffers grow with m).
+ * them on one stream. Small graphs are solved in one launch and arrays up to
+ * 1,179,648 vertices by the whole bitmap in LDS, as in cc_solve_async; the other
+ * hooks are the direct ones (the regrouped hooks' buffers grow with m).
  *   n, m, edge_list, L, zroot_hint, stream   as for cc_solve_async
  *   flags   CC_F_ZROOT, CC_F_ZROOT_HINT, CC_F_NO_SPLIT, CC_F_NO_TILE,
  *           CC_F_SYMMETRIC (CC_F_ZROOT_EXACT or others: CC_EINVAL)

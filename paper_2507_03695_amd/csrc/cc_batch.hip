@@ -484,7 +484,8 @@ __global__ __launch_bounds__(kBatchBlock) void k_solve_small(const int32_t* edge
 }
 
 // Sizes at which one workgroup (1.3 G entries/s) beats the separate launches. Whole
-// solves, launches against this (us): R-MAT n = 1,500, 12,000 entries plain 45
+// solves, launches against this (us, this without its leading coherence point, 2 us
+// more): R-MAT n = 1,500, 12,000 entries plain 45
 // against 26 on its own, 56 against 36 through cc_solve with its waits; with the
 // zero root 75 against 25; R-MAT n = 16,000, 60,000 entries 56 against 48; ER n =
 // 300, 300 entries 19 against 9. The counts of the zero root take as much LDS again

@@ -966,7 +966,7 @@ static int hook_by_bits(Slot* s, uint64_t n, uint64_t m, EdgeList E, uint32_t* P
             return rc;
         // Below 5/4 entries per vertex half of a uniform list shows no giant
         // component even where the whole has one, so the filter takes every list
-        // (ER n = 67 M, 60 M entries: 7.6 ms filtered, 8.6 direct, 9.2 sampled and
+        // (ER n = 67 M, 60 M entries: 7.1 ms filtered, 8.6 direct, 9.2 sampled and
         // then direct; a twentieth of R-MAT-26, n = 71 M, 52 M entries: 1.4, 2.7). The
         // sample only decides whether the survivors' bits are tested again. Beyond
         // 256 slices a larger sample's marks are worth more (a sixteenth of R-MAT-28:

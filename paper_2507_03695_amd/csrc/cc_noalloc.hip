@@ -11,7 +11,8 @@
 // hipGetSymbolAddress, taken once per device with that device current, and only
 // that address is used. The regrouped hooks (whose buffers grow with the entry
 // count) and the exact-degree zero root (a count per vertex) are not available
-// here; the direct hooks handle every size.
+// here. Small graphs take the one-launch solve and arrays up to lds_bits_max_n() the
+// whole bitmap in LDS, as everywhere; the direct hooks handle every other size.
 #include <mutex>
 
 #include "cc_internal.h"

@@ -1,10 +1,13 @@
-// cc_tiled.hip — the zero-root hook with both membership tests in LDS.
+// cc_tiled.hip — the regrouped hooks: the filter with both membership tests in LDS,
+// against the bitmap of the zero root's component or, on a plain whole solve, of the
+// giant component's; and hooks of the regrouped entries without a bitmap.
 //
 // The plain bitmap hook pays two random L2/MALL line reads per entry (the
 // bitmap is n/8 bytes, 8.5 MB at RMAT-26, twice one XCD's L2). Here the
 // entries are first regrouped so that each workgroup sees only entries whose
 // endpoints fall in two fixed vertex ranges ("slices" of 2^kSliceBits
-// vertices), and it holds the bitmap words of both slices in LDS:
+// vertices), and it holds the bitmap words of both slices in LDS. Up to 22 slices
+// one pass makes the (a, b) tiles (k_tile_part, below); beyond:
 //
 //  1. k_t1_part   — every chunk of kC1 entries is sorted in LDS by the slice
 //                   of its first endpoint (a) and written back in place order;
@@ -16,11 +19,13 @@
 //  4. k_t2_part   — every kC2-entry piece of an a-bucket is gathered from its
 //                   segments, sorted in LDS by the slice of the second
 //                   endpoint (b) and written contiguously, with its b-runs.
-//  5. k_t3_filter — one workgroup per (a, b): both slices' bitmap words in
+//  5. k_t3_filter — one workgroup per (a, few b): both slices' bitmap words in
 //                   LDS; an entry with both endpoints marked is dropped, one
 //                   with a single marked endpoint marks the other (LDS and
 //                   global) and is dropped, the rest go to a survivor list.
 //  6. k_t4_hook   — the ordinary hook over the survivor list.
+// Without a giant component: k_t2_hookplain hooks the buckets of 1-3, k_tile_hook the
+// one-pass tiles.
 //
 // After this step the components are given by P and the bitmap together
 // (k_compress / k_resolve in cc_kernels.hip read both).
@@ -1284,12 +1289,12 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
 
 // ---- few slices: one pass over (a, b) ------------------------------------------------------
 // With at most kMaxOnePass slices the (a, b) tiles are few enough (R * R <= 484)
-// that one LDS sort of an 8192-entry chunk leaves runs of 17 entries or more per
-// tile, so the second partition pass (11 B per entry read and written, and its
-// tables) is not needed: 8 B read, 5 written, 5 read per entry in all. The tiles
-// take the filter's form at once: chunk c's entries at [c * kC2, ...) sorted by
-// tile, run2T[d * nch + c] the start of tile d's run. The filter splits each
-// tile's chunks over `parts` workgroups.
+// that one LDS sort of an 8192-entry chunk leaves runs of 17 entries per tile, on
+// average and on uniform lists (others leave shorter and empty ones), so the second
+// partition pass (11 B per entry read and written, and its tables) is not needed: 8 B
+// read, 5 written, 5 read per entry in all. The tiles take the filter's form at once:
+// chunk c's entries at [c * kC2, ...) sorted by tile, run2T[d * nch + c] the start of
+// tile d's run.
 constexpr int kMaxOnePass = 22;
 constexpr int kMaxTiles = kMaxOnePass * kMaxOnePass;
 
@@ -1366,9 +1371,10 @@ __global__ __launch_bounds__(256) void k_tile_count(const uint16_t* __restrict__
 // each. The tiles are one index space (a tile kVisit wider than its entries, the time
 // its run table takes to read) cut into parts, one per workgroup: kHookPart, or wider
 // on long lists (kHookParts of them; 16,000 workgroups that leave at a shut gate take 9
-// us, these 4). Consecutive workgroups go
-// to the XCDs in turn, so part numbers are dealt so that an XCD's workgroups take
-// neighbouring parts and share the slices in its L2.
+// us, these 4). Consecutive workgroups go to the XCDs in turn, so part numbers are dealt
+// so that an XCD's workgroups take neighbouring parts and share the slices in its L2.
+// Bound by the reads of the parents: 12 parts dealt over n = 4 M, 64 M entries, whole
+// solve 1.59 ms; by first-endpoint buckets, without the sample, 2.00.
 constexpr uint32_t kHookPart = 8192, kHookParts = 4096;
 constexpr uint32_t kVisit = 1024;
 constexpr int kXcds = 8;
@@ -1478,7 +1484,7 @@ bool tiled_eligible(uint64_t n, uint64_t m, bool zr) {
 // entry per vertex a plain solve's component is seldom worth it; with a zero root
 // two passes take such lists too, since a share of a skewed graph is one (a
 // twentieth of R-MAT-26, n = 71 M, 52 M entries: 1.4 ms against 2.7 direct; ER
-// n = 67 M, 60 M entries 7.6 and 8.6, pieces of a path 6.0 and 3.4). A plain solve
+// n = 67 M, 60 M entries 7.1 and 8.6, pieces of a path 5.8 and 3.4). A plain solve
 // takes two passes from 5/2 entries per vertex where it has the buckets too (ER
 // n = 67 M, 134 M entries 10.1 ms against 9.3 by buckets, 200 M 10.5 and 11.9).
 // Two passes start at the size their fixed costs (16 launches) are worth; one pass was faster from 2^20 entries on
