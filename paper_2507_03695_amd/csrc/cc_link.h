@@ -186,15 +186,15 @@ __device__ __forceinline__ void queue_hook(WaveQueues& q, int lane, const Settle
     q.ln = 0;
     wave_order();
 }
-// DIRECT: hook only notes the entry, so it is called at once.
-template <bool DIRECT = false, class Settle, class Hook>
+// direct: hook only notes the entry, and is called at once.
+template <class Settle, class Hook>
 __device__ __forceinline__ void queue_settle(WaveQueues& q, int lane, const Settle& settle,
-                                             const Hook& hook) {
+                                             const Hook& hook, bool direct = false) {
     wave_order();
     const bool act = (uint32_t)lane < q.pn;
     const u32x2 x = act ? q.pq[lane] : u32x2{0u, 0u};
     const bool keep = act && settle(x);
-    if (DIRECT) {
+    if (direct) {
         q.pn = 0;
         if (keep) hook(x);
         wave_order();
@@ -210,21 +210,22 @@ __device__ __forceinline__ void queue_settle(WaveQueues& q, int lane, const Sett
     }
     wave_order();
 }
-template <bool DIRECT = false, class Settle, class Hook>
+template <class Settle, class Hook>
 __device__ __forceinline__ void queue_push(WaveQueues& q, int lane, bool pend, u32x2 x,
-                                           const Settle& settle, const Hook& hook) {
+                                           const Settle& settle, const Hook& hook,
+                                           bool direct = false) {
     const uint64_t ball = __ballot(pend);
     if (!ball) return;
     const uint32_t c = (uint32_t)__popcll(ball);
-    if (q.pn + c > kQueueCap) queue_settle<DIRECT>(q, lane, settle, hook);
+    if (q.pn + c > kQueueCap) queue_settle(q, lane, settle, hook, direct);
     if (pend) q.pq[q.pn + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull))] = x;
     q.pn += c;
 }
-template <bool DIRECT = false, class Settle, class Hook>
+template <class Settle, class Hook>
 __device__ __forceinline__ void queue_finish(WaveQueues& q, int lane, const Settle& settle,
-                                             const Hook& hook) {
-    if (q.pn) queue_settle<DIRECT>(q, lane, settle, hook);
-    if (!DIRECT && q.ln) queue_hook(q, lane, settle, hook);
+                                             const Hook& hook, bool direct = false) {
+    if (q.pn) queue_settle(q, lane, settle, hook, direct);
+    if (q.ln) queue_hook(q, lane, settle, hook);
 }
 
 }  // namespace ccm

@@ -860,17 +860,20 @@ __device__ __forceinline__ void t3_flush(const uint32_t* w, uint32_t* zbits, uin
 //              2^16 entries on R-MAT-26, and hooking its rest at its end
 //              would leave the CU waiting: filter 4.2 ms against 2.9 + 0.4)
 //  kManyRuns   the same beyond kFewSlices slices, where a tile is small: marks go
-//              to the global bitmap one by one (t3_flush's pass over a slice costs
-//              as much as some ten thousand of them)
-//  kSparseRuns the same on other lists of fewer than kFlushEntries entries to a
-//              workgroup: the others see the marks at once, and the entries that are
-//              kept, which are most, are written when first settled (zero root, ER n =
-//              67 M, 60 M entries: 7.6 ms as kFullRuns, 7.1 so; a twentieth of R-MAT-26
-//              2.4 and 1.9). Where marks settle most entries, a second look when the
-//              second queue is full saves more (R-MAT-24 rows, 60 M entries, 121,000 to
-//              a workgroup: survivor hook 65 us with it, 118 without).
-enum FilterMode { kMarkTiles, kFullTiles, kFullRuns, kManyRuns, kSparseRuns };
-constexpr uint64_t kFlushEntries = 32768;
+//              to the global bitmap one by one, where the others see them at once
+//              (t3_flush's pass over a slice costs as much as some ten thousand)
+//  kMixedRuns  the same on lists whose workgroups may be small: those of fewer than
+//              kFlushEntries entries mark one by one (zero root, ER n = 67 M, 60 M
+//              entries 7.6 ms with flushes, 7.1 so; a twentieth of R-MAT-26 2.4 and
+//              1.9), the others flush: a share of a larger graph fills few first slices
+//              (16 shares of R-MAT-26: 21.3 ms with flushes, 27.4 one by one). The small
+//              ones also write the entries that are kept, which are most, when they are
+//              first settled; where marks settle most, a second look when the second
+//              queue is full saves more (R-MAT-24 rows, 60 M entries, 121,000 to a
+//              workgroup: survivor hook 65 us with it, 118 without). The choice in the
+//              kernel spills three registers, so long lists take kFullRuns.
+enum FilterMode { kMarkTiles, kFullTiles, kFullRuns, kManyRuns, kMixedRuns };
+constexpr uint32_t kFlushEntries = 32768;
 constexpr uint32_t kMarkPart = 8;
 constexpr uint32_t kTileCost = 8192;  // entries' worth of a tile's fixed time (8 us)
 
@@ -902,7 +905,6 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
     // copies of any one slice and see each other's marks through the global
     // bitmap sooner. (a, bg) = (i mod R, (i div R + a) mod nbg) is a bijection.
     const int kB = TILES ? 1 : b_per_block(R);
-    constexpr bool one_by_one = MODE == kManyRuns || MODE == kSparseRuns, direct = MODE == kSparseRuns;
     const uint32_t nbg = ((uint32_t)R + kB - 1) / kB;
     int a = (int)(blockIdx.x % (uint32_t)R);
     const int bg = (int)((blockIdx.x / (uint32_t)R + (uint32_t)a) % nbg);
@@ -958,6 +960,8 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         oh = sh + wgoff[wi];
         cap = (uint32_t)(wgoff[wi + 1] - wgoff[wi]);
     }
+    const bool direct = MODE == kMixedRuns && cap < kFlushEntries;
+    const bool one_by_one = MODE == kManyRuns || direct;
     constexpr int PER = kSliceWords / kHook3Block;       // 16 words per thread per slice
     auto load_slice = [&](uint32_t* dst, int slice) {
         const uint64_t w0 = (uint64_t)slice * kSliceWords;
@@ -1098,7 +1102,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                     if (MODE == kMarkTiles) {
                         if (h && !both) (void)settle(x);
                     } else {
-                        queue_push<direct>(q, lane, h && !both, x, settle, hook);
+                        queue_push(q, lane, h && !both, x, settle, hook, direct);
                     }
                 }
                 continue;
@@ -1146,7 +1150,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
                     if (MODE == kMarkTiles) {
                         if (pend) (void)settle(x);
                     } else {
-                        queue_push<direct>(q, lane, pend, x, settle, hook);
+                        queue_push(q, lane, pend, x, settle, hook, direct);
                     }
                 }
                 if (!more) break;
@@ -1155,7 +1159,7 @@ __global__ __launch_bounds__(kHook3Block) void k_t3_filter(L2Buf tmp2,
         }
         // this slice's pending entries are settled before the next slice's
         // bitmap replaces it
-        if (MODE != kMarkTiles) queue_finish<direct>(q, lane, settle, hook);
+        if (MODE != kMarkTiles) queue_finish(q, lane, settle, hook, direct);
         if (b != a && !one_by_one) {
             __syncthreads();
             t3_flush(sb, zbits, (uint64_t)b * kSliceWords, words);
@@ -1681,9 +1685,9 @@ static int filter_runs(int R, uint64_t m, uint64_t nch2, L2Buf tmp2, uint16_t* r
     if ((rc = cohere(stream))) return rc;
     k_t3_offsets<<<(uint32_t)R, 64, 0, stream>>>(wgcnt, R, base2, wgoff, gate);
     if ((rc = cohere(stream))) return rc;
-    auto filter = R > kFewSlices            ? &k_t3_filter<kManyRuns>
-                  : m < kFlushEntries * nwg ? &k_t3_filter<kSparseRuns>
-                                            : &k_t3_filter<kFullRuns>;
+    auto filter = R > kFewSlices                    ? &k_t3_filter<kManyRuns>
+                  : m < 2ull * kFlushEntries * nwg ? &k_t3_filter<kMixedRuns>
+                                                   : &k_t3_filter<kFullRuns>;
     filter<<<nwg, kHook3Block, 0, stream>>>(tmp2, run2, nch2, R, nullptr, base2, cbase, zbits, words, P,
                                             sw, sh, wgoff, wgcnt, st, gate);
     if ((rc = cohere(stream))) return rc;

@@ -523,13 +523,17 @@ def test_few_tiles_without_a_giant_component(ctx):
         assert_same_labels(to_host_u32(by_steps(ctx, ed, n)), want, f"first in {lo} steps")
 
 
-@pytest.mark.parametrize("n,m", [(60 * SLICE, (1 << 24) + 1), (36 * SLICE + 7, 23_035_903), (36 * SLICE + 7, 23_035_904)])
+@pytest.mark.parametrize("n,m", [(60 * SLICE, (1 << 24) + 1), (36 * SLICE + 7, 23_035_903), (36 * SLICE + 7, 23_035_904),
+                                 (22 * SLICE + 5, 18_087_935), (22 * SLICE + 5, 18_087_936)])
 def test_few_entries_to_a_workgroup(ctx, n, m):
     """Two passes with few entries to a workgroup of the filter, and each side of 32,768
-    (37 slices: 37 * 19 workgroups): nearly all entries are kept, or a skewed list's marks
-    settle most."""
-    for kind in ("er", "rmat", "paths"):
-        e = graph(kind, n, m, n + m)
+    (37 slices: 37 * 19 workgroups) and of twice that (23 slices: 23 * 12) on average:
+    nearly all entries are kept, or a skewed list's marks settle most; a share's first
+    endpoints lie in few slices, whose workgroups have many."""
+    for kind in ("er", "rmat", "paths", "share"):
+        e = graph("rmat" if kind == "share" else kind, n, m, n + m)
+        if kind == "share":
+            e[:, 0] %= 2 * SLICE + 77
         want = oracle.cc_labels(n, e)
         ed = to_dev(e)
         off, adj = rows_of(e, n)
