@@ -36,8 +36,8 @@ PEAK_HBM_GBS = 8000.0
 # each counter scaled by what it reads for a 4 GiB device copy. Keyed by
 # (workload, variant); valid only for the kernel sources they were taken on.
 TRAFFIC = {
-    ("rmat26", "zroot"): {"bytes": 47065756685,
-                          "src_sha256": "4ea6f64bbddbe1e0028426c37be55794a159dc522e21c1cf68ded0243d2ad065"},
+    ("rmat26", "zroot"): {"bytes": 47129222424,
+                          "src_sha256": "3837bb869752c64fa85303879b632b95ee43bf917188405f4ad7b2acf6f7d7a0"},
 }
 
 HOOK_KERNELS = {
