@@ -1375,11 +1375,11 @@ __global__ __launch_bounds__(256) void k_tile_count(const uint16_t* __restrict__
 // each. The tiles are one index space (a tile kVisit wider than its entries, the time
 // its run table takes to read) cut into parts, one per workgroup: kHookPart, or wider
 // on long lists (kHookParts of them; 16,000 workgroups that leave at a shut gate take 9
-// us, these 4). Consecutive workgroups go to the XCDs in turn, so part numbers are dealt
+// us, these 5). Consecutive workgroups go to the XCDs in turn, so part numbers are dealt
 // so that an XCD's workgroups take neighbouring parts and share the slices in its L2.
 // Bound by the reads of the parents: 12 parts dealt over n = 4 M, 64 M entries, whole
 // solve 1.59 ms; by first-endpoint buckets, without the sample, 2.00.
-constexpr uint32_t kHookPart = 8192, kHookParts = 4096;
+constexpr uint32_t kHookPart = 8192, kHookParts = 8192;
 constexpr uint32_t kVisit = 1024;
 constexpr int kXcds = 8;
 constexpr int kTileEPT = 4;
