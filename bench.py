@@ -36,8 +36,8 @@ PEAK_HBM_GBS = 8000.0
 # each counter scaled by what it reads for a 4 GiB device copy. Keyed by
 # (workload, variant); valid only for the kernel sources they were taken on.
 TRAFFIC = {
-    ("rmat26", "zroot"): {"bytes": 47129222424,
-                          "src_sha256": "3837bb869752c64fa85303879b632b95ee43bf917188405f4ad7b2acf6f7d7a0"},
+    ("rmat26", "zroot"): {"bytes": 47124486839,
+                          "src_sha256": "a82ab159f9868944d80bbbbc53ae8ccb65c5c6dadf2fe191a0e74074d4a31960"},
 }
 
 HOOK_KERNELS = {
