@@ -1279,8 +1279,8 @@ __global__ __launch_bounds__(kHook4Block) void k_t4_hook(const uint32_t* __restr
         uint32_t pu[kHook4EPT], pv[kHook4EPT];
 #pragma unroll
         for (int k = 0; k < kHook4EPT; ++k) {
-            pu[k] = h[k] ? P[u[k]] : 0u;
-            pv[k] = h[k] ? P[v[k]] : 0u;
+            pu[k] = P[h[k] ? u[k] : 0u];
+            pv[k] = P[h[k] ? v[k] : 0u];
         }
 #pragma unroll
         for (int k = 0; k < kHook4EPT; ++k) {
