@@ -36,8 +36,8 @@ PEAK_HBM_GBS = 8000.0
 # each counter scaled by what it reads for a 4 GiB device copy. Keyed by
 # (workload, variant); valid only for the kernel sources they were taken on.
 TRAFFIC = {
-    ("rmat26", "zroot"): {"bytes": 47124486839,
-                          "src_sha256": "a82ab159f9868944d80bbbbc53ae8ccb65c5c6dadf2fe191a0e74074d4a31960"},
+    ("rmat26", "zroot"): {"bytes": 47127737985,
+                          "src_sha256": "853a2ffb9bd02dd6f8ea1a185f7fbbeb556ed8867c8c918aa4a2601aee7257b6"},
 }
 
 HOOK_KERNELS = {
